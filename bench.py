@@ -185,7 +185,7 @@ FAMILY_SOURCE = {
     "inject": ["gst_plan_kernels.hip"], "fill": ["gst_plan_kernels.hip"], "grad_gemm": ["gst_plan_kernels.hip"],
     "reduce": ["gst_plan_kernels.hip"], "tiles_3q_fwd": ["gst_kernels64.hip"], "tiles_3q_bwd": ["gst_kernels64.hip"],
     "readout_3q": ["gst_kernels64.hip"], "gemm_3q": ["gst_kernels64.hip"],
-    "reduce_3q": ["gst_kernels64.hip", "gst_kernels.hip"], "chain_3q": ["gst_kernels64.hip"],
+    "reduce_3q": ["gst_kernels64.hip", "gst_kernels.hip"], "chain_3q": ["gst_kernels64.hip", "gst_sched.hip"],
     "tiles_2q": ["gst_batch.hip"], "tiles_1q": ["gst_lane1q.hip"], "tiles_reduce": ["gst_batch.hip"],
 }
 
@@ -1062,10 +1062,10 @@ def algorithmic_flops(family, D, M, S, sum_len, info):
     if info is None:
         if family in ("leaf", "tiles_2q", "tiles_1q"):
             return 6.0 * D * D * sum_len + 6.0 * D * M * S
-        if family == "chain_3q":   # forward and adjoint products, readout, seed, dE
-            return 4.0 * D * D * sum_len + 6.0 * D * M * S
-        if family == "gemm_3q":    # dG_k = sum b f^T
-            return 2.0 * D * D * sum_len
+        if family == "chain_3q":   # two launches: the forward sweep, the adjoint sweep with dG_k += b f^T
+            return 3.0 * D * D * sum_len
+        if family == "readout_3q":   # readout, seed and effect gradient of every sequence
+            return 6.0 * D * M * S
         return 0.0
     if info.get("grouped"):
         # three qubits, grouped chains: every trie node is one step of its

@@ -299,6 +299,15 @@ static int64_t tile_seqs_for(int64_t S) {
   return 16 * std::min<int64_t>(std::max<int64_t>(per, 1), 8);
 }
 
+// A grouped schedule on the device (gst_sched.hip).
+struct Schedule {
+  int tile_seqs = 0;
+  int64_t n_tiles = 0, n_entries = 0;
+  DevBuf buf;
+  int64_t* tile_ptr = nullptr;
+  uint32_t* entries = nullptr;
+};
+
 struct gst_req {
   gst_ctx* ctx = nullptr;
   int n_qubits = 0, D = 0, M = 0, K = 0;
@@ -316,14 +325,12 @@ struct gst_req {
   unsigned* queue = nullptr;            // device: work-queue counter [64] + nonpos counter
   int64_t n_steps = 0;
   // three-qubit requests (D = 64)
-  int64_t tile_seqs64 = 0, n_tiles64 = 0, n_chunks64 = 0;
-  int64_t* pos64 = nullptr;             // step positions grouped by gate
-  int64_t* chunk_beg64 = nullptr;
-  int64_t* chunk_end64 = nullptr;
-  int64_t* gate_chunk_ptr64 = nullptr;  // [K + 1]
-  double* tile_slab64 = nullptr;        // [n_tiles64][1 + 64 + 64 M]
-  double* chunk_slab64 = nullptr;       // [n_chunks64][4096]
-  double* part64 = nullptr;             // scratch of the ordered tile reduction
+  // without shared prefixes: tiles of a grouped schedule
+  Schedule sched;
+  int readout_blocks64 = 0, blocks64 = 0;
+  int64_t* gate_chunk_ptr64 = nullptr;  // [K + 1]: the gates' ranges of the reverse workgroups' tiles
+  double* head64 = nullptr;             // [readout waves + reverse workgroups][1 + 64 + 64 M]
+  double* part64 = nullptr;             // scratch of the ordered head sum
   size_t eval_ws_bytes = 0;             // context workspace one evaluation with gradient needs
   DevicePlan plan;
   DevicePlan64 plan64;
@@ -331,6 +338,57 @@ struct gst_req {
   size_t resident_bytes = 0;
   int64_t n_tiles() const { return tile_q.empty() ? 0 : (int64_t)tile_q.size() - 1; }
 };
+
+// Workgroups of the three-qubit readout of n slots: a wave per group of 16.
+static int readout_blocks_of(const gst_ctx* ctx, int64_t n) {
+  const int64_t per = 16 * gst::READOUT64_WAVES;
+  return (int)std::min<int64_t>(std::max<int64_t>((n + per - 1) / per, 1),
+                                (int64_t)gst::readout64_blocks_per_cu() * ctx->n_cu);
+}
+
+// A three-qubit request without a plan: its head rows, and the context
+// workspace of an evaluation.
+static int head_rows64(const gst_req* r) { return r->readout_blocks64 * gst::READOUT64_WAVES + r->blocks64; }
+static size_t chain64_ws_bytes(const gst_req* r, bool want_grad) {
+  size_t d = (size_t)r->S * 64;
+  if (want_grad) d += (size_t)r->K * r->blocks64 * 4096 + (size_t)(r->sched.n_entries + 1) * gst::SCHED_COLS * 64;
+  return d * 8 + 256;
+}
+
+// The grouped schedule of a request's words: counted, then written (on the
+// null stream, like the request's uploads).
+static int build_schedule(gst_req* r) {
+  Schedule& d = r->sched;
+  DevBuf count;
+  int rc = count.reserve((size_t)(d.n_tiles + 1) * 8, nullptr);
+  if (rc) return rc;
+  gst::SchedBuild b{};
+  b.off = r->offsets;
+  b.gates = r->gates;
+  b.order = r->order;
+  b.S = r->S;
+  b.K = r->K;
+  b.tile_seqs = d.tile_seqs;
+  b.tile_n = reinterpret_cast<int64_t*>(count.p);
+  HIP_TRY(gst::launch_sched(b, d.n_tiles, nullptr));
+  std::vector<int64_t> ptr((size_t)d.n_tiles + 1, 0);
+  if (d.n_tiles > 0) HIP_TRY(hipMemcpy(ptr.data() + 1, count.p, (size_t)d.n_tiles * 8, hipMemcpyDeviceToHost));
+  for (int64_t t = 0; t < d.n_tiles; ++t) ptr[t + 1] += ptr[t];
+  d.n_entries = ptr[d.n_tiles];
+  Carver cv;
+  const size_t o_p = cv.take<int64_t>(ptr.size()), o_e = cv.take<uint32_t>((size_t)d.n_entries + 1);
+  rc = d.buf.reserve(cv.off, nullptr);
+  if (rc) return rc;
+  d.tile_ptr = reinterpret_cast<int64_t*>((char*)d.buf.p + o_p);
+  d.entries = reinterpret_cast<uint32_t*>((char*)d.buf.p + o_e);
+  HIP_TRY(hipMemcpy(d.tile_ptr, ptr.data(), ptr.size() * 8, hipMemcpyHostToDevice));
+  b.tile_n = nullptr;
+  b.tile_ptr = d.tile_ptr;
+  b.entries = d.entries;
+  HIP_TRY(gst::launch_sched(b, d.n_tiles, nullptr));
+  HIP_TRY(hipStreamSynchronize(nullptr));
+  return GST_OK;
+}
 
 struct gst_batch {
   gst_ctx* ctx = nullptr;
@@ -683,10 +741,7 @@ int upload_plan64(gst_req* r, gst::Plan64& P, const int32_t* counts_host) {
   for (int64_t i = 0; i < NC; ++i)
     if (P.chunk_end[i] - P.chunk_beg[i] > gst::GEMM64_TS_CHUNK_MAX) return GST_EINVAL;
   // the readout takes groups of 16 slots, a wave per group at a time
-  const int64_t n_groups = (P.n_slots + 15) / 16;
-  d.readout_blocks = (int)std::min<int64_t>(std::max<int64_t>((n_groups + gst::READOUT64_WAVES - 1) /
-                                                                  gst::READOUT64_WAVES, 1),
-                                            (int64_t)gst::readout64_blocks_per_cu() * r->ctx->n_cu);
+  d.readout_blocks = readout_blocks_of(r->ctx, P.n_slots);
   const int64_t n_waves = (int64_t)d.readout_blocks * gst::READOUT64_WAVES;
   const int64_t Pc = 1 + 64 + (int64_t)M * 64;
   Carver c;
@@ -1554,34 +1609,21 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   }
   std::vector<gst::BatchTile> tiles = gst::batch_tiles({&r->tile_q}, {&r->tile_cost}, {0});
   const int64_t Pw = gst::slab_width(D, n_outcomes, n_gates);
-  // three-qubit requests: tiles of 16 sequences for the chain kernel, and the
-  // step positions of each gate (ascending) cut into chunks for the
-  // gate-gradient kernel
-  std::vector<int64_t> pos64, cbeg64, cend64, gcp64;
+  // three-qubit requests without deep sharing: tiles of a grouped schedule, two
+  // per CU (there and back over the lengths) until the tiles are full
+  std::vector<int64_t> gcp64;
   // three-qubit lists with deep sharing: the grouped-chain plan instead
   gst::Plan64 p64;
   const bool use_p64 = D == 64 && S > 0 && gst::build_plan64(sl->offsets, sl->gate_idx, S, n_gates,
                                                               gst::Plan64Options(), &p64);
   if (D == 64 && !use_p64) {
-    r->tile_seqs64 = ctx->tune_tile[3] > 0 ? ctx->tune_tile[3] : 16;
-    r->n_tiles64 = (S + r->tile_seqs64 - 1) / r->tile_seqs64;
-    std::vector<int64_t> gp((size_t)n_gates + 1, 0);
-    for (int64_t t = 0; t < n_steps; ++t) gp[sl->gate_idx[t] + 1] += 1;
-    for (int k = 0; k < n_gates; ++k) gp[k + 1] += gp[k];
-    pos64.resize((size_t)n_steps);
-    std::vector<int64_t> fill(gp.begin(), gp.end() - 1);
-    for (int64_t t = 0; t < n_steps; ++t) pos64[fill[sl->gate_idx[t]]++] = t;
-    gcp64.assign((size_t)n_gates + 1, 0);
-    for (int k = 0; k < n_gates; ++k) {
-      gcp64[k] = (int64_t)cbeg64.size();
-      for (int64_t b = gp[k]; b < gp[k + 1]; b += gst::GEMM64_CHUNK) {
-        cbeg64.push_back(b);
-        cend64.push_back(std::min(b + gst::GEMM64_CHUNK, gp[k + 1]));
-      }
-    }
-    gcp64[n_gates] = (int64_t)cbeg64.size();
-    r->n_chunks64 = (int64_t)cbeg64.size();
-    r->eval_ws_bytes = (size_t)n_steps * 64 * 8 * 2 + 256;
+    const int64_t per = (S + 2 * ctx->n_cu - 1) / (2 * ctx->n_cu);
+    const int64_t want = ctx->tune_tile[3] > 0 ? ctx->tune_tile[3] : per;
+    r->sched.tile_seqs = (int)std::min<int64_t>(std::max<int64_t>(want, 1), gst::SCHED_CHAINS);
+    r->sched.n_tiles = (S + r->sched.tile_seqs - 1) / r->sched.tile_seqs;
+    r->blocks64 = (int)std::min<int64_t>(r->sched.n_tiles, ctx->n_cu);
+    r->readout_blocks64 = readout_blocks_of(ctx, S);
+    for (int k = 0; k <= n_gates; ++k) gcp64.push_back((int64_t)k * r->blocks64);
   }
   const int64_t Pc64 = 1 + 64 + (int64_t)n_outcomes * 64;
   Carver cv;
@@ -1589,12 +1631,9 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
                o_c = cv.take<int32_t>(counts_host ? S * n_outcomes : 1), o_ord = cv.take<int64_t>(S + 1),
                o_sl = cv.take<double>((size_t)std::max<int64_t>(r->n_tiles(), 1) * Pw),
                o_t = cv.take<gst::BatchTile>(tiles.size() + 1), o_q = cv.take<unsigned>(kQueueWords + 2),
-               o_p64 = cv.take<int64_t>(pos64.size() + 1), o_cb64 = cv.take<int64_t>(cbeg64.size() + 1),
-               o_ce64 = cv.take<int64_t>(cend64.size() + 1), o_gc64 = cv.take<int64_t>(gcp64.size() + 1),
-               o_ts64 = cv.take<double>((size_t)std::max<int64_t>(r->n_tiles64, 1) * (D == 64 ? Pc64 : 1)),
-               o_cs64 = cv.take<double>((size_t)std::max<int64_t>(r->n_chunks64, 1) * (D == 64 ? 4096 : 1)),
-               o_pt64 = cv.take<double>(D == 64 ? (size_t)gst::reduce_parts((int)std::max<int64_t>(r->n_tiles64, 1)) *
-                                                      Pc64 : 1);
+               o_gc64 = cv.take<int64_t>(gcp64.size() + 1),
+               o_hd64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)head_rows64(r.get()) * Pc64),
+               o_pt64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)gst::reduce_parts(head_rows64(r.get())) * Pc64);
   rc = r->data.reserve(cv.off + 256, ctx->stream);
   if (rc) return rc;
   char* base = reinterpret_cast<char*>(r->data.p);
@@ -1607,21 +1646,11 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   r->queue = reinterpret_cast<unsigned*>(base + o_q);
   r->n_steps = n_steps;
   if (D == 64) {
-    r->pos64 = reinterpret_cast<int64_t*>(base + o_p64);
-    r->chunk_beg64 = reinterpret_cast<int64_t*>(base + o_cb64);
-    r->chunk_end64 = reinterpret_cast<int64_t*>(base + o_ce64);
     r->gate_chunk_ptr64 = reinterpret_cast<int64_t*>(base + o_gc64);
-    r->tile_slab64 = reinterpret_cast<double*>(base + o_ts64);
-    r->chunk_slab64 = reinterpret_cast<double*>(base + o_cs64);
+    r->head64 = reinterpret_cast<double*>(base + o_hd64);
     r->part64 = reinterpret_cast<double*>(base + o_pt64);
-    if (!pos64.empty()) HIP_TRY(hipMemcpy(r->pos64, pos64.data(), pos64.size() * 8, hipMemcpyHostToDevice));
-    if (!cbeg64.empty()) {
-      HIP_TRY(hipMemcpy(r->chunk_beg64, cbeg64.data(), cbeg64.size() * 8, hipMemcpyHostToDevice));
-      HIP_TRY(hipMemcpy(r->chunk_end64, cend64.data(), cend64.size() * 8, hipMemcpyHostToDevice));
-    }
-    HIP_TRY(hipMemcpy(r->gate_chunk_ptr64, gcp64.data(), gcp64.size() * 8, hipMemcpyHostToDevice));
-    // an empty list has no tiles: its single partial row stays zero
-    if (r->n_tiles64 == 0) HIP_TRY(hipMemset(r->tile_slab64, 0, (size_t)Pc64 * 8));
+    if (!gcp64.empty())
+      HIP_TRY(hipMemcpy(r->gate_chunk_ptr64, gcp64.data(), gcp64.size() * 8, hipMemcpyHostToDevice));
   }
   if (!tiles.empty())
     HIP_TRY(hipMemcpy(r->tiles, tiles.data(), tiles.size() * sizeof(gst::BatchTile), hipMemcpyHostToDevice));
@@ -1643,7 +1672,12 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
     rc = upload_plan64(r.get(), p64, counts_host);
     if (rc) return rc;
   }
-  r->resident_bytes = r->data.bytes + r->plan.buf.bytes + r->plan64.buf.bytes;
+  if (r->sched.tile_seqs > 0) {
+    rc = build_schedule(r.get());
+    if (rc) return rc;
+    if (D == 64) r->eval_ws_bytes = chain64_ws_bytes(r.get(), true);
+  }
+  r->resident_bytes = r->data.bytes + r->plan.buf.bytes + r->plan64.buf.bytes + r->sched.buf.bytes;
   (void)o_off;
   *out = r.release();
   return GST_OK;
@@ -1759,75 +1793,81 @@ static int run_tiles(gst_req* r, const gst_gateset* th, int mode, const double* 
   return GST_OK;
 }
 
-// A three-qubit request: chain kernel over its tiles, gate-gradient kernel
-// over the recorded steps, ordered reduction.  `nonpos` (optional) receives
-// the count of p <= 0 with N > 0 of this evaluation.
+// A three-qubit request: the grouped-chain plan, or for lists without shared
+// prefixes the forward sweep of its grouped schedule, the readout of the final
+// states, the reverse sweep with the gate gradient, and the ordered sums.
+// `nonpos` (optional) receives the count of p <= 0 with N > 0 of this evaluation.
 static int run64(gst_req* r, const gst_gateset* th, int mode, const double* w, double* probs, double* objective,
                  double* grad, unsigned long long* nonpos = nullptr) {
   if (r->plan64.used) return run_plan64(r, th, mode, w, probs, objective, grad, nonpos);
   gst_ctx* ctx = r->ctx;
   const bool want_grad = grad != nullptr;
+  const bool need_head = objective || grad;
   unsigned long long* np = nonpos ? nonpos : reinterpret_cast<unsigned long long*>(r->queue + kQueueWords);
-  if (want_grad) {
-    // per-step records in the context workspace (calls on a context are stream ordered)
-    int rc = ctx->ws.reserve(r->eval_ws_bytes, ctx->stream);
-    if (rc) return rc;
-  }
-  double* rec_b = want_grad ? reinterpret_cast<double*>(ctx->ws.p) : nullptr;
-  double* rec_f = want_grad ? rec_b + (size_t)r->n_steps * 64 : nullptr;
+  // final states (in place: seeds), the gate tiles and the recorded states in
+  // the context workspace (calls on a context are stream ordered)
+  int rc = ctx->ws.reserve(chain64_ws_bytes(r, want_grad), ctx->stream);
+  if (rc) return rc;
+  double* fin = reinterpret_cast<double*>(ctx->ws.p);
+  double* dg = fin + (size_t)r->S * 64;
+  double* rec = dg + (size_t)r->K * r->blocks64 * 4096;
   HIP_TRY(gst::launch_queue_reset(r->queue, np, 1, ctx->stream));
+  const int64_t Pc = 1 + 64 + (int64_t)r->M * 64;
+  const int ro_rows = r->readout_blocks64 * gst::READOUT64_WAVES;
   gst::Chain64Launch a{};
-  a.M = r->M;
   a.K = r->K;
+  a.M = r->M;
   a.rho = th->rho;
-  a.E = th->effects;
   a.G = th->gates;
   a.off = r->offsets;
-  a.gates = r->gates;
   a.order = r->order;
-  a.counts = r->counts;
-  a.W = w;
-  a.probs = probs;
-  a.mode = mode;
-  a.want_grad = want_grad ? 1 : 0;
   a.S = r->S;
-  a.tile_seqs = (int)r->tile_seqs64;
-  a.n_tiles = r->n_tiles64;
-  a.queue = r->queue;
-  a.rec_b = rec_b;
-  a.rec_f = rec_f;
-  a.slab = r->tile_slab64;
-  a.status = ctx->status;
-  a.nonpos = np;
-  const int grid = (int)std::min<int64_t>(
-      r->n_tiles64, (int64_t)capped(gst::chain64_blocks_per_cu(r->K), ctx->tune_bpc[3]) * ctx->n_cu);
-  if (grid > 0) {
+  a.tile_seqs = r->sched.tile_seqs;
+  a.n_tiles = (int)r->sched.n_tiles;
+  a.tile_row = std::max(r->blocks64, 1);
+  a.tile_ptr = r->sched.tile_ptr;
+  a.entries = r->sched.entries;
+  a.rec_f = want_grad ? rec : nullptr;
+  a.fin = fin;
+  a.head = r->head64 + (size_t)ro_rows * Pc;
+  a.dg = dg;
+  if (a.n_tiles > 0) {
     ProfScope ps(ctx, FAM_CHAIN64);
-    HIP_TRY(gst::launch_chain64(a, grid, ctx->stream));
+    HIP_TRY(gst::launch_chain64_fwd(a, r->blocks64, ctx->stream));
   }
-  if (want_grad && r->n_chunks64 > 0) {
-    ProfScope ps(ctx, FAM_GEMM64);
-    gst::Gemm64Launch g{};
-    g.rec_b = rec_b;
-    g.rec_f = rec_f;
-    g.pos = r->pos64;
-    g.chunk_beg = r->chunk_beg64;
-    g.chunk_end = r->chunk_end64;
-    g.slab = r->chunk_slab64;
-    g.n_chunks = (int)r->n_chunks64;
-    HIP_TRY(gst::launch_gemm64(g, ctx->stream));
+  {
+    ProfScope ps(ctx, FAM_P64_READ);
+    gst::Readout64Launch ro{};
+    ro.M = r->M;
+    ro.E = th->effects;
+    ro.FA = fin;
+    ro.n_slots = r->S;
+    ro.slot_seq = r->order;
+    ro.counts = r->counts;
+    ro.W = w;
+    ro.probs = probs;
+    ro.mode = mode;
+    ro.want_grad = want_grad ? 1 : 0;
+    ro.INJ = fin;  // a wave reads its sixteen states before it writes their seeds
+    ro.slab = need_head ? r->head64 : nullptr;
+    ro.status = ctx->status;
+    ro.nonpos = np;
+    HIP_TRY(gst::launch_readout64(ro, r->readout_blocks64, ctx->stream));
   }
-  if (objective || grad) {
+  if (want_grad && a.n_tiles > 0) {
+    ProfScope ps(ctx, FAM_CHAIN64);
+    HIP_TRY(gst::launch_chain64_bwd(a, r->blocks64, ctx->stream));
+  }
+  if (need_head) {
     ProfScope ps(ctx, FAM_REDUCE64);
-    // [objective | rho | E] from the tile partials (two ordered stages) ...
-    const int64_t Pc = 1 + 64 + (int64_t)r->M * 64;
-    HIP_TRY(gst::launch_reduce(r->tile_slab64, (int)std::max<int64_t>(r->n_tiles64, 1), Pc, objective, grad,
-                               nullptr, 64, r->part64, ctx->stream));
-    // ... and the gate columns from the chunk partials
+    // [objective | rho | E] from the head rows (two ordered stages) ...
+    HIP_TRY(gst::launch_reduce(r->head64, ro_rows + (want_grad ? r->blocks64 : 0), Pc, objective, grad, nullptr, 64,
+                               r->part64, ctx->stream));
+    // ... and the gate columns from the reverse workgroups' sums
     gst::Reduce64Launch red{};
     red.M = r->M;
     red.K = r->K;
-    red.chunk_slab = r->chunk_slab64;
+    red.chunk_slab = dg;
     red.gate_chunk_ptr = r->gate_chunk_ptr64;
     red.grad = grad;
     red.nonpos = np;

@@ -241,42 +241,47 @@ hipError_t launch_queue_reset(unsigned* q, unsigned long long* req_nonpos, int n
 int batch_reduce_chunks(int64_t n_tiles);
 hipError_t launch_batch_reduce(const BatchReduce& a, int n_items, int max_chunks, hipStream_t stream);
 
-// Three-qubit gate sets (D = 64): one chain per wave, the gate set in LDS,
-// per-step records for the gate gradient (see gst_kernels64.hip).
-constexpr int CHAIN64_WAVES = 8;        // waves per workgroup of the chain kernel
-constexpr int64_t GEMM64_CHUNK = 8192;  // positions per chunk of the gate-gradient kernel
-struct Chain64Launch {
-  int M, K;
-  const double* rho;        // [64]
-  const double* E;          // [M][64]
-  const double* G;          // [K][64][64]
-  const int64_t* off;       // [S+1]
-  const uint8_t* gates;     // [sum L]
-  const int64_t* order;     // sequences by length, descending
-  const int32_t* counts;    // [S][M] (MODE_LOGLIK)
-  const double* W;          // [S][M] (MODE_VJP)
-  double* probs;            // [S][M] or null
-  int mode, want_grad;
+// Grouped schedules (gst_sched.hip): tiles of up to 16 consecutive chains of a
+// length-sorted order.  An entry advances up to four chains by one gate, and
+// entries 2m and 2m + 1 (a round) advance different chains: bits
+// 6r .. 6r + 5 hold, for column r, the chain's index in the tile times two plus
+// the parity of its step (chain 16: no chain), bits 24..27 the gate.  Tile t's
+// entries are tile_ptr[t] .. tile_ptr[t + 1], padded to a multiple of
+// SCHED_ALIGN with entries without chains.
+constexpr int SCHED_CHAINS = 16, SCHED_COLS = 4, SCHED_ALIGN = 4;
+constexpr uint32_t SCHED_NONE = (2u * SCHED_CHAINS) * (1u | 1u << 6 | 1u << 12 | 1u << 18);
+struct SchedBuild {
+  const int64_t* off;
+  const uint8_t* gates;
+  const int64_t* order;      // sequences by length, descending
   int64_t S;
-  int tile_seqs;            // sequences per tile (consecutive in `order`)
-  int64_t n_tiles;
-  unsigned* queue;          // tile counter, zero before the launch
-  double* rec_b;            // [sum L][64]: adjoint after each step (want_grad)
-  double* rec_f;            // [sum L][64]: state before each step (want_grad)
-  double* slab;             // [n_tiles][1 + 64 + 64 M]
-  unsigned long long* status;
-  unsigned long long* nonpos;
+  int K;
+  int tile_seqs;             // chains per tile (<= SCHED_CHAINS)
+  int64_t* tile_n;           // first pass (entries = null): the entries of each tile
+  const int64_t* tile_ptr;   // second pass
+  uint32_t* entries;
 };
-struct Gemm64Launch {
-  const double* rec_b;
-  const double* rec_f;
-  const int64_t* row_b;      // optional: rows of rec_b and rec_f of each record (else pos for both)
-  const int64_t* row_f;
-  const int64_t* pos;        // step positions grouped by gate, ascending within a gate
-  const int64_t* chunk_beg;  // [n_chunks] ranges in pos (one gate each)
-  const int64_t* chunk_end;
-  double* slab;              // [n_chunks][4096]
-  int n_chunks;
+hipError_t launch_sched(const SchedBuild& a, int64_t n_tiles, hipStream_t stream);
+
+// Three-qubit lists without shared prefixes (D = 64): tiles of a grouped
+// schedule, one workgroup each (see gst_kernels64.hip).
+struct Chain64Launch {
+  int K;
+  const double* rho;         // [64]
+  const double* G;           // [K][64][64]
+  const int64_t* off;        // [S+1]
+  const int64_t* order;      // sequences by length, descending
+  int64_t S;
+  int tile_seqs;             // chains per tile (consecutive in `order`)
+  int n_tiles;
+  int tile_row;          // workgroups take the tiles there and back in rows of this many
+  const int64_t* tile_ptr;   // [n_tiles + 1]
+  const uint32_t* entries;
+  double* rec_f;             // [entries][4][64]: the states before each step (null: not recorded)
+  double* fin;               // [S][64], in `order`: final states (forward), seeds (reverse)
+  int M;                     // reverse: width of the head rows, 1 + 64 + 64 M
+  double* head;              // reverse: [gridDim.x] head rows, [0 | dL/drho | 0]
+  double* dg;                // reverse: [K][gridDim.x][4096]: each workgroup's dL/dG
 };
 struct Reduce64Launch {            // gate columns only
   int M, K;
@@ -334,6 +339,7 @@ struct Readout64Launch {
   const int64_t* slot_ptr;
   const int64_t* slot_seq;
   const int64_t* slot_pack;  // [n_slots][4]: node row, first sequence, slot_ptr[s], slot_ptr[s + 1]
+                             // (null: slot s is the one sequence slot_seq[s], its state row s)
   const int32_t* slot_cnt;   // [n_slots][M]: the first sequence's counts
   const int32_t* counts;
   const double* W;
@@ -360,10 +366,8 @@ hipError_t launch_readout64(const Readout64Launch& a, int n_blocks, hipStream_t 
 hipError_t launch_root64(const Root64Launch& a, hipStream_t stream);
 int readout64_blocks_per_cu();
 
-size_t chain64_lds(int K);
-int chain64_blocks_per_cu(int K);
-hipError_t launch_chain64(const Chain64Launch& a, int n_blocks, hipStream_t stream);
-hipError_t launch_gemm64(const Gemm64Launch& a, hipStream_t stream);
+hipError_t launch_chain64_fwd(const Chain64Launch& a, int n_blocks, hipStream_t stream);
+hipError_t launch_chain64_bwd(const Chain64Launch& a, int n_blocks, hipStream_t stream);
 hipError_t launch_reduce64(const Reduce64Launch& a, hipStream_t stream);
 
 // One request of a batched launch of three-qubit grouped-chain plans: the

@@ -3,28 +3,15 @@
 // Thesis Sec. 6.3.1: p[s][m] = e_m^T G[s_L] ... G[s_1] rho, the multinomial
 // log-likelihood of the counts and its gradient.
 //
-// Layout on the chip
-//   * One chain per wave: lane i holds component i of the state.  A step is
-//     the 64 fused multiply-adds acc = fma(G[k][i][j], f[j], acc), j
-//     ascending from acc = 0 (the order of the plain definition, so states
-//     and probabilities are bit-identical to a sequential loop).  f[j] is
-//     broadcast inside its 16-lane row by DPP row_newbcast; the four rows
-//     reach every lane through four row copies (ds_bpermute).
-//   * The whole gate set sits in LDS (K <= 5 gates of 32 KB).  Inside a gate
-//     the column pairs of row i are XOR-permuted by i mod 32, so the row
-//     reads of the forward product (lane i reads row i) and the column reads
-//     of the adjoint product (lane j reads column j) are both free of bank
-//     conflicts.
-//   * With the LDS full, the gradient of the gates is not accumulated on
-//     chip: the chain kernel writes, for every step of every sequence, the
-//     state before the step and the adjoint after it (one 512-byte row each,
-//     at the step's position in the sequence list), and a second kernel adds
-//     dG_k = sum b f^T over the positions of gate k with FP64 MFMA 16x16x4
-//     tiles, in fixed chunks.  A third kernel adds the per-tile and per-chunk
-//     partial sums in a fixed order.
-//   * Work is cut into tiles of consecutive sequences of the length-sorted
-//     order; each wave takes tiles from an atomic counter and writes one row
-//     of partial sums per tile, so results do not depend on scheduling.
+// Two evaluations share the kernels below: lists with shared prefixes as a
+// grouped-chain plan (gst_plan64.h), other lists as grouped schedules
+// (gst_sched.hip).  Both hold the gates in registers as operands of the FP64
+// matrix cores and step a block of states at a time, 16 columns with one word
+// in the plan's tiles, 4 columns that happen to need the same gate in the
+// schedules' tiles.  An FP64 MFMA adds its four products one after another in
+// ascending order, so every state is the chain of fused multiply-adds
+// acc = fma(G[i][j], f[j], acc), j = 0 .. 63 from acc = 0, of the plain
+// definition, and probabilities are bit-identical to a sequential loop.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -39,235 +26,314 @@ namespace {
 constexpr int N64 = 64;
 constexpr int GATE64 = N64 * N64;  // doubles per gate in LDS
 
-// Position (in doubles) of G[i][j] inside a gate: column pairs XOR-permuted
-// by the row.
-__device__ __forceinline__ int swz(int i, int j) { return i * N64 + ((((j >> 1) ^ (i & 31)) << 1) | (j & 1)); }
-
-// x of lane 16 r + (l & 15), in every lane l.
-__device__ __forceinline__ double row_copy(double x, int r, int lane) { return __shfl(x, 16 * r + (lane & 15)); }
-
-// Row i of gate Gk dotted with x, columns ascending from 0 (bit-exact chain).
-__device__ __forceinline__ double mv_row(const double* Gk, int i, double x) {
-  const double* row = Gk + i * N64;
-  const int s = i & 31;
-  double acc = 0.0;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const double xr = row_copy(x, r, i);
-    Row16 R;
-    R.a0 = *reinterpret_cast<const double2*>(row + 2 * ((8 * r + 0) ^ s));
-    R.a1 = *reinterpret_cast<const double2*>(row + 2 * ((8 * r + 1) ^ s));
-    R.a2 = *reinterpret_cast<const double2*>(row + 2 * ((8 * r + 2) ^ s));
-    R.a3 = *reinterpret_cast<const double2*>(row + 2 * ((8 * r + 3) ^ s));
-    R.a4 = *reinterpret_cast<const double2*>(row + 2 * ((8 * r + 4) ^ s));
-    R.a5 = *reinterpret_cast<const double2*>(row + 2 * ((8 * r + 5) ^ s));
-    R.a6 = *reinterpret_cast<const double2*>(row + 2 * ((8 * r + 6) ^ s));
-    R.a7 = *reinterpret_cast<const double2*>(row + 2 * ((8 * r + 7) ^ s));
-    acc = dot16_from(acc, xr, R);
-  }
-  return acc;
-}
-
-// Column j of gate Gk dotted with x (the adjoint product G^T x): four
-// independent partial chains, one per row block, added in a fixed order.
-__device__ __forceinline__ double mv_col(const double* Gk, int j, double x) {
-  double part[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const double xr = row_copy(x, r, j);
-    Row16 R;
-    const int i0 = 16 * r;
-    R.a0 = double2{Gk[swz(i0 + 0, j)], Gk[swz(i0 + 1, j)]};
-    R.a1 = double2{Gk[swz(i0 + 2, j)], Gk[swz(i0 + 3, j)]};
-    R.a2 = double2{Gk[swz(i0 + 4, j)], Gk[swz(i0 + 5, j)]};
-    R.a3 = double2{Gk[swz(i0 + 6, j)], Gk[swz(i0 + 7, j)]};
-    R.a4 = double2{Gk[swz(i0 + 8, j)], Gk[swz(i0 + 9, j)]};
-    R.a5 = double2{Gk[swz(i0 + 10, j)], Gk[swz(i0 + 11, j)]};
-    R.a6 = double2{Gk[swz(i0 + 12, j)], Gk[swz(i0 + 13, j)]};
-    R.a7 = double2{Gk[swz(i0 + 14, j)], Gk[swz(i0 + 15, j)]};
-    part[r] = dot16(xr, R);
-  }
-  return (part[0] + part[1]) + (part[2] + part[3]);
-}
-
-// E row m (global memory) dotted with x, columns ascending from 0.
-__device__ __forceinline__ double mv_global_row(const double* __restrict__ row, int lane, double x) {
-  const auto* g = as_global(row);
-  double acc = 0.0;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const double xr = row_copy(x, r, lane);
-    const auto* q = g + 16 * r;
-    Row16 R;
-    R.a0 = double2{q[0], q[1]};
-    R.a1 = double2{q[2], q[3]};
-    R.a2 = double2{q[4], q[5]};
-    R.a3 = double2{q[6], q[7]};
-    R.a4 = double2{q[8], q[9]};
-    R.a5 = double2{q[10], q[11]};
-    R.a6 = double2{q[12], q[13]};
-    R.a7 = double2{q[14], q[15]};
-    acc = dot16_from(acc, xr, R);
-  }
-  return acc;
-}
-
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int sh = 1; sh < 64; sh <<= 1) v += __shfl_xor(v, sh);
   return v;
 }
 
-__global__ __launch_bounds__(CHAIN64_WAVES * 64) void chain64_kernel(const Chain64Launch a) {
-  extern __shared__ double G_lds[];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int K = a.K, M = a.M;
-  for (int x = tid; x < K * GATE64; x += CHAIN64_WAVES * 64) {
-    const int k = x >> 12, i = (x >> 6) & 63, j = x & 63;
-    G_lds[k * GATE64 + swz(i, j)] = a.G[x];
+// Workgroup barrier for the LDS exchange of a step: waits for this wave's LDS
+// operations only, so the global stores of the step and the operand loads of
+// the next step stay in flight across it (a full __syncthreads() would wait for
+// them as well).  The memory clobber keeps the compiler from moving LDS
+// accesses across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// ---------------------------------------------------------------------------
+// Lists without shared prefixes: grouped schedules (gst_sched.hip).
+//
+// A tile of up to 16 chains is a workgroup's; an entry steps up to four chains
+// by one gate: 64 x 64 times 64 x 4, wave w computing rows 16w .. 16w + 15 with
+// sixteen v_mfma_f64_4x4x4 (four blocks of four rows by the same four columns;
+// 16 cycles each, 22 in a dependent chain, the rate of the 16x16x4 form).  A
+// wave keeps its operands of all K <= 5 gates in registers (160 VGPRs), so the
+// gates cost no bandwidth; with each step's 32 KB gate read from LDS, one
+// chain per wave, those reads bound a chain-step at 256 cycles per CU.  The
+// states live in LDS, double-buffered by the parity of the chain's step, so a
+// round of two entries (of different chains) needs one barrier.
+//
+// Both kernels run eight waves, two per SIMD.  Forward: four waves per entry of
+// the round, so the two products fill each other's latencies (302 -> 170 us
+// below, against one entry after the other on two workgroups of four waves per
+// CU); each entry's four states before it are recorded (2 KB in a row).
+// Reverse: four waves step the adjoints of both entries, at a raised priority,
+// and the other four load the recorded states two rounds ahead and add
+// dG += b f^T, one 16x16x4 MFMA per 16 x 16 tile and entry, in accumulators for
+// all gates (160 registers), so the adjoints are never stored and the states
+// are read once.  (One role per wave: the transposed gates' operands and the
+// accumulators together spill, 461 instead of 253 us.)  A tile belongs to a
+// fixed workgroup, so the sums do not depend on scheduling.
+//
+// 8,000 words of up to 128 gates (510,378 steps), per evaluation with the
+// gradient: 4.86 -> 0.45 ms, against a chain per wave with the gates in LDS,
+// stored adjoints, and a GEMM over the stored pairs.  A round takes about 0.5 us
+// forward and 0.9 us reverse; the LDS reads of a round (each wave reads all
+// four states, repeated for its four row blocks) take half of that, the
+// products the other half.
+// ---------------------------------------------------------------------------
+
+// A state in LDS: component 4s + k at k * SKS + s, so that a lane reads its
+// sixteen operands of row k with eight 16-byte reads.
+constexpr int SKS = 18;            // stride of the four component classes (doubles)
+constexpr int SST = 4 * SKS + 2;   // stride of a state
+constexpr int SLOTS = 2 * (SCHED_CHAINS + 1);
+__device__ __forceinline__ int state_at(int j) { return (j & 3) * SKS + (j >> 2); }
+
+// Operands of G (or, TR, of its transpose) for the 4x4x4 MFMA: lane 16k + 4b + i
+// holds rows 16w + 4b + i, columns 4s + k, s = 0 .. 15.
+template <bool TR>
+struct SchedGates {
+  double g[5][16];
+  __device__ __forceinline__ void load(const double* G, int K, int w, int l) {
+    const auto* p = as_global(G);
+    const int row = 16 * w + (l & 15), k = l >> 4;
+#pragma unroll
+    for (int x = 0; x < 5; ++x)
+      if (x < K) {
+#pragma unroll
+        for (int s = 0; s < 16; ++s)
+          g[x][s] = TR ? p[x * GATE64 + (4 * s + k) * N64 + row] : p[x * GATE64 + row * N64 + 4 * s + k];
+      }
   }
-  __syncthreads();
-  const auto* g_off = as_global(a.off);
-  const auto* g_order = as_global(a.order);
-  const auto* g_gates = as_global(a.gates);
-  const auto* g_counts = as_global(a.counts);
-  const auto* g_W = as_global(a.W);
-  auto* g_probs = as_global(a.probs);
-  auto* g_rec_b = as_global(a.rec_b);
-  auto* g_rec_f = as_global(a.rec_f);
-  const bool grad = a.want_grad != 0;
-  const double rho_i = a.rho[lane];
-  const int mrow = lane < M ? lane : M - 1;       // lanes >= M compute a discarded readout
-  const double* Erow = a.E + (size_t)mrow * N64;
-  unsigned bad = 0, nonpos = 0;
-  for (;;) {
-    int tile = 0;
-    if (lane == 0) tile = (int)atomicAdd(a.queue, 1u);
-    tile = __builtin_amdgcn_readfirstlane(tile);
-    if (tile >= a.n_tiles) break;
-    double obj = 0.0, drho = 0.0;
-    double dE[16];
-#pragma unroll
-    for (int m = 0; m < 16; ++m) dE[m] = 0.0;
-    const int64_t q0 = (int64_t)tile * a.tile_seqs;
-    const int64_t q1 = q0 + a.tile_seqs < a.S ? q0 + a.tile_seqs : a.S;
-    for (int64_t q = q0; q < q1; ++q) {
-      const int64_t seq = g_order[q];
-      const int64_t beg = g_off[seq];
-      const int L = (int)(g_off[seq + 1] - beg);
-      double f = rho_i;
-      // ---- forward: gate indices of 64 steps per load, broadcast by readlane ----
-      for (int t0 = 0; t0 < L; t0 += 64) {
-        const int n = L - t0 < 64 ? L - t0 : 64;
-        const int kv = lane < n ? (int)g_gates[beg + t0 + lane] : 0;
-        for (int x = 0; x < n; ++x) {
-          int k = __builtin_amdgcn_readlane(kv, x);
-          if (k >= K) {
-            bad += lane == 0;
-            k = 0;
-          }
-          if (grad) g_rec_f[(beg + t0 + x) * N64 + lane] = f;
-          f = mv_row(G_lds + k * GATE64, lane, f);
-        }
-      }
-      // ---- readout: lane m < M holds p_m ----
-      const double p = mv_global_row(Erow, lane, f);
-      double dp = 0.0;
-      if (lane < M) {
-        const int64_t o = seq * M + lane;
-        if (a.probs) g_probs[o] = p;
-        if (a.mode == MODE_LOGLIK) {
-          const int32_t N = g_counts[o];
-          if (N > 0) {
-            if (p <= 0.0) {
-              ++nonpos;
-              obj = INFINITY;  // -N log p with p <= 0; no term is ever -inf
-            } else {
-              obj -= (double)N * log(p);
-              dp = -(double)N / p;
-            }
-          }
-        } else if (a.mode == MODE_VJP) {
-          dp = g_W[o];
-        }
-      }
-      if (!grad) continue;
-      // ---- effect gradient dE[m][j] += dp_m f_j and seed b_j = sum_m E[m][j] dp_m ----
-      double b = 0.0;
-#pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        if (m < M) {
-          const double dpm = __shfl(dp, m);
-          dE[m] = fma(dpm, f, dE[m]);
-          b = fma(a.E[(size_t)m * N64 + lane], dpm, b);
-        }
-      }
-      // ---- reverse sweep: record (b after step, state before step) ----
-      for (int c0 = ((L - 1) / 64) * 64; c0 >= 0 && L > 0; c0 -= 64) {
-        const int n = L - c0 < 64 ? L - c0 : 64;
-        int kv = lane < n ? (int)g_gates[beg + c0 + lane] : 0;
-        if (kv >= K) kv = 0;  // counted in the forward sweep
-        for (int x = n - 1; x >= 0; --x) {
-          const int k = __builtin_amdgcn_readlane(kv, x);
-          g_rec_b[(beg + c0 + x) * N64 + lane] = b;
-          b = mv_col(G_lds + k * GATE64, lane, b);
-        }
-      }
-      drho += b;
+};
+
+// The workgroup's tiles: there and back over rows of `row` length-sorted tiles,
+// so that the tiles of a workgroup, and of workgroups that share a CU, differ
+// in length.  `at` is the place in that order; next_tile advances it to the
+// next tile (n_tiles: none left).
+__device__ __forceinline__ int next_tile(int& at, int row, int n_tiles) {
+  for (;; at += gridDim.x) {
+    const int y = at / row, x = at - y * row;
+    if (y * row >= n_tiles) return n_tiles;
+    const int t = y * row + ((y & 1) ? row - 1 - x : x);
+    if (t < n_tiles) {
+      at += gridDim.x;
+      return t;
     }
-    // ---- this tile's partial sums ----
-    const int64_t Pc = 1 + N64 + (int64_t)M * N64;
-    double* out = a.slab + (int64_t)tile * Pc;
-    const double o = wave_sum(obj);
-    if (lane == 0) out[0] = o;
-    out[1 + lane] = drho;
-#pragma unroll
-    for (int m = 0; m < 16; ++m)
-      if (m < M) out[1 + N64 + m * N64 + lane] = dE[m];
-  }
-  if (lane == 0 && bad) atomicAdd(a.status + 0, (unsigned long long)bad);
-  const unsigned np = (unsigned)wave_sum((double)nonpos);
-  if (lane == 0 && np) {
-    atomicAdd(a.status + 1, (unsigned long long)np);
-    atomicAdd(a.nonpos, (unsigned long long)np);
   }
 }
 
-// dG_k partial over one chunk of positions of gate k: wave w owns rows
-// 16w .. 16w+15 (four 16x16 tiles); four positions per MFMA, in order.
-__global__ __launch_bounds__(256) void gemm64_kernel(const Gemm64Launch a) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int z = lane >> 4, ii = lane & 15;
-  const int c = blockIdx.x;
-  const int64_t r0 = a.chunk_beg[c], r1 = a.chunk_end[c];
-  const auto* g_pos = as_global(a.pos);
-  const auto* g_b = as_global(a.rec_b);
-  const auto* g_f = as_global(a.rec_f);
-  d4 acc[4];
-#pragma unroll
-  for (int tc = 0; tc < 4; ++tc) acc[tc] = d4{0.0, 0.0, 0.0, 0.0};
-  const auto* g_rb = as_global(a.row_b);
-  const auto* g_rf = as_global(a.row_f);
-  for (int64_t r = r0; r < r1; r += 4) {
-    const bool v = r + z < r1;
-    const int64_t idx = v ? r + z : r0;
-    const int64_t pb = a.row_b ? g_rb[idx] : g_pos[idx];
-    const int64_t pf = a.row_b ? g_rf[idx] : pb;
-    const double av = v ? g_b[pb * N64 + 16 * w + ii] : 0.0;
-    double bv[4];
-#pragma unroll
-    for (int tc = 0; tc < 4; ++tc) bv[tc] = v ? g_f[pf * N64 + 16 * tc + ii] : 0.0;
-#pragma unroll
-    for (int tc = 0; tc < 4; ++tc) acc[tc] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[tc], acc[tc], 0, 0, 0);
+// Field r of an entry: two times the chain's index, plus the parity of its step.
+__device__ __forceinline__ int entry_field(uint32_t e, int r) { return (int)((e >> (6 * r)) & 63u); }
+
+// A wave's rows of the product of an entry's gate with the entry's block: acc
+// holds row 16w + 4b + k of column i in lane 16k + 4b + i.
+template <bool TR>
+__device__ __forceinline__ double sched_product(const SchedGates<TR>& gates, uint32_t en, const double2 (&v)[8]) {
+  double acc = 0.0;
+  switch (en >> 24) {
+#define GST_S64_CASE(X)                                                                    \
+  _Pragma("unroll") for (int s = 0; s < 8; ++s) {                                          \
+    acc = __builtin_amdgcn_mfma_f64_4x4x4f64(gates.g[X][2 * s], v[s].x, acc, 0, 0, 0);     \
+    acc = __builtin_amdgcn_mfma_f64_4x4x4f64(gates.g[X][2 * s + 1], v[s].y, acc, 0, 0, 0); \
+  }                                                                                        \
+  break;
+    case 0: GST_S64_CASE(0)
+    case 1: GST_S64_CASE(1)
+    case 2: GST_S64_CASE(2)
+    case 3: GST_S64_CASE(3)
+    default: GST_S64_CASE(4)
+#undef GST_S64_CASE
   }
+  return acc;
+}
+
+// An entry's product: FLIP reads the state of the entry's fields with the other
+// parity (the reverse sweep) and writes the field's own.
+template <bool TR, int FLIP>
+__device__ __forceinline__ void sched_step(const SchedGates<TR>& gates, double* V, uint32_t en, int w, int l) {
+  const int k4 = l >> 4, b4 = (l >> 2) & 3, j4 = l & 3;
+  const int f = (int)((en >> (6 * j4)) & 63u) ^ FLIP;
+  const double2* src = reinterpret_cast<const double2*>(V + f * SST + k4 * SKS);
+  double2 v[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) v[s] = src[s];
+  const double acc = sched_product<TR>(gates, en, v);
+  if (f < 2 * SCHED_CHAINS) V[(f ^ 1) * SST + k4 * SKS + 4 * w + b4] = acc;
+}
+
+// An entry without chains (the second of a round, or padding).
+__device__ __forceinline__ bool sched_empty(uint32_t en) { return (en & 0xffffffu) == SCHED_NONE; }
+
+// Eight waves, two per SIMD: waves 0 .. 3 step a round's first entry, waves
+// 4 .. 7 its second.
+__global__ __launch_bounds__(512, 2) void chain64_fwd_kernel(const Chain64Launch a) {
+  __shared__ double V[SLOTS * SST];
+  const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3, z = wave >> 2;
+  SchedGates<false> gates;
+  gates.load(a.G, a.K, w, l);
+  const double rho = as_global(a.rho)[l];
+  const auto* entries = as_global(a.entries);
+  auto* rec = as_global(a.rec_f);
+  auto* fin = as_global(a.fin);
+  int at = blockIdx.x;
+  for (int tile = next_tile(at, a.tile_row, a.n_tiles); tile < a.n_tiles; tile = next_tile(at, a.tile_row, a.n_tiles)) {
+    const int64_t q0 = (int64_t)tile * a.tile_seqs;
+    const int n = (int)(q0 + a.tile_seqs < a.S ? a.tile_seqs : a.S - q0);
+    const int64_t e0 = uniform64(a.tile_ptr[tile]);
+    const int ne = (int)(uniform64(a.tile_ptr[tile + 1]) - e0);
+    for (int c = wave; c <= SCHED_CHAINS; c += 8) {
+      V[2 * c * SST + state_at(l)] = c < n ? rho : 0.0;
+      if (c == SCHED_CHAINS) V[(2 * c + 1) * SST + state_at(l)] = 0.0;
+    }
+    uint32_t next = entries[e0 + min(l, max(ne - 1, 0))];
+    lds_barrier();
+    for (int eb = 0; eb < ne; eb += 64) {  // the entries' count is a multiple of SCHED_ALIGN
+      const uint32_t cur = next;
+      const int m = min(ne - eb, 64);
+      next = entries[e0 + min(eb + 64 + l, ne - 1)];
+      for (int x = 0; x < m; x += 2) {
+        const uint32_t en = (uint32_t)__builtin_amdgcn_readlane((int)cur, x + z);
+        if (!sched_empty(en)) {
+          sched_step<false, 0>(gates, V, en, w, l);
+          // the state before the entry is still there: the step wrote the other parity
+          if (a.rec_f) rec[((e0 + eb + x + z) * SCHED_COLS + w) * N64 + l] = V[entry_field(en, w) * SST + state_at(l)];
+        }
+        lds_barrier();
+      }
+    }
+    for (int c = wave; c < n; c += 8) {
+      const int64_t seq = a.order[q0 + c];
+      const int odd = (int)(a.off[seq + 1] - a.off[seq]) & 1;
+      fin[(q0 + c) * N64 + l] = V[(2 * c + odd) * SST + state_at(l)];
+    }
+    lds_barrier();  // the states have been read
+  }
+}
+
+constexpr int SFS = 80;  // stride (doubles) of an entry's staged states: a half-wave's reads hit distinct banks
+
+// dg[tc] += b f^T over an entry's four columns, for the four 16 x 16 tiles of a
+// wave's rows.
+__device__ __forceinline__ void add_outer(d4 (&dg)[4], double b, const double (&f)[4]) {
+#pragma unroll
+  for (int tc = 0; tc < 4; ++tc) dg[tc] = __builtin_amdgcn_mfma_f64_16x16x4f64(b, f[tc], dg[tc], 0, 0, 0);
+}
+
+// Waves 0 .. 3: the adjoints.  Waves 4 .. 7: dG.  Both pass the same barriers.
+__global__ __launch_bounds__(512, 2) void chain64_bwd_kernel(const Chain64Launch a) {
+  __shared__ double V[SLOTS * SST];
+  __shared__ double F[2][2][SCHED_COLS * SFS];  // the recorded states of a round's entries, double-buffered
+  const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3;
+  const auto* entries = as_global(a.entries);
+  const int64_t P = 1 + N64 + (int64_t)a.M * N64;
+  double* head = a.head + (int64_t)blockIdx.x * P;
+  if (wave < 4) {
+    __builtin_amdgcn_s_setprio(2);  // the chains are what a round waits for
+    SchedGates<true> gates;
+    gates.load(a.G, a.K, w, l);
+    const auto* fin = as_global(a.fin);
+    double drho = 0.0;
+    int at = blockIdx.x;
+    for (int tile = next_tile(at, a.tile_row, a.n_tiles); tile < a.n_tiles;
+         tile = next_tile(at, a.tile_row, a.n_tiles)) {
+      const int64_t q0 = (int64_t)tile * a.tile_seqs;
+      const int n = (int)(q0 + a.tile_seqs < a.S ? a.tile_seqs : a.S - q0);
+      const int64_t e0 = uniform64(a.tile_ptr[tile]);
+    const int ne = (int)(uniform64(a.tile_ptr[tile + 1]) - e0);
+      uint32_t next = entries[e0 + max(ne - 1 - l, 0)];
+      for (int c = w; c <= SCHED_CHAINS; c += 4) {
+        if (c < n) {
+          const int64_t seq = a.order[q0 + c];
+          const int odd = (int)(a.off[seq + 1] - a.off[seq]) & 1;
+          V[(2 * c + odd) * SST + state_at(l)] = fin[(q0 + c) * N64 + l];
+        }
+        if (c == SCHED_CHAINS) {
+          V[2 * c * SST + state_at(l)] = 0.0;
+          V[(2 * c + 1) * SST + state_at(l)] = 0.0;
+        }
+      }
+      lds_barrier();
+      for (int xb = 0; xb < ne; xb += 64) {
+        const uint32_t cur = next;
+        const int m = min(ne - xb, 64);
+        next = entries[e0 + max(ne - 65 - xb - l, 0)];
+        for (int x = 0; x < m; x += 2) {
+          const uint32_t en0 = (uint32_t)__builtin_amdgcn_readlane((int)cur, x);
+          const uint32_t en1 = (uint32_t)__builtin_amdgcn_readlane((int)cur, x + 1);
+          if (!sched_empty(en0)) sched_step<true, 1>(gates, V, en0, w, l);
+          if (!sched_empty(en1)) sched_step<true, 1>(gates, V, en1, w, l);
+          lds_barrier();
+        }
+      }
+      for (int c = w; c < n; c += 4) drho += V[2 * c * SST + state_at(l)];
+      lds_barrier();  // the adjoints have been read
+    }
+    V[w * SST + l] = drho;
+    lds_barrier();
+    // the head row: dL/drho of the four waves added in order
+    for (int64_t x = threadIdx.x; x < P; x += 256) {
+      const int j = (int)x - 1;
+      head[x] = x >= 1 && x <= N64 ? (V[j] + V[SST + j]) + (V[2 * SST + j] + V[3 * SST + j]) : 0.0;
+    }
+    return;
+  }
+  const int k4 = l >> 4, i16 = l & 15;
+  const auto* rec = as_global(a.rec_f);
+  d4 dg[5][4];
+#pragma unroll
+  for (int x = 0; x < 5; ++x)
+#pragma unroll
+    for (int tc = 0; tc < 4; ++tc) dg[x][tc] = d4{0.0, 0.0, 0.0, 0.0};
+  int at = blockIdx.x;
+  for (int tile = next_tile(at, a.tile_row, a.n_tiles); tile < a.n_tiles; tile = next_tile(at, a.tile_row, a.n_tiles)) {
+    const int64_t e0 = uniform64(a.tile_ptr[tile]);
+    const int ne = (int)(uniform64(a.tile_ptr[tile + 1]) - e0);
+    // column w's state of the entry x before the last one
+    auto state = [&](int x) { return rec[((e0 + max(ne - 1 - x, 0)) * SCHED_COLS + w) * N64 + l]; };
+    uint32_t next = entries[e0 + max(ne - 1 - l, 0)];
+    double ring[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) ring[u] = state(u);
+    F[0][0][w * SFS + l] = ring[0];
+    F[0][1][w * SFS + l] = ring[1];
+    ring[0] = state(4);
+    ring[1] = state(5);
+    lds_barrier();
+    for (int xb = 0; xb < ne; xb += 64) {
+      const uint32_t cur = next;
+      const int m = min(ne - xb, 64);
+      next = entries[e0 + max(ne - 65 - xb - l, 0)];
+      for (int x0 = 0; x0 < m; x0 += 4) {
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          // the next round's states, loaded two rounds ago, and the loads that replace them
+          F[y ^ 1][0][w * SFS + l] = ring[2 - 2 * y];
+          F[y ^ 1][1][w * SFS + l] = ring[3 - 2 * y];
+          ring[2 - 2 * y] = state(xb + x0 + 2 * y + 6);
+          ring[3 - 2 * y] = state(xb + x0 + 2 * y + 7);
+#pragma unroll
+          for (int z = 0; z < 2; ++z) {
+            const uint32_t en = (uint32_t)__builtin_amdgcn_readlane((int)cur, x0 + 2 * y + z);
+            // A[i][c] = b of column c (rows 16w + i), B[c][j] = f of column c
+            const int fc = (int)((en >> (6 * k4)) & 63u) ^ 1;
+            const double bc = V[fc * SST + state_at(16 * w + i16)];
+            double fv[4];
+#pragma unroll
+            for (int tc = 0; tc < 4; ++tc) fv[tc] = F[y][z][k4 * SFS + 16 * tc + i16];
+            // one test per gate: with a switch the compiler keeps a second copy of the
+            // accumulators (160 spilled registers)
+            const uint32_t gk = en >> 24;
+#pragma unroll
+            for (int X = 0; X < 5; ++X)
+              if (gk == (uint32_t)X && !sched_empty(en)) add_outer(dg[X], bc, fv);
+          }
+          lds_barrier();
+        }
+      }
+    }
+    lds_barrier();  // the adjoints have been read
+  }
+  lds_barrier();  // the head row
   // tile element C[r][cc] sits in lane 16*(r&3)+cc, register r>>2
-  double* out = a.slab + (int64_t)c * GATE64;
 #pragma unroll
-  for (int tc = 0; tc < 4; ++tc)
+  for (int x = 0; x < 5; ++x)
+    if (x < a.K) {
+      double* out = a.dg + ((int64_t)x * gridDim.x + blockIdx.x) * GATE64;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = 4 * v + (lane >> 4), cc = lane & 15;
-      out[(16 * w + r) * N64 + 16 * tc + cc] = acc[tc][v];
+      for (int tc = 0; tc < 4; ++tc)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[(16 * w + 4 * v + k4) * N64 + 16 * tc + i16] = dg[x][tc][v];
     }
 }
 
@@ -331,13 +397,6 @@ __global__ __launch_bounds__(256) void gate_prep64_kernel(const double* G, const
                                                           double* GAT, double* FA) {
   gate_prep64_body(G, rho, GA, GAT, FA, blockIdx.x);
 }
-
-// Workgroup barrier for the LDS exchange of a step: waits for this wave's LDS
-// operations only, so the global stores of the step and the operand loads of
-// the next step stay in flight across it (a full __syncthreads() would wait for
-// them as well).  The memory clobber keeps the compiler from moving LDS
-// accesses across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 __device__ __forceinline__ void load_ops(double (&dst)[16], const double* base, int lane) {
   const auto* g = as_global(base);
@@ -796,6 +855,10 @@ constexpr int RO_DST = 17;  // the same for its dL/dp tile
 
 // Workgroup blk of n_blocks (the waves' slot groups depend on the count, so a
 // request's sums are the same in any launch that gives it n_blocks workgroups).
+// PACK: the slots of a plan; otherwise slot s is the one sequence slot_seq[s],
+// its state row s (a variant of its own: the choice at run time cost the plan's
+// evaluation 18 us on the 200,960-sequence list).
+template <bool PACK>
 __device__ __forceinline__ void readout64_body(const Readout64Launch& a, int64_t blk, int64_t n_blocks) {
   __shared__ double Fs[READOUT64_WAVES][16 * RO_FST];
   __shared__ double Ds[READOUT64_WAVES][16 * RO_DST];
@@ -831,7 +894,7 @@ __device__ __forceinline__ void readout64_body(const Readout64Launch& a, int64_t
   for (int64_t gi = wv; gi < n_groups; gi += nw) {
     // slot 16 gi + c: its state row, the A operand of P^T (elements 4kk + r4)
     const int64_t sc = gi * 16 + c;
-    const int64_t rowc = g_pack[4 * (sc < a.n_slots ? sc : 0)];
+    const int64_t rowc = PACK ? g_pack[4 * (sc < a.n_slots ? sc : 0)] : (sc < a.n_slots ? sc : a.n_slots - 1);
     // the sixteen rows read whole (two rows of 512 B per load, 16 B per lane)
     // into the wave's tile, then the A operand from there
     {
@@ -859,12 +922,19 @@ __device__ __forceinline__ void readout64_body(const Readout64Launch& a, int64_t
     for (int v = 0; v < 4; ++v) {
       const int64_t s = gi * 16 + 4 * v + r4;
       const bool valid = s < a.n_slots;
-      const int64_t b = 4 * (valid ? s : 0);
-      seq0[v] = g_pack[b + 1];
-      q0[v] = g_pack[b + 2];
-      q1[v] = valid ? g_pack[b + 3] : q0[v];
       n0[v] = 0.0;
-      if (a.mode == MODE_LOGLIK && valid && c < M) n0[v] = (double)g_cnt[s * M + c];
+      if (PACK) {
+        const int64_t b = 4 * (valid ? s : 0);
+        seq0[v] = g_pack[b + 1];
+        q0[v] = g_pack[b + 2];
+        q1[v] = valid ? g_pack[b + 3] : q0[v];
+        if (a.mode == MODE_LOGLIK && valid && c < M) n0[v] = (double)g_cnt[s * M + c];
+      } else {  // one sequence per slot
+        seq0[v] = g_seq[valid ? s : 0];
+        q0[v] = 0;
+        q1[v] = valid ? 1 : 0;
+        if (a.mode == MODE_LOGLIK && valid && c < M) n0[v] = (double)g_counts[seq0[v] * M + c];
+      }
     }
     if (a.mode == MODE_VJP) {
 #pragma unroll
@@ -955,8 +1025,9 @@ __device__ __forceinline__ void readout64_body(const Readout64Launch& a, int64_t
   }
 }
 
+template <bool PACK>
 __global__ __launch_bounds__(READOUT64_WAVES * 64) void readout64_kernel(const Readout64Launch a) {
-  readout64_body(a, blockIdx.x, gridDim.x);
+  readout64_body<PACK>(a, blockIdx.x, gridDim.x);
 }
 
 __device__ __forceinline__ void root64_body(const Root64Launch& a) {
@@ -1007,7 +1078,7 @@ __global__ __launch_bounds__(READOUT64_WAVES * 64) void readout64_batch(const Pl
   const int nb = q.ro_blocks;
   if ((int)blockIdx.x >= nb) return;
   const Readout64Launch a = q.ro;
-  readout64_body(a, blockIdx.x, nb);
+  readout64_body<true>(a, blockIdx.x, nb);
 }
 
 __global__ __launch_bounds__(256) void gemm64_ts_batch(const Plan64Req* r) {
@@ -1080,13 +1151,16 @@ hipError_t launch_plan64_bwd(const Plan64Launch& a, int n_tiles, bool reg_gates,
 
 int readout64_blocks_per_cu() {
   int n = 0;
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, readout64_kernel, READOUT64_WAVES * 64, 0);
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, readout64_kernel<true>, READOUT64_WAVES * 64, 0);
   return (e == hipSuccess && n > 0) ? n : 1;
 }
 
 hipError_t launch_readout64(const Readout64Launch& a, int n_blocks, hipStream_t stream) {
   if (n_blocks <= 0 || a.M < 1 || a.M > 16) return hipErrorInvalidValue;
-  gst_launch(readout64_kernel, dim3(n_blocks), dim3(READOUT64_WAVES * 64), 0, stream, a);
+  if (a.slot_pack)
+    gst_launch(readout64_kernel<true>, dim3(n_blocks), dim3(READOUT64_WAVES * 64), 0, stream, a);
+  else
+    gst_launch(readout64_kernel<false>, dim3(n_blocks), dim3(READOUT64_WAVES * 64), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -1095,24 +1169,19 @@ hipError_t launch_root64(const Root64Launch& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-size_t chain64_lds(int K) { return (size_t)K * GATE64 * sizeof(double); }
-
-int chain64_blocks_per_cu(int K) {
-  int n = 0;
-  const hipError_t e =
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, chain64_kernel, CHAIN64_WAVES * 64, chain64_lds(K));
-  return (e == hipSuccess && n > 0) ? n : 1;
+static bool chain64_ok(const Chain64Launch& a, int n_blocks) {
+  return a.K >= 1 && a.K <= 5 && a.tile_seqs >= 1 && a.tile_seqs <= SCHED_CHAINS && a.tile_row >= 1 && n_blocks >= 1;
 }
 
-hipError_t launch_chain64(const Chain64Launch& a, int n_blocks, hipStream_t stream) {
-  if (a.K < 1 || a.K > 5 || a.M < 1 || a.M > 16) return hipErrorInvalidValue;
-  gst_launch(chain64_kernel, dim3(n_blocks), dim3(CHAIN64_WAVES * 64), chain64_lds(a.K), stream, a);
+hipError_t launch_chain64_fwd(const Chain64Launch& a, int n_blocks, hipStream_t stream) {
+  if (!chain64_ok(a, n_blocks)) return hipErrorInvalidValue;
+  gst_launch(chain64_fwd_kernel, dim3(n_blocks), dim3(512), 0, stream, a);
   return hipGetLastError();
 }
 
-hipError_t launch_gemm64(const Gemm64Launch& a, hipStream_t stream) {
-  if (a.n_chunks <= 0) return hipSuccess;
-  gst_launch(gemm64_kernel, dim3(a.n_chunks), dim3(256), 0, stream, a);
+hipError_t launch_chain64_bwd(const Chain64Launch& a, int n_blocks, hipStream_t stream) {
+  if (!chain64_ok(a, n_blocks) || !a.rec_f || a.M < 1 || a.M > 16) return hipErrorInvalidValue;
+  gst_launch(chain64_bwd_kernel, dim3(n_blocks), dim3(512), 0, stream, a);
   return hipGetLastError();
 }
 
