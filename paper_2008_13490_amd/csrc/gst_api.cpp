@@ -284,18 +284,19 @@ struct DevicePlan64 {
   int64_t n_chunks = 0;
 };
 
-// Sequences per batch tile: a request's sequences, sorted by length, are cut
-// into tiles of this many (16 chains x 8); fixed, so a request's tiling and
-// summation order depend on the request alone.
-// Sequences per tile of a request: a multiple of the 16 chains of one
-// workgroup, chosen from S alone so that the cut (and with it the order of
-// the partial sums) is a property of the request.
 // Device words of a request's work-queue area: six queue counters 16 words
 // apart (zeroed by the queue-reset kernel), then the nonpos counter (64-bit).
 constexpr int kQueueWords = 96;
 
+// Sequences per tile of a request: a multiple of the 16 chains of one
+// workgroup, chosen from S alone so that the cut (and with it the order of
+// the partial sums) is a property of the request.  One round of chains up to
+// 65,536 sequences: the longest words bound a launch, and a tile of two rounds
+// takes them one after the other (30,000 words: 351 us with 32 a tile, 301
+// with 16); beyond, more, up to eight rounds, so that the tiles' partial sums
+// stay small beside the work.
 static int64_t tile_seqs_for(int64_t S) {
-  const int64_t per = (S + 16 * 1024 - 1) / (16 * 1024);
+  const int64_t per = (S + 64 * 1024 - 1) / (64 * 1024);
   return 16 * std::min<int64_t>(std::max<int64_t>(per, 1), 8);
 }
 
@@ -458,6 +459,9 @@ static int group_family(int g) { return g == 0 ? FAM_TILES16 : FAM_TILES4; }
 // Workgroups of a launch over n tiles (lane kernel: four waves, one tile each).
 static int capped(int bpc, int cap) { return cap > 0 ? std::min(bpc, cap) : bpc; }
 
+// A launch of n workgroups' worth of tiles that two per CU hold.
+static bool few_tiles(const gst_ctx* ctx, int64_t n) { return n <= 2 * (int64_t)ctx->n_cu; }
+
 static int group_grid(gst_ctx* ctx, int g, int kmax, int64_t n) {
   if (n <= 0) return 0;
   const int cap = ctx->tune_bpc[g == 0 ? 2 : 1];
@@ -465,7 +469,8 @@ static int group_grid(gst_ctx* ctx, int g, int kmax, int64_t n) {
     const int64_t blocks = (n + 3) / 4;
     return (int)std::min<int64_t>(blocks, (int64_t)capped(gst::lane1q_blocks_per_cu(g - 1), cap) * ctx->n_cu);
   }
-  return (int)std::min<int64_t>(n, (int64_t)capped(gst::batch_blocks_per_cu(g == 0 ? 16 : 4, kmax), cap) * ctx->n_cu);
+  const int per_cu = gst::batch_blocks_per_cu(g == 0 ? 16 : 4, kmax, few_tiles(ctx, n));
+  return (int)std::min<int64_t>(n, (int64_t)capped(per_cu, cap) * ctx->n_cu);
 }
 
 // Checkpoint doubles of one chain group (team or wave) and of a whole launch.
@@ -559,6 +564,7 @@ int enqueue_leaf(gst_ctx* ctx, const gst::LeafLaunch& base, int64_t max_len, dou
   a.ckpt = a.want_grad ? reinterpret_cast<double*>((char*)buf + z.slab_bytes + z.part_bytes) : nullptr;
   const int64_t ck_team = z.ck_team;
   a.ckpt_per_team = ck_team;
+  a.few = few_tiles(ctx, blocks) ? 1 : 0;
   a.max_len = (int)max_len;
   a.status = ctx->status;
   if (max_len > (int64_t)1 << 30) return fail(GST_EINVAL, "sequence too long");
@@ -615,9 +621,6 @@ gst::LeafLaunch plain_launch(int D, const gst_gateset* gs, const gst_seqlist* sl
   a.n_items = sl->n_seq;
   a.off = sl->offsets;
   a.gates = sl->gate_idx;
-  a.items = nullptr;
-  a.anchor_states = nullptr;
-  a.anchor_adj = nullptr;
   a.counts = counts;
   a.W = w;
   a.probs = probs;
@@ -1767,6 +1770,7 @@ static int run_tiles(gst_req* r, const gst_gateset* th, int mode, const double* 
   l.one = batch_req_of(r, th, mode, w, probs, want_grad);
   l.tiles = r->tiles;
   l.n_tiles = (int)nt;
+  l.few = few_tiles(ctx, nt) ? 1 : 0;
   l.queue = r->queue;
   l.ckpt = want_grad ? reinterpret_cast<double*>(ctx->ws.p) : nullptr;
   l.ckpt_per_team = group_ckpt_stride(g, r->max_len);
@@ -2239,6 +2243,7 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
     l.reqs = reinterpret_cast<const gst::BatchReq*>(base + o_rq);
     l.tiles = reinterpret_cast<const gst::BatchTile*>(base + o_t[g]);
     l.n_tiles = b->n_tiles[g];
+    l.few = few_tiles(ctx, b->n_tiles[g]) ? 1 : 0;
     l.queue = queues + 16 * g;
     l.ckpt = reinterpret_cast<double*>(base + o_ck);
     l.ckpt_per_team = group_ckpt_stride(g, b->max_len);

@@ -9,201 +9,80 @@
 // depend on which workgroup ran which tile, nor on the other requests of the
 // batch.
 //
-// The per-sequence work is that of the plain sequence kernel (forward chain
-// with checkpoints, readout, objective, seeds, reverse sweep, dG through the
-// LDS stash and MFMA tiles).
+// The per-sequence work is that of the plain sequence kernel (gst_seq.h).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
 #include "gst_device.h"
 #include "gst_internal.h"
+#include "gst_seq.h"
 
 namespace gst {
 namespace {
 
-// The slab reduction reuses the LDS of the staged gate set (as in the plain
-// sequence kernel), so a workgroup restages after every tile that writes a
-// slab; the smaller footprint keeps two or three workgroups per CU.
 // The tile index a workgroup works on sits in the last 16 bytes.  (A static
 // __shared__ variable would be placed before the dynamic area and shift it
 // off the 16-byte alignment that the row reads of ds_read_b128 need.)
-__host__ __device__ inline size_t batch_lds_core(int K) {
-  const size_t a = lds_main_bytes(K), b = lds_red_bytes(K);
-  return ((a > b ? a : b) + 15) / 16 * 16;
-}
+__host__ __device__ inline size_t batch_lds_core(int K) { return (seq_lds_bytes(K) + 15) / 16 * 16; }
 __host__ __device__ inline size_t batch_lds_bytes(int K) { return batch_lds_core(K) + 16; }
 
-template <int D>
-__global__ __launch_bounds__(256) void batch_kernel(const BatchLaunch a) {
+template <int D, int KT, bool PRE>
+__global__ __launch_bounds__(256, seq_waves(PRE)) void batch_kernel(const BatchLaunch a) {
   extern __shared__ double lds_raw[];
   int& tile_sh = *reinterpret_cast<int*>(reinterpret_cast<char*>(lds_raw) + batch_lds_core(a.kmax));
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, team = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, team = lane >> 4;
   int staged = -1;
-  Lds s = carve(lds_raw, a.kmax);
-  double* st_b = s.stash + (size_t)wave * 2 * ENT * 16;
-  double* st_f = st_b + ENT * 16;
-  uint8_t* st_k = s.sk + wave * ENT;
+  const Lds s = carve(lds_raw, a.kmax);
   const int64_t gteam = ((int64_t)blockIdx.x * WAVES + wave) * TPW + team;
   double* ck = a.ckpt + gteam * a.ckpt_per_team;
   for (;;) {
     if (tid == 0) tile_sh = (int)atomicAdd(a.queue, 1u);
     __syncthreads();
-    const int tile = tile_sh;
+    const int tile = uniform(tile_sh);
     __syncthreads();
     if (tile >= a.n_tiles) break;
-    const BatchTile T = a.tiles[tile];
-    const BatchReq R = a.reqs ? a.reqs[T.req] : a.one;
-    const int K = R.K, M = R.M;
-    const auto* g_off = as_global(R.off);
-    const auto* g_order = as_global(R.order);
-    const auto* g_gates = as_global(R.gates);
-    const auto* g_counts = as_global(R.counts);
-    const auto* g_W = as_global(R.W);
-    auto* g_probs = as_global(R.probs);
-    if (T.req != staged) {
-      // a different gate set: restage (carve for this request's K inside the kmax layout)
-      s = carve(lds_raw, a.kmax);
-      stage_gateset_compact<D>(s, R.G, R.E, R.rho, K, M);  // the tile loop is short of registers
-      staged = T.req;
+    const BatchTile* tp = a.tiles + tile;
+    const int req = uniform(tp->req);
+    const int64_t q0 = uniform64(tp->q0);
+    const int nq = (int)(uniform64(tp->q1) - q0);
+    const BatchReq* rp = a.reqs ? a.reqs + req : &a.one;
+    const int K = uniform(rp->K), M = uniform(rp->M), mode = uniform(rp->mode);
+    const auto* g_off = as_global(uniform_ptr(rp->off));
+    const auto* g_order = as_global(uniform_ptr(rp->order));
+    const auto* g_gates = as_global(uniform_ptr(rp->gates));
+    if (req != staged) {
+      stage_gateset_compact<D>(s, rp->G, rp->E, rp->rho, K, M);  // the tile loop is short of registers
+      staged = req;
     }
-    const bool grad = R.want_grad != 0;
-    d4 acc[KMAX];
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) acc[k] = d4{0.0, 0.0, 0.0, 0.0};
-    double obj = 0.0, drho = 0.0;
-    double dE[16];
-#pragma unroll
-    for (int m = 0; m < 16; ++m) dE[m] = 0.0;
-    unsigned bad = 0, nonpos = 0;
-    const int64_t nq = T.q1 - T.q0;
-    const int64_t n_groups = (nq + TPW - 1) / TPW;
-    for (int64_t grp = wave; grp < n_groups; grp += WAVES) {
-      const int64_t qq = T.q0 + grp * TPW + team;
-      const bool has = qq < T.q1;
-      const int64_t seq = has ? (R.order ? g_order[qq] : qq) : 0;
+    const SeqArgs q{K,
+                    M,
+                    mode,
+                    uniform(rp->want_grad) != 0,
+                    g_gates,
+                    as_global(uniform_ptr(rp->counts)),
+                    as_global(uniform_ptr(rp->W)),
+                    as_global(uniform_ptr(rp->probs)),
+                    ck};
+    SeqSums<KT> sum;
+    sum.clear();
+    Pairs* st = wave_pairs(lds_raw, a.kmax, wave);
+    for (int x = wave * TPW + team; x - team < nq; x += WAVES * TPW) {
+      const bool has = x < nq;
+      const int64_t seq = has ? g_order[q0 + x] : 0;
       const int64_t beg = has ? g_off[seq] : 0;
       const int L = has ? (int)(g_off[seq + 1] - beg) : 0;
-      const int Lw = wave_max4(L);
-      const auto* word = g_gates + beg;
-      double f = s.rho[i];
-      // Gate indices are loaded one chunk of 16 steps ahead of their use.
-      // The loads are unconditional (past the end of the word they read the
-      // first index of the list, which always exists) so that the compiler
-      // can wait for the previous load alone.
-      int kv_next = *(i < L ? word + i : g_gates);
-      kv_next = i < L ? kv_next : 0;
-      for (int t0 = 0; t0 < Lw; t0 += 16) {
-        int kv = kv_next;
-        const bool in = t0 + 16 + i < L;
-        kv_next = *(in ? word + t0 + 16 + i : g_gates);
-        kv_next = in ? kv_next : 0;
-        if (t0 + i < L && kv >= K) {
-          ++bad;
-          kv = 0;
-        }
-#define GST_FWD_STEP(RR)                                                   \
-  if (t0 + RR < Lw) {                                                      \
-    const int t = t0 + RR;                                                 \
-    const int k = bcast_i32<RR>(kv);                                       \
-    if (grad && (RR % C) == 0 && t < L) ck[(t / C) * 16 + i] = f;          \
-    const double fn = dot16_bcast(f, grow(s, k, i));                       \
-    f = t < L ? fn : f;                                                    \
-  }
-        GST_FWD_STEP(0) GST_FWD_STEP(1) GST_FWD_STEP(2) GST_FWD_STEP(3)
-        GST_FWD_STEP(4) GST_FWD_STEP(5) GST_FWD_STEP(6) GST_FWD_STEP(7)
-        GST_FWD_STEP(8) GST_FWD_STEP(9) GST_FWD_STEP(10) GST_FWD_STEP(11)
-        GST_FWD_STEP(12) GST_FWD_STEP(13) GST_FWD_STEP(14) GST_FWD_STEP(15)
-#undef GST_FWD_STEP
-      }
-      const double p = dot16_bcast(f, reinterpret_cast<const double2*>(s.Es + i * ROW));
-      double dp = 0.0;
-      if (has && i < M) {
-        const int64_t o = seq * M + i;
-        if (R.probs) g_probs[o] = p;
-        if (R.mode == MODE_LOGLIK) {
-          const int32_t N = g_counts[o];
-          if (N > 0) {
-            if (p <= 0.0) {
-              ++nonpos;
-              obj = INFINITY;
-            } else {
-              obj -= (double)N * log(p);
-              dp = -(double)N / p;
-            }
-          }
-        } else if (R.mode == MODE_VJP) {
-          dp = g_W[o];
-        }
-      }
-      if (!grad) continue;
-#define GST_DE(RR) \
-  if (RR < M) dE[RR] = fma(bcast_f64<RR>(dp), f, dE[RR]);
-      GST_DE(0) GST_DE(1) GST_DE(2) GST_DE(3) GST_DE(4) GST_DE(5) GST_DE(6) GST_DE(7)
-      GST_DE(8) GST_DE(9) GST_DE(10) GST_DE(11) GST_DE(12) GST_DE(13) GST_DE(14) GST_DE(15)
-#undef GST_DE
-      const int nseg = (L + C - 1) / C;
-      const int nsegw = wave_max4(nseg);
-      // segment c needs its C gate indices and its checkpoint; both are
-      // loaded one segment ahead of their use
-      int kv_nx, kv_in;
-      double ck_nx;
-      {
-        const int c = nsegw - 1;
-        const bool seg = c >= 0 && c < nseg;
-        kv_in = seg && i < C && c * C + i < L;
-        kv_nx = *(kv_in ? word + c * C + i : g_gates);
-        ck_nx = *(seg ? ck + c * 16 + i : ck);
-        kv_nx = kv_in ? kv_nx : 0;
-      }
-      double b = dot16_bcast(dp, reinterpret_cast<const double2*>(s.ETs + i * ROW));
-      for (int c = nsegw - 1; c >= 0; --c) {
-        const bool act = c < nseg;
-        const int base = c * C;
-        int kv = kv_in ? kv_nx : 0;
-        if (kv >= K) kv = 0;
-        double fs[C];
-        fs[0] = act ? ck_nx : 0.0;
-        {
-          const bool seg = c >= 1 && c - 1 < nseg;
-          kv_in = seg && i < C && (c - 1) * C + i < L;
-          kv_nx = *(kv_in ? word + (c - 1) * C + i : g_gates);
-          ck_nx = *(seg ? ck + (c - 1) * 16 + i : ck);
-        }
-#define GST_REC(RR)                                          \
-  {                                                          \
-    const int k = bcast_i32<RR - 1>(kv);                     \
-    fs[RR] = dot16_bcast(fs[RR - 1], grow(s, k, i));         \
-  }
-        GST_REC(1) GST_REC(2) GST_REC(3) GST_REC(4) GST_REC(5) GST_REC(6) GST_REC(7)
-#undef GST_REC
-#define GST_BWD(RR)                                          \
-  {                                                          \
-    const bool v = act && (base + RR < L);                   \
-    const int k = bcast_i32<RR>(kv);                         \
-    const int e = team * C + RR;                             \
-    st_b[e * 16 + i] = b;                                    \
-    st_f[e * 16 + i] = fs[RR];                               \
-    if (i == 0) st_k[e] = v ? (uint8_t)k : (uint8_t)0xFF;    \
-    const double bn = dot16(b, load_row(s.GTs + k * GATE_STRIDE + i * ROW)); \
-    b = v ? bn : b;                                          \
-  }
-        GST_BWD(7) GST_BWD(6) GST_BWD(5) GST_BWD(4) GST_BWD(3) GST_BWD(2) GST_BWD(1) GST_BWD(0)
-#undef GST_BWD
-        wave_sync();
-        flush_stash(st_b, st_f, st_k, K, acc, lane);
-        wave_sync();
-      }
-      if (has) drho += b;
+      seq_group<D, KT, PRE>(q, s, st, has, seq, g_gates + beg, L, sum);
     }
-    if (bad) atomicAdd(a.status + 0, (unsigned long long)bad);
-    if (nonpos) {
-      atomicAdd(a.status + 1, (unsigned long long)nonpos);
-      atomicAdd(a.req_nonpos + T.req, (unsigned long long)nonpos);
+    if (sum.bad) atomicAdd(a.status + 0, (unsigned long long)sum.bad);
+    if (sum.nonpos) {
+      atomicAdd(a.status + 1, (unsigned long long)sum.nonpos);
+      atomicAdd(a.req_nonpos + req, (unsigned long long)sum.nonpos);
     }
-    if (grad || R.mode == MODE_LOGLIK) {
-      write_slab<D>(lds_raw, obj, drho, dE, acc, M, K, R.slab + (int64_t)T.local * slab_width(D, M, K));
-      staged = -1;
+    if (q.grad || mode == MODE_LOGLIK) {
+      write_slab<D, KT>(lds_raw + lds_main_bytes(a.kmax) / 8, sum, M, K,
+                        rp->slab + (int64_t)tp->local * slab_width(D, M, K));
+      __syncthreads();  // the row has been read
     }
   }
 }
@@ -279,20 +158,32 @@ __global__ __launch_bounds__(256) void batch_reduce_final_kernel(const BatchRedu
 
 size_t batch_lds(int kmax) { return batch_lds_bytes(kmax); }
 
-int batch_blocks_per_cu(int D, int kmax) {
+// Accumulators for six gates cover the two-qubit configurations; with more the
+// gate set leaves room for two workgroups per CU, and one-qubit requests come
+// here with more than four gates only: those load ahead whatever their number.
+// `few`: the launch's tiles fill at most two workgroups per CU.
+int batch_blocks_per_cu(int D, int kmax, bool few) {
   int n = 0;
   const size_t bytes = batch_lds_bytes(kmax);
-  hipError_t e = D == 16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<16>, 256, bytes)
-                         : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<4>, 256, bytes);
+  const hipError_t e =
+      D != 16    ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<4, KMAX, true>, 256, bytes)
+      : kmax > 6 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<16, KMAX, true>, 256, bytes)
+      : few      ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<16, 6, true>, 256, bytes)
+                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<16, 6, false>, 256, bytes);
   return (e == hipSuccess && n > 0) ? n : 1;
 }
 
 hipError_t launch_batch(const BatchLaunch& a, int n_blocks, hipStream_t stream) {
   const size_t bytes = batch_lds_bytes(a.kmax);
-  if (a.D == 16)
-    gst_launch(batch_kernel<16>, dim3(n_blocks), dim3(256), bytes, stream, a);
+  if (a.kmax < 1 || a.kmax > KMAX) return hipErrorInvalidValue;
+  if (a.D == 16 && a.kmax <= 6 && !a.few)
+    gst_launch(batch_kernel<16, 6, false>, dim3(n_blocks), dim3(256), bytes, stream, a);
+  else if (a.D == 16 && a.kmax <= 6)
+    gst_launch(batch_kernel<16, 6, true>, dim3(n_blocks), dim3(256), bytes, stream, a);
+  else if (a.D == 16)
+    gst_launch(batch_kernel<16, KMAX, true>, dim3(n_blocks), dim3(256), bytes, stream, a);
   else if (a.D == 4)
-    gst_launch(batch_kernel<4>, dim3(n_blocks), dim3(256), bytes, stream, a);
+    gst_launch(batch_kernel<4, KMAX, true>, dim3(n_blocks), dim3(256), bytes, stream, a);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -17,7 +17,6 @@ constexpr int ROW = 18;                // padded LDS row stride in doubles
 constexpr int GATE_STRIDE = 16 * ROW;  // doubles per gate matrix in LDS
 constexpr int KMAX = 8;                // gates accumulated on chip
 constexpr int C = 8;                   // steps per reverse segment (checkpoint interval)
-constexpr int ENT = TPW * C;           // stash entries per wave (<= 64)
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
@@ -128,6 +127,13 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// A pointer that every lane has the same value of, in scalar registers (one read
+// from memory by a vector load is in vector registers).
+template <class T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+  return reinterpret_cast<T*>(uniform64(reinterpret_cast<int64_t>(p)));
+}
+
 // A pointer read from memory is generic to the compiler, and a generic (flat)
 // load is counted by both vmcnt and lgkmcnt, so the first LDS wait after it
 // also waits for it.  This cast states that the pointer addresses global
@@ -171,8 +177,7 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // ---------------------------------------------------------------------------
-// LDS layout (doubles): Gs[K][16][ROW] | GTs[K][16][ROW] | Es[16][ROW] | ETs[16][ROW] |
-//   rho[16] | per wave stash: b[ENT][16], f[ENT][16] | stash gate bytes [WAVES][ENT]
+// LDS layout (doubles): Gs[K][16][ROW] | GTs[K][16][ROW] | Es[16][ROW] | ETs[16][ROW] | rho[16]
 // ---------------------------------------------------------------------------
 struct Lds {
   double* Gs;
@@ -180,23 +185,14 @@ struct Lds {
   double* Es;
   double* ETs;
   double* rho;
-  double* stash;
-  uint8_t* sk;
 };
 
 __host__ __device__ inline size_t lds_main_bytes(int K) {
-  size_t d = (size_t)2 * K * GATE_STRIDE + 2 * 16 * ROW + 16 + (size_t)WAVES * 2 * ENT * 16;
-  return d * 8 + (size_t)WAVES * ENT;
+  return ((size_t)2 * K * GATE_STRIDE + 2 * 16 * ROW + 16) * 8;
 }
 
-__host__ __device__ inline size_t lds_red_bytes(int K) {
-  return (size_t)WAVES * (1 + 16 + 256 + (size_t)K * 256) * 8;
-}
-
-__host__ inline size_t lds_bytes(int K) {
-  const size_t a = lds_main_bytes(K), b = lds_red_bytes(K);
-  return a > b ? a : b;
-}
+// One row of partial sums, added wave by wave.
+__host__ __device__ inline size_t lds_red_bytes(int K) { return (1 + 16 + 256 + (size_t)K * 256) * 8; }
 
 __device__ __forceinline__ Lds carve(double* base, int K) {
   Lds l;
@@ -205,8 +201,6 @@ __device__ __forceinline__ Lds carve(double* base, int K) {
   l.Es = l.GTs + (size_t)K * GATE_STRIDE;
   l.ETs = l.Es + 16 * ROW;
   l.rho = l.ETs + 16 * ROW;
-  l.stash = l.rho + 16;
-  l.sk = reinterpret_cast<uint8_t*>(l.stash + (size_t)WAVES * 2 * ENT * 16);
   return l;
 }
 
@@ -305,102 +299,6 @@ __device__ __forceinline__ const double2* grow(const Lds& s, int k, int i) {
 }
 __device__ __forceinline__ const double2* gtrow(const Lds& s, int k, int i) {
   return reinterpret_cast<const double2*>(s.GTs + k * GATE_STRIDE + i * ROW);
-}
-
-// dG_k += sum over the wave's stashed steps with gate k of b f^T, four steps
-// per MFMA 16x16x4 (A[i][z] = b_z[i], B[z][j] = f_z[j]).
-__device__ __forceinline__ void flush_stash(const double* st_b, const double* st_f, const uint8_t* st_k, int K,
-                                            d4 (&acc)[KMAX], int lane) {
-  const int i = lane & 15;
-  const int my_k = lane < ENT ? (int)st_k[lane] : 0xFF;
-#pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-    if (k < K) {
-      unsigned long long mask = __ballot(my_k == k);
-      while (mask) {
-        int e4[4];
-#pragma unroll
-        for (int z = 0; z < 4; ++z) {
-          if (mask) {
-            e4[z] = __ffsll((long long)mask) - 1;
-            mask &= mask - 1;
-          } else {
-            e4[z] = -1;
-          }
-        }
-        const int sel = lane >> 4;
-        const int e = sel == 0 ? e4[0] : sel == 1 ? e4[1] : sel == 2 ? e4[2] : e4[3];
-        const double av = e >= 0 ? st_b[e * 16 + i] : 0.0;
-        const double bv = e >= 0 ? st_f[e * 16 + i] : 0.0;
-        acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[k], 0, 0, 0);
-      }
-    }
-  }
-}
-
-// Adds the four chains of each wave and the four waves and writes the slab
-// row `slab` = [objective | drho (D) | dE (M*D) | dG (K*D*D)] (the caller
-// picks the row).  Reuses the LDS from its start: the staged gate set is
-// overwritten.
-template <int D>
-__device__ void write_slab(double* lds_raw, double obj, double drho, double (&dE)[16], d4 (&acc)[KMAX], int M,
-                           int K, double* slab) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  __syncthreads();  // LDS is reused from here on
-  const int P16 = 1 + 16 + 256 + K * 256;
-  double* mine = lds_raw + (size_t)wave * P16;
-  double o = obj;
-#pragma unroll
-  for (int sh = 1; sh < 64; sh <<= 1) o += __shfl_xor(o, sh);
-  double dr = drho;
-  dr += __shfl_xor(dr, 16);
-  dr += __shfl_xor(dr, 32);
-#pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    dE[m] += __shfl_xor(dE[m], 16);
-    dE[m] += __shfl_xor(dE[m], 32);
-  }
-  if (lane == 0) mine[0] = o;
-  if (lane < 16) {
-    mine[1 + lane] = dr;
-#pragma unroll
-    for (int m = 0; m < 16; ++m) mine[17 + m * 16 + lane] = dE[m];
-  }
-  // tile element C[r][c] sits in lane 16*(r&3)+c, register r>>2
-#pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-    if (k < K) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int r = 4 * v + (lane >> 4), c = lane & 15;
-        mine[273 + k * 256 + r * 16 + c] = acc[k][v];
-      }
-    }
-  }
-  __syncthreads();
-  const int64_t P = slab_width(D, M, K);
-  double* out = slab;
-  const double* red = lds_raw;
-  for (int x = tid; x < P; x += blockDim.x) {
-    int src;
-    if (x == 0) {
-      src = 0;
-    } else if (x < 1 + D) {
-      src = x;
-    } else if (x < 1 + D + M * D) {
-      const int y = x - 1 - D;
-      src = 17 + (y / D) * 16 + (y % D);
-    } else {
-      const int y = x - 1 - D - M * D;
-      const int k = y / (D * D), r = (y / D) % D, c = y % D;
-      src = 273 + k * 256 + r * 16 + c;
-    }
-    double v = red[src];
-    v += red[P16 + src];
-    v += red[2 * P16 + src];
-    v += red[3 * P16 + src];
-    out[x] = v;
-  }
 }
 
 // C = A B for 16 x 16 matrices in the gate layout (LDS), by one wave on the

@@ -34,22 +34,17 @@ inline void gst_launch(F kernel, dim3 grid, dim3 block, size_t lds, hipStream_t 
 // Evaluation modes of the sequence kernel.
 enum Mode : int { MODE_PROBS = 0, MODE_LOGLIK = 1, MODE_VJP = 2 };
 
-// One launch of the sequence ("leaf") kernel.  A work item is one sequence:
-// the chain starts at a stored anchor state (or at rho) and applies the
-// gates gate_idx[beg .. end) in time order; the readout belongs to sequence
-// `seq` (row of counts / probs / w).
+// One launch of the sequence ("leaf") kernel: sequence q of (off, gates) starts
+// at rho and applies its gates in time order.
 struct LeafLaunch {
   int D, M, K;                 // D = 4^n (4, 16 or 64)
+  int few;                     // at most two workgroups per CU: the variant that loads rows ahead
   const double* rho;           // [D]
   const double* E;             // [M][D]
   const double* G;             // [K][D][D]
   int64_t n_items;
-  // item table; if items == nullptr, item q is sequence q of (off, gates)
   const int64_t* off;          // [S+1]
   const uint8_t* gates;        // [off[S]]
-  const int64_t* items;        // [n_items][4]: seq, beg, end, anchor node (-1 = rho) or null
-  const double* anchor_states; // [n_nodes][D] states of stored trie nodes
-  double* anchor_adj;          // [n_items][D] adjoint at the anchor (trie mode) or null
   const int32_t* counts;       // [S][M]  (MODE_LOGLIK)
   const double* W;             // [S][M]  (MODE_VJP)
   double* probs;               // [S][M] or null
@@ -204,6 +199,7 @@ struct BatchLaunch {
   BatchReq one;
   const BatchTile* tiles;
   int n_tiles;
+  int few;                         // at most two workgroups per CU: the variant that loads rows ahead
   unsigned* queue;
   double* ckpt;
   int64_t ckpt_per_team;
@@ -233,7 +229,7 @@ int lane1q_ckpt_per_wave(int64_t max_len);
 int lane1q_blocks_per_cu(int K);
 hipError_t launch_lane1q(const BatchLaunch& a, int K, int n_blocks, hipStream_t stream);
 // Resident workgroups per CU of the batched kernel (occupancy with its LDS).
-int batch_blocks_per_cu(int D, int kmax);
+int batch_blocks_per_cu(int D, int kmax, bool few);
 hipError_t launch_batch(const BatchLaunch& a, int n_blocks, hipStream_t stream);
 hipError_t launch_queue_reset(unsigned* q, unsigned long long* req_nonpos, int n_req, hipStream_t stream);
 // Chunks of the two-stage tile-slab sum for a request of n_tiles tiles; the

@@ -123,8 +123,6 @@ __device__ __forceinline__ Lds carve_trunk(double* base, int K) {
   l.Es = nullptr;
   l.ETs = nullptr;
   l.rho = base + (size_t)K * GATE_STRIDE;
-  l.stash = nullptr;
-  l.sk = nullptr;
   return l;
 }
 __host__ __device__ inline size_t trunk_inj_doubles(int K) { return (size_t)K * GATE_STRIDE + 16; }
