@@ -60,3 +60,34 @@ def test_team_kernels(oracle_lib, gpu, kind, K, S, lengths):
         assert abs(float(obj.cpu()[0]) - F) <= 1e-10 * abs(F), label
         assert np.abs(g.cpu().numpy() - g_or).max() <= 1e-10 * np.abs(g_or).max(), label
     req.close()
+
+
+@pytest.mark.parametrize("K,S,lengths", [
+    (1, 63, (9, 3)), (2, 64, (16,)), (3, 65, (8, 7, 0, 1)), (4, 130, (17, 24, 16, 40)), (3, 200, (33,)),
+    (2, 1, (15,)), (4, 256, (8,)), (4, 1000, (31, 32, 33)),
+])
+def test_lane_kernel(oracle_lib, gpu, K, S, lengths):
+    """One chain per lane: tiles of 64 words, full and not; segments of 8 that all words of a tile run through and not."""
+    api, ctx = gpu
+    rng = np.random.default_rng([K, S, len(lengths)])
+    m = _model("1q", K, rng)
+    sl = W.from_words([rng.integers(0, K, size=lengths[s % len(lengths)]).tolist() for s in range(S)])
+    counts = rng.integers(0, 40, size=(S, m.M)).astype(np.int32)
+    counts[oracle_lib.probs(m.rho, m.effects, m.gates, sl.offsets, sl.gates) <= 0] = 0
+    F, p_or, g_or, _, rc = oracle_lib.loglik(m.rho, m.effects, m.gates, sl.offsets, sl.gates, counts)
+    assert rc == 0
+    gs = api.DeviceGateSet.from_numpy(m.n_qubits, m.rho, m.effects, m.gates)
+    req = api.Request(ctx, m.n_qubits, K, m.M, sl.offsets, sl.gates, counts)
+    bt = api.Batch(ctx, [req], [gs], want_probs=True, want_grad=True)
+
+    def batch():
+        bt.run()
+        return bt.obj[0], bt.probs[0], bt.grad[0]
+    for label, call in (("batch", batch), ("request", lambda: req.eval(gs, want_probs=True))):
+        obj, p, g = call()
+        ctx.sync()
+        assert np.array_equal(p.cpu().numpy(), p_or), label
+        assert abs(float(obj.cpu()[0]) - F) <= 1e-10 * abs(F), label
+        assert np.abs(g.cpu().numpy() - g_or).max() <= 1e-10 * np.abs(g_or).max(), label
+    bt.close()
+    req.close()
