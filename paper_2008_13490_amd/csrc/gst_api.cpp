@@ -253,10 +253,10 @@ struct DevicePlan {
   uint8_t* fill_gate3 = nullptr;
 };
 
-// Levels whose longest chain has at least this many steps run the sweeps
-// with the gate operands held in registers (loaded once per tile); the others
-// load each step's operands (a tile of a few steps would load all K gates for
-// nothing).
+// Levels whose longest chain has at least this many steps run the sweeps four
+// chains to a workgroup with the gate operands held in registers (loaded once);
+// the others sixteen, loading each step's operands (a tile of a few steps would
+// load all K gates for nothing).
 constexpr int kRegGateSteps = 32;
 
 // Device copy of a three-qubit grouped-chain plan (gst_plan64.h) with its
@@ -929,6 +929,7 @@ static gst::Plan64Req plan64_req(gst_req* r, const gst_gateset* th, int mode, co
     g.FA = d.FA;
     g.tile_row0 = d.tile_row0;
     g.col_anchor = d.col_anchor;
+    g.col_chain = d.col_chain;
     g.ts_tile = d.ts_tile;
     g.ts_step = d.ts_step;
     g.chunk_beg = d.chunk_beg;
@@ -1617,8 +1618,9 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   std::vector<int64_t> gcp64;
   // three-qubit lists with deep sharing: the grouped-chain plan instead
   gst::Plan64 p64;
-  const bool use_p64 = D == 64 && S > 0 && gst::build_plan64(sl->offsets, sl->gate_idx, S, n_gates,
-                                                              gst::Plan64Options(), &p64);
+  gst::Plan64Options opt64;
+  if (D == 64) opt64.ts_blocks = gst::gemm64_ts_blocks_per_cu() * ctx->n_cu;
+  const bool use_p64 = D == 64 && S > 0 && gst::build_plan64(sl->offsets, sl->gate_idx, S, n_gates, opt64, &p64);
   if (D == 64 && !use_p64) {
     const int64_t per = (S + 2 * ctx->n_cu - 1) / (2 * ctx->n_cu);
     const int64_t want = ctx->tune_tile[3] > 0 ? ctx->tune_tile[3] : per;

@@ -316,6 +316,7 @@ struct Gemm64TsLaunch {
   const double* FA;
   const int64_t* tile_row0;
   const int64_t* col_anchor;
+  const int64_t* col_chain;  // -1: no chain (columns are filled from the first)
   const int64_t* ts_tile;
   const int32_t* ts_step;
   const int64_t* chunk_beg;
@@ -323,7 +324,8 @@ struct Gemm64TsLaunch {
   double* slab;              // [n_chunks][4096]
   int n_chunks;
 };
-constexpr int GEMM64_TS_CHUNK_MAX = 64;  // tile-steps per chunk at most (staged in LDS)
+constexpr int GEMM64_TS_CHUNK_MAX = 96;  // tile-steps per chunk at most (staged in LDS)
+int gemm64_ts_blocks_per_cu();
 hipError_t launch_gemm64_ts(const Gemm64TsLaunch& a, hipStream_t stream);
 constexpr int READOUT64_WAVES = 4;
 struct Readout64Launch {
@@ -356,8 +358,8 @@ struct Root64Launch {        // the adjoint of rho: root seed + chains anchored 
 };
 hipError_t launch_gate_prep64(const double* G, const double* rho, int K, double* GA, double* GAT, double* FA,
                               hipStream_t stream);
-hipError_t launch_plan64_fwd(const Plan64Launch& a, int n_tiles, bool reg_gates, hipStream_t stream);
-hipError_t launch_plan64_bwd(const Plan64Launch& a, int n_tiles, bool reg_gates, hipStream_t stream);
+hipError_t launch_plan64_fwd(const Plan64Launch& a, int n_tiles, bool long_chains, hipStream_t stream);
+hipError_t launch_plan64_bwd(const Plan64Launch& a, int n_tiles, bool long_chains, hipStream_t stream);
 hipError_t launch_readout64(const Readout64Launch& a, int n_blocks, hipStream_t stream);
 hipError_t launch_root64(const Root64Launch& a, hipStream_t stream);
 int readout64_blocks_per_cu();
@@ -394,10 +396,10 @@ struct Plan64Req {
   Reduce64Launch r64;         // r64.grad = null: no gate columns
 };
 hipError_t launch_gate_prep64_batch(const Plan64Req* reqs, int n, int K_max, hipStream_t stream);
-hipError_t launch_plan64_fwd_batch(const Plan64Req* reqs, int n, int level, int grid_x, bool reg_gates,
+hipError_t launch_plan64_fwd_batch(const Plan64Req* reqs, int n, int level, int grid_x, bool long_chains,
                                    hipStream_t stream);
 hipError_t launch_readout64_batch(const Plan64Req* reqs, int n, int grid_x, hipStream_t stream);
-hipError_t launch_plan64_bwd_batch(const Plan64Req* reqs, int n, int level, int grid_x, bool reg_gates,
+hipError_t launch_plan64_bwd_batch(const Plan64Req* reqs, int n, int level, int grid_x, bool long_chains,
                                    hipStream_t stream);
 hipError_t launch_gemm64_ts_batch(const Plan64Req* reqs, int n, int grid_x, hipStream_t stream);
 hipError_t launch_root64_batch(const Plan64Req* reqs, int n, hipStream_t stream);

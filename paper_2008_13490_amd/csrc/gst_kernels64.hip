@@ -421,53 +421,17 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // a step's row of 
 // banks.
 constexpr int VST = 66;
 
-// Where a step's gate operands come from.  RegGates: a wave's operand blocks of
-// all K <= 5 gates (16 doubles per lane each) stay in registers for the whole
-// sweep and a step picks its gate by a uniform branch, so the vector memory
-// path carries only the stored states, not 32 KB of gate operands per
-// tile-step; for the levels with long chains.  LoadGates: the operands of the
-// next step are loaded while the current one runs; for levels of short
-// chains, where loading all K gates up front would cost more than the steps.
-struct RegGates {
-  static constexpr bool kReg = true;
-  double g[5][16];
-  __device__ __forceinline__ void init(const double* base, int K, int w, int l) {
-#pragma unroll
-    for (int k = 0; k < 5; ++k)
-      if (k < K) load_ops(g[k], base + ((int64_t)k * 4 + w) * 1024, l);
-  }
-  __device__ __forceinline__ void start(const double*, int, int, int) {}
-  // the wave's 16 x 64 block of gate k times B, sixteen MFMAs in ascending k
-  __device__ __forceinline__ d4 product(const double*, int k, int, const double* B, int w, int l) {
-    (void)w;
-    d4 acc = {0.0, 0.0, 0.0, 0.0};
-    switch (k) {
-#define GST_P64_CASE(K)                                                                    \
-  case K:                                                                                  \
-    _Pragma("unroll") for (int kk = 0; kk < 16; ++kk)                                      \
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(g[K][kk], B[kk * VST + l], acc, 0, 0, 0);  \
-    break;
-      GST_P64_CASE(0) GST_P64_CASE(1) GST_P64_CASE(2) GST_P64_CASE(3)
-      default:
-        GST_P64_CASE(4)
-#undef GST_P64_CASE
-    }
-    return acc;
-  }
-};
-
+// Levels of short chains: the operands of the next step's gate are loaded while
+// the current step runs.
 struct LoadGates {
-  static constexpr bool kReg = false;
   double an[16];
-  __device__ __forceinline__ void init(const double*, int, int, int) {}
   __device__ __forceinline__ void start(const double* base, int k, int w, int l) {
     load_ops(an, base + ((int64_t)k * 4 + w) * 1024, l);
   }
-  // operands of gate k (loaded a step ago); each register takes gate k_next's
-  // operand (< 0: none) as soon as its MFMA has read it, so one set of 16
+  // the gate loaded a step ago times B; each register takes gate k_next's operand
+  // (< 0: none) as soon as its MFMA has read it, so one set of 16
   // registers serves both
-  __device__ __forceinline__ d4 product(const double* base, int k, int k_next, const double* B, int w, int l) {
-    (void)k;
+  __device__ __forceinline__ d4 product(const double* base, int k_next, const double* B, int w, int l) {
     d4 acc = {0.0, 0.0, 0.0, 0.0};
     if (k_next >= 0) {
       const auto* g = as_global(base + ((int64_t)k_next * 4 + w) * 1024);
@@ -503,7 +467,6 @@ __device__ __forceinline__ void store_tile_rows(const double* V, double* out, in
   }
 }
 
-template <class Gates>
 __device__ __forceinline__ void plan64_fwd_body(const Plan64Launch& a, int64_t tile) {
   __shared__ double Vs[2][16 * VST];
   __shared__ uint8_t Ws[CH_STEPS + 1];
@@ -511,8 +474,7 @@ __device__ __forceinline__ void plan64_fwd_body(const Plan64Launch& a, int64_t t
   const int c = l & 15, r4 = l >> 4;
   const int64_t anc = a.col_anchor[tile * 16 + c];
   const auto* fa = as_global(a.FA);
-  Gates gs;
-  gs.init(a.GA, a.K, w, l);
+  LoadGates gs;
 #pragma unroll
   for (int v = 0; v < 4; ++v) Vs[0][(4 * w + v) * VST + l] = fa[anc * N64 + 4 * (4 * w + v) + r4];
   const int len = uniform(a.tile_len[tile]);
@@ -527,7 +489,7 @@ __device__ __forceinline__ void plan64_fwd_body(const Plan64Launch& a, int64_t t
     if (t0 == 0) gs.start(a.GA, uniform(Ws[0]), w, l);
     for (int x = 0; x < n; ++x) {
       const int t = t0 + x;
-      const d4 acc = gs.product(a.GA, uniform(Ws[x]), t + 1 < len ? uniform(Ws[x + 1]) : -1, Vs[cur], w, l);
+      const d4 acc = gs.product(a.GA, t + 1 < len ? uniform(Ws[x + 1]) : -1, Vs[cur], w, l);
       // rows 16w + 4v + r4 of column c: operand block kk = 4w + v of the next step
       // (stored straight from the registers: measured faster here than the
       // row-wise stores through LDS that the reverse sweep uses)
@@ -543,9 +505,8 @@ __device__ __forceinline__ void plan64_fwd_body(const Plan64Launch& a, int64_t t
   }
 }
 
-template <class Gates>
 __global__ __launch_bounds__(256) void plan64_fwd_kernel(const Plan64Launch a) {
-  plan64_fwd_body<Gates>(a, a.t_begin + blockIdx.x);
+  plan64_fwd_body(a, a.t_begin + blockIdx.x);
 }
 
 // Rows 4(4w + v) + r4 of the INJ rows that events of one node add to column c:
@@ -557,18 +518,19 @@ __global__ __launch_bounds__(256) void plan64_fwd_kernel(const Plan64Launch a) {
 // most events of one column at this step (a uniform count); a lane with fewer
 // loads rows of the step's other events, which `n` masks out where they are
 // added.
-template <int W>
+// R rows of a column per lane, the first of them row0, four apart.
+template <int W, int R>
 struct NodeAdds {
-  double r[W][4];
+  double r[W][R];
   int n;     // this column's events at the node
   int most;  // the most events of one column at the node (uniform)
 };
 
 // Events e0 .. e0 + W - 1 of the node (a window of W rows; a node has up to
 // EV_NODE, so a window smaller than that is loaded in several rounds).
-template <int W>
-__device__ __forceinline__ void load_node_adds(NodeAdds<W>& q, const int32_t* Es, const int32_t* Ev, const u32x4* Cc,
-                                               int x, int e0, int c, int w, int r4, const double* inj) {
+template <int W, int R>
+__device__ __forceinline__ void load_node_adds(NodeAdds<W, R>& q, const int32_t* Es, const int32_t* Ev, const u32x4* Cc,
+                                               int x, int e0, int c, int row0, const double* inj) {
   const auto* g = as_global(inj);
   const int jb = uniform(Es[x]), tot = uniform(Es[x + 1]) - jb;
   const auto* row = reinterpret_cast<const uint8_t*>(Cc + x);
@@ -584,19 +546,19 @@ __device__ __forceinline__ void load_node_adds(NodeAdds<W>& q, const int32_t* Es
 #pragma unroll
   for (int e = 0; e < W; ++e)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) q.r[e][v] = 0.0;
+    for (int v = 0; v < R; ++v) q.r[e][v] = 0.0;
 #pragma unroll
   for (int e = 0; e < W; ++e)
     if (e0 + e < q.most)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) q.r[e][v] = g[(int64_t)src[e] * N64 + 4 * (4 * w + v) + r4];
+      for (int v = 0; v < R; ++v) q.r[e][v] = g[(int64_t)src[e] * N64 + row0 + 4 * v];
 }
 
 // Adds the window's events to `add` in their order (absent ones add zero); the
 // first window starts the sum with its first row, so the node's sum is the same
 // chain of additions whatever the window.
-template <int W>
-__device__ __forceinline__ double node_add(const NodeAdds<W>& q, int e0, double add, int v) {
+template <int W, int R>
+__device__ __forceinline__ double node_add(const NodeAdds<W, R>& q, int e0, double add, int v) {
 #pragma unroll
   for (int e = 0; e < W; ++e) {
     const double r = e0 + e < q.n ? q.r[e][v] : 0.0;
@@ -606,16 +568,56 @@ __device__ __forceinline__ double node_add(const NodeAdds<W>& q, int e0, double 
 }
 
 // A node's events summed: the first window loaded earlier (q), the others now.
-template <int W>
-__device__ __forceinline__ void node_sum(NodeAdds<W>& q, const int32_t* Es, const int32_t* Ev, const u32x4* Cc, int x,
-                                         int c, int w, int r4, const double* inj, double (&add)[4]) {
+template <int W, int R>
+__device__ __forceinline__ void node_sum(NodeAdds<W, R>& q, const int32_t* Es, const int32_t* Ev, const u32x4* Cc, int x,
+                                         int c, int row0, const double* inj, double (&add)[R]) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) add[v] = node_add(q, 0, 0.0, v);
+  for (int v = 0; v < R; ++v) add[v] = node_add(q, 0, 0.0, v);
   for (int e0 = W; e0 < q.most; e0 += W) {
-    load_node_adds(q, Es, Ev, Cc, x, e0, c, w, r4, inj);
+    load_node_adds(q, Es, Ev, Cc, x, e0, c, row0, inj);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) add[v] = node_add(q, e0, add[v], v);
+    for (int v = 0; v < R; ++v) add[v] = node_add(q, e0, add[v], v);
   }
+}
+
+// A chunk of a tile's reverse sweep, staged in LDS: the steps [t0, t1) with at
+// most CH_STEPS steps and CH_EVENTS events, and the events of step t0 - 1, which
+// are added at the end of step t0.
+struct ChunkLds {
+  // Ws[x] = word[t0 - 1 + x] (x = 0 only if t0 > 0), EV_FLAG set if the step
+  // before it has events
+  uint8_t Ws[CH_STEPS + 1];
+  int32_t Es[CH_STEPS + 2];     // events before step s0 + x
+  int32_t Ev[CH_EVENTS];
+  u32x4 Cc[CH_STEPS + 1];       // the column table of step s0 + x
+};
+constexpr int EV_FLAG = 0x80;  // (K <= 5)
+
+struct Chunk {
+  int t0, s0;
+};
+
+__device__ __forceinline__ Chunk stage_chunk(ChunkLds& S, const Plan64Launch& a, int64_t tile, int t1, int tid) {
+  const auto* word = as_global(a.words + a.tile_word[tile]);
+  const int64_t tev = a.tile_ev[tile];
+  const auto* evp = as_global(a.ev_ptr + tev);
+  const auto* cend = as_global(reinterpret_cast<const u32x4*>(a.ev_cend) + tev);
+  const auto* evs = as_global(a.ev_src);
+  int t0 = t1 - CH_STEPS > 0 ? t1 - CH_STEPS : 0;
+  const int64_t e1 = uniform64(evp[t1]);
+  while (t1 - t0 > 1 && uniform64(evp[t0 > 0 ? t0 - 1 : 0]) + CH_EVENTS < e1) t0 = t1 - (t1 - t0) / 2;
+  const int s0 = t0 > 0 ? t0 - 1 : 0;
+  const int64_t e0 = uniform64(evp[s0]);
+  for (int x = tid; x <= t1 - t0; x += 256)
+    if (x > 0 || t0 > 0) {
+      const int t = t0 - 1 + x;
+      S.Ws[x] = word[t] | (t > 0 && evp[t] > evp[t - 1] ? EV_FLAG : 0);
+    }
+  for (int x = tid; x <= t1 - s0; x += 256) S.Es[x] = (int32_t)(evp[s0 + x] - e0);
+  for (int x = tid; x < t1 - s0; x += 256) S.Cc[x] = cend[s0 + x];
+  for (int j = tid; j < (int)(e1 - e0); j += 256) S.Ev[j] = (int32_t)evs[e0 + j];
+  lds_barrier();
+  return Chunk{t0, s0};
 }
 
 // Reverse sweep of a tile.  b_t, the adjoint of the node after step t, is
@@ -624,86 +626,42 @@ __device__ __forceinline__ void node_sum(NodeAdds<W>& q, const int32_t* Es, cons
 // events of node t-1 added becomes b_{t-1}.  The events' rows are loaded while
 // the step's product runs, the next gate's operands a step ahead.  At the end each
 // chain delivers G_0^T b_0 to its anchor.
-template <class Gates, int EVW>
+constexpr int EV_WINDOW = 3;  // events of a node held at once (more cost occupancy)
 __device__ __forceinline__ void plan64_bwd_body(const Plan64Launch& a, int64_t tile) {
   __shared__ double Bs[2][16 * VST];
-  __shared__ uint8_t Ws[CH_STEPS + 1];
-  __shared__ int32_t Es[CH_STEPS + 2];
-  __shared__ int32_t Ev[CH_EVENTS];
-  __shared__ u32x4 Cc[CH_STEPS + 1];
-  __shared__ unsigned long long Em[5];  // bit x: step s0 + x of the chunk has events
+  __shared__ ChunkLds S;
   const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
-  const int c = l & 15, r4 = l >> 4;
+  const int c = l & 15, r4 = l >> 4, row = 16 * w + r4;
   const int len = uniform(a.tile_len[tile]);
-  const auto* word = as_global(a.words + a.tile_word[tile]);
   const int64_t row0 = a.tile_row0[tile];
-  const int64_t tev = a.tile_ev[tile];
-  const auto* evp = as_global(a.ev_ptr + tev);
-  const auto* cend = as_global(reinterpret_cast<const u32x4*>(a.ev_cend) + tev);
-  const auto* evs = as_global(a.ev_src);
-  Gates gs;
-  gs.init(a.GAT, a.K, w, l);
+  LoadGates gs;
   int cur = 0;
   for (int t1 = len; t1 > 0;) {
-    // chunk [t0, t1) with at most CH_STEPS steps and CH_EVENTS events
-    // (and the events of step t0 - 1, added at the end of step t0)
-    int t0 = t1 - CH_STEPS > 0 ? t1 - CH_STEPS : 0;
-    const int64_t e1 = uniform64(evp[t1]);
-    while (t1 - t0 > 1 && uniform64(evp[t0 > 0 ? t0 - 1 : 0]) + CH_EVENTS < e1) t0 = t1 - (t1 - t0) / 2;
-    const int s0 = t0 > 0 ? t0 - 1 : 0;
-    const int64_t e0 = uniform64(evp[s0]);
-    const int n = t1 - t0;
-    // Ws[x] = word[t0 - 1 + x] (x = 0 only if t0 > 0); Es[x] = events before
-    // step s0 + x; Cc[x] = the column table of step s0 + x
-    for (int x = tid; x <= n; x += 256)
-      if (x > 0 || t0 > 0) Ws[x] = word[t0 - 1 + x];
-    for (int x = tid; x <= t1 - s0; x += 256) Es[x] = (int32_t)(evp[s0 + x] - e0);
-    for (int x = tid; x < t1 - s0; x += 256) Cc[x] = cend[s0 + x];
-    for (int j = tid; j < (int)(e1 - e0); j += 256) Ev[j] = (int32_t)evs[e0 + j];
-    {
-      // which of the chunk's steps have events: a step without any skips the
-      // lookup (the steps s0 .. t1 - 1, at most CH_STEPS + 1)
-      const int xa = tid, xb = tid + 256;
-      const bool fa = xa < t1 - s0 && evp[s0 + xa + 1] > evp[s0 + xa];
-      const bool fb = xb < t1 - s0 && evp[s0 + xb + 1] > evp[s0 + xb];
-      const unsigned long long ba = __ballot(fa), bb = __ballot(fb);
-      if (l == 0) {
-        Em[w] = ba;
-        if (w == 0) Em[4] = bb;
-      }
-    }
-    lds_barrier();
-    const unsigned long long em0 = uniform64((int64_t)Em[0]), em1 = uniform64((int64_t)Em[1]),
-                             em2 = uniform64((int64_t)Em[2]), em3 = uniform64((int64_t)Em[3]),
-                             em4 = uniform64((int64_t)Em[4]);
-    auto has_events = [&](int xs) {
-      const int wi = xs >> 6;
-      const unsigned long long b = wi == 0 ? em0 : wi == 1 ? em1 : wi == 2 ? em2 : wi == 3 ? em3 : em4;
-      return ((b >> (xs & 63)) & 1ull) != 0;
-    };
+    const Chunk ck = stage_chunk(S, a, tile, t1, tid);
+    const int t0 = ck.t0, s0 = ck.s0, n = t1 - t0;
     if (t1 == len) {
       // b of the last node: its events alone
-      NodeAdds<EVW> q;
-      load_node_adds(q, Es, Ev, Cc, t1 - 1 - s0, 0, c, w, r4, a.INJ);
+      NodeAdds<EV_WINDOW, 4> q;
+      load_node_adds(q, S.Es, S.Ev, S.Cc, t1 - 1 - s0, 0, c, row, a.INJ);
       double add[4];
-      node_sum(q, Es, Ev, Cc, t1 - 1 - s0, c, w, r4, a.INJ, add);
+      node_sum(q, S.Es, S.Ev, S.Cc, t1 - 1 - s0, c, row, a.INJ, add);
 #pragma unroll
       for (int v = 0; v < 4; ++v) Bs[0][(4 * w + v) * VST + l] = add[v];
-      gs.start(a.GAT, uniform(Ws[n]), w, l);
+      gs.start(a.GAT, uniform(S.Ws[n]) & ~EV_FLAG, w, l);
       lds_barrier();
     }
     for (int x = n - 1; x >= 0; --x) {
       const int t = t0 + x;
-      NodeAdds<EVW> q;  // events of node t - 1 (the first window before the product)
+      NodeAdds<EV_WINDOW, 4> q;  // events of node t - 1 (the first window before the product)
       q.n = 0;
       q.most = 0;
-      const bool ev = t > 0 && has_events(t - 1 - s0);
-      if (ev) load_node_adds(q, Es, Ev, Cc, t - 1 - s0, 0, c, w, r4, a.INJ);
-      const d4 acc = gs.product(a.GAT, uniform(Ws[x + 1]), t > 0 ? uniform(Ws[x]) : -1, Bs[cur], w, l);
+      const bool ev = (uniform(S.Ws[x + 1]) & EV_FLAG) != 0;
+      if (ev) load_node_adds(q, S.Es, S.Ev, S.Cc, t - 1 - s0, 0, c, row, a.INJ);
+      const d4 acc = gs.product(a.GAT, t > 0 ? uniform(S.Ws[x]) & ~EV_FLAG : -1, Bs[cur], w, l);
       store_tile_rows(Bs[cur], a.BA + (row0 + (int64_t)t * 16) * N64, tid);
       if (ev) {
         double add[4];
-        node_sum(q, Es, Ev, Cc, t - 1 - s0, c, w, r4, a.INJ, add);
+        node_sum(q, S.Es, S.Ev, S.Cc, t - 1 - s0, c, row, a.INJ, add);
 #pragma unroll
         for (int v = 0; v < 4; ++v) Bs[cur ^ 1][(4 * w + v) * VST + l] = acc[v] + add[v];
       } else {
@@ -723,55 +681,199 @@ __device__ __forceinline__ void plan64_bwd_body(const Plan64Launch& a, int64_t t
   }
 }
 
-// Event windows: the long level keeps all of a node's rows at once (a tile per
-// CU either way), the levels of short chains three (occupancy).
-template <class Gates>
 __global__ __launch_bounds__(256) void plan64_bwd_kernel(const Plan64Launch a) {
-  plan64_bwd_body<Gates, Gates::kReg ? EV_NODE : 3>(a, a.t_begin + blockIdx.x);
+  plan64_bwd_body(a, a.t_begin + blockIdx.x);
+}
+
+// ---------------------------------------------------------------------------
+// Levels of long chains: a tile's sixteen chains are split over four workgroups
+// of four, which need nothing of each other.  Such a level has few tiles (113 of
+// up to 386 steps in a list of 200,960 sequences), and what it takes is the time
+// of one step, times the longest chain.  With 16 x 16 x 4 products a step was
+// sixteen dependent MFMAs of 64 cycles and an exchange of the states through
+// LDS; the 4 x 4 x 4 product of four blocks (wave w: the blocks are its rows
+// 16w + 4b .. + 3, the columns the workgroup's four) takes 22 cycles in a dependent
+// chain, adds in the same ascending order, and reads the same operand layout of
+// the gates.  A wave's operands of all K <= 5 gates stay in registers, a step
+// picks its gate by a uniform branch, and two workgroups share a CU.  Quarters of
+// a tile without chains are skipped (here and in the gradient).
+// The level of that list: forward 289 -> 157 us, reverse 367 -> 190 us, a step
+// about 1,000 and 1,200 cycles, of which 352 are the products and most of the rest the
+// way through LDS (write, barrier, read).  Eight columns per workgroup, two
+// independent products each: 168 and 224 us.
+// ---------------------------------------------------------------------------
+constexpr int QC = 4;       // columns of a workgroup
+constexpr int QWG = 16 / QC; // workgroups per tile
+
+struct RegGates {
+  double g[5][16];
+  __device__ __forceinline__ void init(const double* base, int K, int w, int l) {
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+      if (k < K) load_ops(g[k], base + ((int64_t)k * 4 + w) * 1024, l);
+  }
+  // The wave's 16 x 64 block of gate k times the four columns, once all waves have
+  // written theirs; B: the lane's operands, two blocks of four rows per 256 bytes.
+  // The barrier stands in each case, so that the branches run while the wave's
+  // own write is on its way; four reads are kept ahead of the products (all
+  // eight up front delay the first product, two leave each pair waiting).
+  __device__ __forceinline__ double product(int k, const d2* B) {
+    constexpr int AHEAD = 4;
+    d2 b[8];
+    double acc = 0.0;
+    switch (k) {
+#define GST_P64_CASE(K)                                                                        \
+  case K:                                                                                      \
+    asm volatile("; gate " #K "\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");           \
+    _Pragma("unroll") for (int h = 0; h < AHEAD; ++h) b[h] = B[h * 16];                        \
+    __builtin_amdgcn_sched_barrier(0);                                                         \
+    _Pragma("unroll") for (int h = 0; h < 8; ++h) {                                            \
+      if (h + AHEAD < 8) b[h + AHEAD] = B[(h + AHEAD) * 16];                                   \
+      acc = __builtin_amdgcn_mfma_f64_4x4x4f64(g[K][2 * h], b[h].x, acc, 0, 0, 0);             \
+      acc = __builtin_amdgcn_mfma_f64_4x4x4f64(g[K][2 * h + 1], b[h].y, acc, 0, 0, 0);         \
+      __builtin_amdgcn_sched_barrier(0);                                                       \
+    }                                                                                          \
+    break;
+      GST_P64_CASE(0) GST_P64_CASE(1) GST_P64_CASE(2) GST_P64_CASE(3)
+      default:
+        GST_P64_CASE(4)
+#undef GST_P64_CASE
+    }
+    return acc;
+  }
+};
+
+// A lane's element of the workgroup's 64 x 4 states: its row, its column, its
+// place in LDS, and where its operands lie.  Element (row 4kk + i, column j) lies at
+// 32(kk / 2) + 8i + 2j + kk % 2, so that a lane reads its operands of two blocks kk
+// at once.
+struct QuarterLane {
+  int row, c, at, rd;
+  __device__ __forceinline__ QuarterLane(int q, int w, int l) {
+    const int i = l >> 4, b = (l >> 2) & 3, j = l & 3;
+    row = 16 * w + 4 * b + i;
+    c = QC * q + j;
+    at = (2 * w + (b >> 1)) * 32 + i * 8 + j * 2 + (b & 1);
+    rd = i * 4 + j;
+  }
+};
+
+__device__ __forceinline__ void plan64_fwd_long(const Plan64Launch& a, int64_t tile, int q) {
+  __shared__ __align__(16) double Vs[2][N64 * QC];
+  __shared__ uint8_t Ws[CH_STEPS + 1];
+  if (uniform64(a.col_chain[tile * 16 + QC * q]) < 0) return;
+  const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
+  const QuarterLane e(q, w, l);
+  RegGates gs;
+  gs.init(a.GA, a.K, w, l);
+  Vs[0][e.at] = as_global(a.FA)[a.col_anchor[tile * 16 + e.c] * N64 + e.row];
+  const int len = uniform(a.tile_len[tile]);
+  const auto* word = as_global(a.words + a.tile_word[tile]);
+  auto* dst = as_global(a.FA + (a.tile_row0[tile] + e.c) * N64 + e.row);
+  int cur = 0;
+  for (int t0 = 0; t0 < len; t0 += CH_STEPS) {
+    const int n = len - t0 < CH_STEPS ? len - t0 : CH_STEPS;
+    for (int x = tid; x < n; x += 256) Ws[x] = word[t0 + x];
+    lds_barrier();
+    int k = uniform(Ws[0]);
+    for (int x = 0; x < n; ++x) {
+      const int kn = Ws[x + 1];  // (the last step's: unused)
+      const double f = gs.product(k, reinterpret_cast<const d2*>(Vs[cur]) + e.rd);
+      cur ^= 1;
+      Vs[cur][e.at] = f;
+      *dst = f;
+      dst += 16 * N64;
+      k = uniform(kn);
+    }
+  }
+}
+
+// The reverse sweep (as plan64_bwd_body); a lane stores its element of b_t when
+// it is made, 128 bytes of four rows per wave and store.
+__device__ __forceinline__ void plan64_bwd_long(const Plan64Launch& a, int64_t tile, int qd) {
+  __shared__ __align__(16) double Bs[2][N64 * QC];
+  __shared__ ChunkLds S;
+  if (uniform64(a.col_chain[tile * 16 + QC * qd]) < 0) return;
+  const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
+  const QuarterLane e(qd, w, l);
+  const int len = uniform(a.tile_len[tile]);
+  RegGates gs;
+  gs.init(a.GAT, a.K, w, l);
+  auto* dst = as_global(a.BA + (a.tile_row0[tile] + (int64_t)(len - 1) * 16 + e.c) * N64 + e.row);
+  double b = 0.0;
+  int cur = 0;
+  for (int t1 = len; t1 > 0;) {
+    const Chunk ck = stage_chunk(S, a, tile, t1, tid);
+    const int t0 = ck.t0, s0 = ck.s0;
+    NodeAdds<EV_NODE, 1> q;
+    if (t1 == len) {
+      // b of the last node: its events alone
+      load_node_adds(q, S.Es, S.Ev, S.Cc, t1 - 1 - s0, 0, e.c, e.row, a.INJ);
+      b = node_add(q, 0, 0.0, 0);
+      Bs[0][e.at] = b;
+    }
+    int k = uniform(S.Ws[t1 - t0]);
+    for (int x = t1 - t0 - 1; x >= 0; --x) {
+      const int kn = S.Ws[x];
+      const bool ev = (k & EV_FLAG) != 0;  // events of node t0 + x - 1, loaded before the product
+      if (ev) load_node_adds(q, S.Es, S.Ev, S.Cc, t0 + x - 1 - s0, 0, e.c, e.row, a.INJ);
+      __builtin_nontemporal_store(b, dst);
+      dst -= 16 * N64;
+      b = gs.product(k & ~EV_FLAG, reinterpret_cast<const d2*>(Bs[cur]) + e.rd);
+      double add = 0.0;
+      if (ev) {
+        // kept a branch: as a select it would have every step wait for the
+        // stores before it (reverse 239 -> 192 us)
+        asm volatile("" ::: "memory");
+        add = node_add(q, 0, 0.0, 0);
+      }
+      b += add;
+      cur ^= 1;
+      Bs[cur][e.at] = b;
+      k = uniform(kn);
+    }
+    t1 = t0;
+  }
+  const int64_t ch = a.col_chain[tile * 16 + e.c];
+  if (ch >= 0) as_global(a.INJ)[(a.n_slots + ch) * N64 + e.row] = b;
+}
+
+__global__ __launch_bounds__(256, 2) void plan64_fwd_long_kernel(const Plan64Launch a) {
+  plan64_fwd_long(a, a.t_begin + blockIdx.x / QWG, blockIdx.x % QWG);
+}
+
+__global__ __launch_bounds__(256, 2) void plan64_bwd_long_kernel(const Plan64Launch a) {
+  plan64_bwd_long(a, a.t_begin + blockIdx.x / QWG, blockIdx.x % QWG);
 }
 
 // The gate gradient of the grouped-chain plan: one workgroup per chunk of
 // tile-steps of one gate, wave w owning rows 16w .. 16w+15 of dG.  A tile-step
-// contributes sum_c b_c f_c^T over its sixteen columns: four MFMAs over the
-// columns per 16 x 16 output tile, operands read straight from the arenas
-// (a tile-step's adjoint rows are consecutive, and so are its state rows
-// except at step 0, where they are the columns' anchors).  The chunk's rows
-// are looked up once, into LDS, and each tile-step's operands are loaded
-// while the previous one's MFMAs run, so that a tile-step waits for one
-// memory round trip at most instead of a chain of dependent ones.
+// contributes sum_c b_c f_c^T over its columns (quarters without chains left
+// out): a quarter is one MFMA per 16 x 16 output tile.  A tile-step's 32 rows (its
+// adjoints, consecutive, and the states before them, consecutive except at step
+// 0, where they are the columns' anchors) are staged in LDS, the next one's loaded
+// meanwhile; the chunk's rows are looked up once.
+// The rows' bytes bound it (650 MB in the list of 200,960 sequences, 158 us).
+// Three workgroups share a CU (their LDS), and the plan cuts the chunks so that
+// whole rounds of workgroups run: 773 chunks of 64 on 768 places took 196 us, 750
+// of 66 take 158 us.
 constexpr int TS_CHUNK_MAX = GEMM64_TS_CHUNK_MAX;
-
-struct TsOps {
-  double av[4];     // adjoint rows 4kb + z, elements 16w + ii
-  double bv[4][4];  // state rows of the same columns, elements 16tc + ii
-};
-
-__device__ __forceinline__ void load_ts(TsOps& o, const double* BA, const double* FA, int64_t rb, const int64_t* rf,
-                                        int w, int z, int ii) {
-  const auto* g_b = as_global(BA);
-  const auto* g_f = as_global(FA);
-#pragma unroll
-  for (int kb = 0; kb < 4; ++kb) {
-    const int col = 4 * kb + z;
-    o.av[kb] = g_b[(rb + col) * N64 + 16 * w + ii];
-    const int64_t r = rf[col];
-#pragma unroll
-    for (int tc = 0; tc < 4; ++tc) o.bv[kb][tc] = g_f[r * N64 + 16 * tc + ii];
-  }
-}
 
 constexpr int TS_SST = 80;  // padded row stride (doubles) of the staged rows: a half-wave's operand reads hit distinct banks
 
 // The 32 rows of tile-step x (16 adjoint rows, then the 16 state rows before
-// them), 16 bytes per thread and load, a row per 32 consecutive threads.
+// them), 16 bytes per thread and load, a row per 32 consecutive threads.  Rows
+// from `rows` on are not defined (quarters of the tile without chains): the
+// first row's bytes come in their place, and no product reads them.
 __device__ __forceinline__ void load_ts_rows(d2 (&rg)[4], const double* BA, const double* FA, int64_t rb,
-                                             const int64_t* rf, int tid) {
+                                             const int32_t* rf, int rows, int tid) {
   const auto* gb = as_global(reinterpret_cast<const d2*>(BA));
   const auto* gf = as_global(reinterpret_cast<const d2*>(FA));
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int item = tid + 256 * i, row = (item >> 5) & 15, j = item & 31;
-    rg[i] = item < 512 ? gb[(rb + row) * (N64 / 2) + j] : gf[rf[row] * (N64 / 2) + j];
+    const int item = tid + 256 * i, at = (item >> 5) & 15, j = item & 31;
+    const int row = at < rows ? at : 0;
+    rg[i] = item < 512 ? gb[(rb + row) * (N64 / 2) + j] : gf[(int64_t)rf[row] * (N64 / 2) + j];
   }
 }
 
@@ -786,7 +888,8 @@ __device__ __forceinline__ void store_ts_rows(const d2 (&rg)[4], double* Sb, dou
 
 __device__ __forceinline__ void gemm64_ts_body(const Gemm64TsLaunch& a, int64_t ch) {
   __shared__ int64_t Rb[TS_CHUNK_MAX];       // adjoint row of column 0 at each tile-step
-  __shared__ int64_t Rf[TS_CHUNK_MAX][16];   // the columns' state rows before it
+  __shared__ int32_t Rf[TS_CHUNK_MAX][16];   // the columns' state rows before it (a row is 512 bytes)
+  __shared__ int Rn[TS_CHUNK_MAX];           // its columns, rounded up to whole quarters
   __shared__ double Sb[2][16 * TS_SST];      // a tile-step's adjoint rows, double-buffered
   __shared__ double Sf[2][16 * TS_SST];      // its state rows
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -798,8 +901,13 @@ __device__ __forceinline__ void gemm64_ts_body(const Gemm64TsLaunch& a, int64_t 
     const int64_t tile = a.ts_tile[x0 + x];
     const int t = a.ts_step[x0 + x];
     const int64_t r0 = a.tile_row0[tile] + (int64_t)t * 16;
-    if (c == 0) Rb[x] = r0;
-    Rf[x][c] = t > 0 ? r0 - 16 + c : a.col_anchor[tile * 16 + c];
+    // (the sixteen threads of a tile-step run together)
+    const unsigned long long live = __ballot(a.col_chain[tile * 16 + c] >= 0) >> (lane & 48) & 0xffff;
+    if (c == 0) {
+      Rb[x] = r0;
+      Rn[x] = (__popcll(live) + 3) / 4 * 4;
+    }
+    Rf[x][c] = (int32_t)(t > 0 ? r0 - 16 + c : a.col_anchor[tile * 16 + c]);
   }
   __syncthreads();
   d4 acc[4];
@@ -807,20 +915,25 @@ __device__ __forceinline__ void gemm64_ts_body(const Gemm64TsLaunch& a, int64_t 
   for (int tc = 0; tc < 4; ++tc) acc[tc] = d4{0.0, 0.0, 0.0, 0.0};
   d2 rg[4];
   if (n > 0) {
-    load_ts_rows(rg, a.BA, a.FA, Rb[0], Rf[0], tid);
+    load_ts_rows(rg, a.BA, a.FA, Rb[0], Rf[0], Rn[0], tid);
     store_ts_rows(rg, Sb[0], Sf[0], tid);
   }
   lds_barrier();
   for (int x = 0; x < n; ++x) {
     const int cur = x & 1;
-    if (x + 1 < n) load_ts_rows(rg, a.BA, a.FA, Rb[x + 1], Rf[x + 1], tid);
+    if (x + 1 < n) load_ts_rows(rg, a.BA, a.FA, Rb[x + 1], Rf[x + 1], Rn[x + 1], tid);
+    const double* B = Sb[cur] + z * TS_SST + 16 * w + ii;
+    const double* F = Sf[cur] + z * TS_SST + ii;
+    const int rows = uniform(Rn[x]);
+    double av = B[0], bv[4] = {F[0], F[16], F[32], F[48]};
+    for (int r = 0; r < rows; r += 4) {
+      const int rn = (r + 4 < rows ? r + 4 : 0) * TS_SST;  // the next four columns' operands
+      const double an = B[rn], bn[4] = {F[rn], F[rn + 16], F[rn + 32], F[rn + 48]};
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-      const int row = 4 * kb + z;
-      const double av = Sb[cur][row * TS_SST + 16 * w + ii];
+      for (int tc = 0; tc < 4; ++tc) acc[tc] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[tc], acc[tc], 0, 0, 0);
+      av = an;
 #pragma unroll
-      for (int tc = 0; tc < 4; ++tc)
-        acc[tc] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, Sf[cur][row * TS_SST + 16 * tc + ii], acc[tc], 0, 0, 0);
+      for (int tc = 0; tc < 4; ++tc) bv[tc] = bn[tc];
     }
     if (x + 1 < n) store_ts_rows(rg, Sb[cur ^ 1], Sf[cur ^ 1], tid);
     lds_barrier();
@@ -1051,26 +1164,44 @@ __global__ __launch_bounds__(256) void gate_prep64_batch(const Plan64Req* r) {
                    blockIdx.x);
 }
 
-template <class Gates>
-__global__ __launch_bounds__(256) void plan64_fwd_batch(const Plan64Req* r, int level, int want_long) {
-  const Plan64Req& q = r[blockIdx.y];
-  if (level >= q.n_levels || (int)q.level_long[level] != want_long) return;
-  const int64_t t0 = q.level_tile[level], t1 = q.level_tile[level + 1];
-  if ((int64_t)blockIdx.x >= t1 - t0) return;
-  const Plan64Launch a = q.tiles;
-  plan64_fwd_body<Gates>(a, t0 + blockIdx.x);
+// The tile of workgroup `blk` of a level, per_tile workgroups each; -1: the level
+// has none, or is of the other kind.
+__device__ __forceinline__ int64_t batch_tile(const Plan64Req& q, int level, int want_long, int blk, int per_tile) {
+  if (level >= q.n_levels || (int)q.level_long[level] != want_long) return -1;
+  const int64_t t = q.level_tile[level] + blk / per_tile;
+  return t < q.level_tile[level + 1] ? t : -1;
 }
 
-template <class Gates>
-__global__ __launch_bounds__(256) void plan64_bwd_batch(const Plan64Req* r, int level, int want_long) {
+__global__ __launch_bounds__(256) void plan64_fwd_batch(const Plan64Req* r, int level) {
   const Plan64Req& q = r[blockIdx.y];
-  if (!q.want_grad || level >= q.n_levels || (int)q.level_long[level] != want_long) return;
-  const int64_t t0 = q.level_tile[level], t1 = q.level_tile[level + 1];
-  if ((int64_t)blockIdx.x >= t1 - t0) return;
+  const int64_t t = batch_tile(q, level, 0, blockIdx.x, 1);
+  if (t < 0) return;
   const Plan64Launch a = q.tiles;
-  // several requests' long levels share the CUs: a window of two rows lets two
-  // of their tiles share a CU
-  plan64_bwd_body<Gates, Gates::kReg ? 2 : 3>(a, t0 + blockIdx.x);
+  plan64_fwd_body(a, t);
+}
+
+__global__ __launch_bounds__(256, 2) void plan64_fwd_long_batch(const Plan64Req* r, int level) {
+  const Plan64Req& q = r[blockIdx.y];
+  const int64_t t = batch_tile(q, level, 1, blockIdx.x, QWG);
+  if (t < 0) return;
+  const Plan64Launch a = q.tiles;
+  plan64_fwd_long(a, t, blockIdx.x % QWG);
+}
+
+__global__ __launch_bounds__(256) void plan64_bwd_batch(const Plan64Req* r, int level) {
+  const Plan64Req& q = r[blockIdx.y];
+  const int64_t t = q.want_grad ? batch_tile(q, level, 0, blockIdx.x, 1) : -1;
+  if (t < 0) return;
+  const Plan64Launch a = q.tiles;
+  plan64_bwd_body(a, t);
+}
+
+__global__ __launch_bounds__(256, 2) void plan64_bwd_long_batch(const Plan64Req* r, int level) {
+  const Plan64Req& q = r[blockIdx.y];
+  const int64_t t = q.want_grad ? batch_tile(q, level, 1, blockIdx.x, QWG) : -1;
+  if (t < 0) return;
+  const Plan64Launch a = q.tiles;
+  plan64_bwd_long(a, t, blockIdx.x % QWG);
 }
 
 __global__ __launch_bounds__(READOUT64_WAVES * 64) void readout64_batch(const Plan64Req* r) {
@@ -1129,24 +1260,30 @@ hipError_t launch_gemm64_ts(const Gemm64TsLaunch& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_plan64_fwd(const Plan64Launch& a, int n_tiles, bool reg_gates, hipStream_t stream) {
+hipError_t launch_plan64_fwd(const Plan64Launch& a, int n_tiles, bool long_chains, hipStream_t stream) {
   if (n_tiles <= 0) return hipSuccess;
   if (a.K < 1 || a.K > 5) return hipErrorInvalidValue;
-  if (reg_gates)
-    gst_launch(plan64_fwd_kernel<RegGates>, dim3(n_tiles), dim3(256), 0, stream, a);
+  if (long_chains)
+    gst_launch(plan64_fwd_long_kernel, dim3(QWG * n_tiles), dim3(256), 0, stream, a);
   else
-    gst_launch(plan64_fwd_kernel<LoadGates>, dim3(n_tiles), dim3(256), 0, stream, a);
+    gst_launch(plan64_fwd_kernel, dim3(n_tiles), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
-hipError_t launch_plan64_bwd(const Plan64Launch& a, int n_tiles, bool reg_gates, hipStream_t stream) {
+hipError_t launch_plan64_bwd(const Plan64Launch& a, int n_tiles, bool long_chains, hipStream_t stream) {
   if (n_tiles <= 0) return hipSuccess;
   if (a.K < 1 || a.K > 5) return hipErrorInvalidValue;
-  if (reg_gates)
-    gst_launch(plan64_bwd_kernel<RegGates>, dim3(n_tiles), dim3(256), 0, stream, a);
+  if (long_chains)
+    gst_launch(plan64_bwd_long_kernel, dim3(QWG * n_tiles), dim3(256), 0, stream, a);
   else
-    gst_launch(plan64_bwd_kernel<LoadGates>, dim3(n_tiles), dim3(256), 0, stream, a);
+    gst_launch(plan64_bwd_kernel, dim3(n_tiles), dim3(256), 0, stream, a);
   return hipGetLastError();
+}
+
+int gemm64_ts_blocks_per_cu() {
+  int n = 0;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm64_ts_kernel, 256, 0);
+  return (e == hipSuccess && n > 0) ? n : 1;
 }
 
 int readout64_blocks_per_cu() {
@@ -1192,23 +1329,23 @@ hipError_t launch_gate_prep64_batch(const Plan64Req* reqs, int n, int K_max, hip
   return hipGetLastError();
 }
 
-hipError_t launch_plan64_fwd_batch(const Plan64Req* reqs, int n, int level, int grid_x, bool reg_gates,
+hipError_t launch_plan64_fwd_batch(const Plan64Req* reqs, int n, int level, int grid_x, bool long_chains,
                                    hipStream_t stream) {
   if (n <= 0 || grid_x <= 0) return hipSuccess;
-  if (reg_gates)
-    gst_launch(plan64_fwd_batch<RegGates>, dim3(grid_x, n), dim3(256), 0, stream, reqs, level, 1);
+  if (long_chains)
+    gst_launch(plan64_fwd_long_batch, dim3(QWG * grid_x, n), dim3(256), 0, stream, reqs, level);
   else
-    gst_launch(plan64_fwd_batch<LoadGates>, dim3(grid_x, n), dim3(256), 0, stream, reqs, level, 0);
+    gst_launch(plan64_fwd_batch, dim3(grid_x, n), dim3(256), 0, stream, reqs, level);
   return hipGetLastError();
 }
 
-hipError_t launch_plan64_bwd_batch(const Plan64Req* reqs, int n, int level, int grid_x, bool reg_gates,
+hipError_t launch_plan64_bwd_batch(const Plan64Req* reqs, int n, int level, int grid_x, bool long_chains,
                                    hipStream_t stream) {
   if (n <= 0 || grid_x <= 0) return hipSuccess;
-  if (reg_gates)
-    gst_launch(plan64_bwd_batch<RegGates>, dim3(grid_x, n), dim3(256), 0, stream, reqs, level, 1);
+  if (long_chains)
+    gst_launch(plan64_bwd_long_batch, dim3(QWG * grid_x, n), dim3(256), 0, stream, reqs, level);
   else
-    gst_launch(plan64_bwd_batch<LoadGates>, dim3(grid_x, n), dim3(256), 0, stream, reqs, level, 0);
+    gst_launch(plan64_bwd_batch, dim3(grid_x, n), dim3(256), 0, stream, reqs, level);
   return hipGetLastError();
 }
 

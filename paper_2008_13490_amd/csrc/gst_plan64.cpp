@@ -385,12 +385,19 @@ bool build_plan64(const int64_t* off, const uint8_t* gates, int64_t S, int K, co
         P.ts_step[r] = (int32_t)t;
       }
   }
+  // Chunks of one length that fill whole rounds of workgroups (a gate's last
+  // chunk is shorter); at least 16 tile-steps, since a chunk's partial gradient
+  // is as many bytes as two of them
+  const int64_t TS = ts_ptr[K];
+  const int64_t rounds = TS / ((int64_t)std::max(opt.ts_blocks - K, 1) * opt.ts_chunk) + 1;
+  const int64_t places = std::max<int64_t>(rounds * opt.ts_blocks - K, 1);
+  const int64_t per = std::min<int64_t>(std::max<int64_t>((TS + places - 1) / places, 16), opt.ts_chunk);
   P.gate_chunk_ptr.assign((size_t)K + 1, 0);
   for (int k = 0; k < K; ++k) {
     P.gate_chunk_ptr[k] = (int64_t)P.chunk_beg.size();
-    for (int64_t b = ts_ptr[k]; b < ts_ptr[k + 1]; b += opt.ts_chunk) {
+    for (int64_t b = ts_ptr[k]; b < ts_ptr[k + 1]; b += per) {
       P.chunk_beg.push_back(b);
-      P.chunk_end.push_back(std::min<int64_t>(b + opt.ts_chunk, ts_ptr[k + 1]));
+      P.chunk_end.push_back(std::min<int64_t>(b + per, ts_ptr[k + 1]));
     }
   }
   P.gate_chunk_ptr[K] = (int64_t)P.chunk_beg.size();

@@ -1,0 +1,59 @@
+"""Grouped-chain plans of three qubits whose tiles are partly filled, against the oracle.
+
+Lists with 5 to 17 fiducials, whose tiles hold between one and sixteen chains
+(quarters of a tile without chains are not computed), and chains on both sides
+of the level rule (32 steps) and of a staged chunk (256 steps).  Probabilities
+must be bit-identical, the objective within 1e-10 relative, the gradient and
+the vector-Jacobian product within 1e-10 of their largest entry.
+"""
+import numpy as np
+import pytest
+
+from paper_2008_13490_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2008_13490_amd import api
+    return api, api.Context(0)
+
+
+@pytest.mark.parametrize("n_fid,spec,powers", [
+    (5, ((2, 3), (3, 2)), (1, 2, 4, 8, 16, 32, 64, 128)), (6, ((2, 2),), (16, 32)), (8, ((2, 4), (3, 4)), (1, 11, 12)),
+    (9, ((2, 5), (3, 5)), (1, 2, 4, 8, 16, 32, 64)), (17, ((2, 2),), (8, 64)), (16, ((3, 3),), (1, 2)),
+])
+def test_partly_filled_tiles(oracle_lib, gpu, n_fid, spec, powers):
+    import torch
+    api, ctx = gpu
+    rng = np.random.default_rng(7)
+    m = W.noisy_gateset("3q", W.LAMBDA, W.SIGMA, rng)
+    fids = W.shortlex_words((1, 2), n_fid)
+    sl = W.structured_list(fids, fids, W.random_germs(m.K, list(spec), rng), list(powers))
+    counts = rng.integers(0, 40, size=(sl.S, m.M)).astype(np.int32)
+    counts[oracle_lib.probs(m.rho, m.effects, m.gates, sl.offsets, sl.gates) <= 0] = 0
+    F, p_or, g_or, _, rc = oracle_lib.loglik(m.rho, m.effects, m.gates, sl.offsets, sl.gates, counts)
+    assert rc == 0
+    gs = api.DeviceGateSet.from_numpy(m.n_qubits, m.rho, m.effects, m.gates)
+    req, req2 = (api.Request(ctx, m.n_qubits, m.K, m.M, sl.offsets, sl.gates, counts) for _ in range(2))
+    assert req.plan_info()["grouped"] == 1
+    bt = api.Batch(ctx, [req, req2], [gs, gs], want_probs=True, want_grad=True)
+    obj, p, g = req.eval(gs, want_probs=True)
+    bt.run()
+    ctx.sync()
+    for o, q, h in ((obj, p, g), (bt.obj[0], bt.probs[0], bt.grad[0]), (bt.obj[1], bt.probs[1], bt.grad[1])):
+        assert np.array_equal(q.cpu().numpy(), p_or)
+        assert abs(float(o.cpu()[0]) - F) <= 1e-10 * abs(F)
+        assert np.abs(h.cpu().numpy() - g_or).max() <= 1e-10 * np.abs(g_or).max()
+    w = rng.standard_normal((sl.S, m.M))
+    v = req.vjp(gs, torch.as_tensor(w, device="cuda"))
+    ctx.sync()
+    v_or = oracle_lib.vjp(m.rho, m.effects, m.gates, sl.offsets, sl.gates, w)
+    assert np.abs(v.cpu().numpy() - v_or).max() <= 1e-10 * np.abs(v_or).max()
+    bt.close()
+    req.close()
+    req2.close()
