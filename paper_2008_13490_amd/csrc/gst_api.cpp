@@ -971,9 +971,8 @@ int run_plan64(gst_req* r, const gst_gateset* th, int mode, const double* w, dou
   DevicePlan64& d = r->plan64;
   const bool want_grad = grad != nullptr;
   unsigned long long* np = nonpos ? nonpos : reinterpret_cast<unsigned long long*>(r->queue + kQueueWords);
-  HIP_TRY(gst::launch_queue_reset(r->queue, np, 1, ctx->stream));
   const gst::Plan64Req q = plan64_req(r, th, mode, w, probs, objective, grad, np);
-  HIP_TRY(gst::launch_gate_prep64(q.G, q.rho, r->K, d.GA, d.GAT, d.FA, ctx->stream));
+  HIP_TRY(gst::launch_gate_prep64(q.G, q.rho, r->K, d.GA, d.GAT, d.FA, np, ctx->stream));
   gst::Plan64Launch a = q.tiles;
   const int L = d.host.n_levels;
   {
@@ -997,11 +996,8 @@ int run_plan64(gst_req* r, const gst_gateset* th, int mode, const double* w, dou
                                        d.level_long[l] != 0, ctx->stream));
       }
     }
-    if (q.gemm.n_chunks > 0) {
-      ProfScope ps(ctx, FAM_GEMM64);
-      HIP_TRY(gst::launch_gemm64_ts(q.gemm, ctx->stream));
-    }
-    HIP_TRY(gst::launch_root64(q.root, ctx->stream));
+    ProfScope ps(ctx, FAM_GEMM64);
+    HIP_TRY(gst::launch_gemm64_ts(q.gemm, q.root, ctx->stream));
   }
   if (q.slab) {
     ProfScope ps(ctx, FAM_REDUCE64);
@@ -1983,11 +1979,8 @@ static int batch_enqueue(gst_batch* b, hipStream_t stream, bool eager) {
           HIP_TRY(gst::launch_plan64_bwd_batch(g.dev, g.n, l, g.grid_short[l], false, stream));
         }
       }
-      {
-        ProfScope ps(pc, FAM_GEMM64);
-        HIP_TRY(gst::launch_gemm64_ts_batch(g.dev, g.n, g.gemm_grid, stream));
-      }
-      HIP_TRY(gst::launch_root64_batch(g.dev, g.n, stream));
+      ProfScope ps(pc, FAM_GEMM64);
+      HIP_TRY(gst::launch_gemm64_ts_batch(g.dev, g.n, g.gemm_grid, stream));
     }
     if (g.any_slab) {
       ProfScope ps(pc, FAM_REDUCE64);

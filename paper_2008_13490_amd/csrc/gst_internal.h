@@ -326,7 +326,6 @@ struct Gemm64TsLaunch {
 };
 constexpr int GEMM64_TS_CHUNK_MAX = 96;  // tile-steps per chunk at most (staged in LDS)
 int gemm64_ts_blocks_per_cu();
-hipError_t launch_gemm64_ts(const Gemm64TsLaunch& a, hipStream_t stream);
 constexpr int READOUT64_WAVES = 4;
 struct Readout64Launch {
   int M;
@@ -357,11 +356,12 @@ struct Root64Launch {        // the adjoint of rho: root seed + chains anchored 
   double* out;               // [64]
 };
 hipError_t launch_gate_prep64(const double* G, const double* rho, int K, double* GA, double* GAT, double* FA,
-                              hipStream_t stream);
+                              unsigned long long* nonpos, hipStream_t stream);
 hipError_t launch_plan64_fwd(const Plan64Launch& a, int n_tiles, bool long_chains, hipStream_t stream);
 hipError_t launch_plan64_bwd(const Plan64Launch& a, int n_tiles, bool long_chains, hipStream_t stream);
 hipError_t launch_readout64(const Readout64Launch& a, int n_blocks, hipStream_t stream);
-hipError_t launch_root64(const Root64Launch& a, hipStream_t stream);
+// the gradient GEMM and the root's adjoint, one launch
+hipError_t launch_gemm64_ts(const Gemm64TsLaunch& a, const Root64Launch& root, hipStream_t stream);
 int readout64_blocks_per_cu();
 
 hipError_t launch_chain64_fwd(const Chain64Launch& a, int n_blocks, hipStream_t stream);
@@ -401,8 +401,7 @@ hipError_t launch_plan64_fwd_batch(const Plan64Req* reqs, int n, int level, int 
 hipError_t launch_readout64_batch(const Plan64Req* reqs, int n, int grid_x, hipStream_t stream);
 hipError_t launch_plan64_bwd_batch(const Plan64Req* reqs, int n, int level, int grid_x, bool long_chains,
                                    hipStream_t stream);
-hipError_t launch_gemm64_ts_batch(const Plan64Req* reqs, int n, int grid_x, hipStream_t stream);
-hipError_t launch_root64_batch(const Plan64Req* reqs, int n, hipStream_t stream);
+hipError_t launch_gemm64_ts_batch(const Plan64Req* reqs, int n, int chunks_max, hipStream_t stream);
 hipError_t launch_slab_sum64_batch(const Plan64Req* reqs, int n, int grid_x, int parts_max, hipStream_t stream);
 hipError_t launch_reduce64_batch(const Plan64Req* reqs, int n, int grid_x, hipStream_t stream);
 

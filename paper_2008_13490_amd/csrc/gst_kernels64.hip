@@ -350,7 +350,19 @@ __device__ __forceinline__ void reduce64_body(const Reduce64Launch& a, int64_t b
   if (y < Y) {
     const int k = (int)(y / GATE64);
     const int64_t e = y % GATE64;
-    for (int64_t c = a.gate_chunk_ptr[k] + ty; c < a.gate_chunk_ptr[k + 1]; c += 4) v += a.chunk_slab[c * GATE64 + e];
+    // eight partials loaded at a time (one after another the loads' latency
+    // was most of the kernel: 200,960 sequences, 150 chunks a gate, 16.5 -> 8.5 us)
+    const double* p = a.chunk_slab + e;
+    const int64_t c1 = a.gate_chunk_ptr[k + 1];
+    int64_t c = a.gate_chunk_ptr[k] + ty;
+    for (; c + 28 < c1; c += 32) {
+      double t[8];
+#pragma unroll
+      for (int x = 0; x < 8; ++x) t[x] = p[(c + 4 * x) * GATE64];
+#pragma unroll
+      for (int x = 0; x < 8; ++x) v += t[x];
+    }
+    for (; c < c1; c += 4) v += p[c * GATE64];
   }
   red[ty][tx] = v;
   __syncthreads();
@@ -380,22 +392,26 @@ __global__ __launch_bounds__(256) void reduce64_kernel(const Reduce64Launch a) {
 // loaded while the current step runs.
 // ---------------------------------------------------------------------------
 
-// GA[k][w][kk][l] = G[k][16w + l%16][4kk + l/16]; GAT the same for G^T.  Block 0
-// also writes rho into row 0 of the state arena.
+// GA[k][w][kk][l] = G[k][16w + l%16][4kk + l/16]; GAT the same for G^T; workgroup
+// `blk` writes 256 entries of each.  The first one also writes rho into row 0 of
+// the state arena, and clears the evaluation's count of p <= 0 entries.
+constexpr int PREP_WG = GATE64 / 256;  // workgroups per gate
 __device__ __forceinline__ void gate_prep64_body(const double* G, const double* rho, double* GA, double* GAT,
-                                                 double* FA, int k) {
-  const double* g = G + (int64_t)k * GATE64;
-  for (int x = threadIdx.x; x < GATE64; x += 256) {
-    const int w = x >> 10, kk = (x >> 6) & 15, l = x & 63;
-    GA[(int64_t)k * GATE64 + x] = g[(16 * w + (l & 15)) * N64 + 4 * kk + (l >> 4)];
-    GAT[(int64_t)k * GATE64 + x] = g[(4 * kk + (l >> 4)) * N64 + 16 * w + (l & 15)];
+                                                 double* FA, unsigned long long* nonpos, int blk) {
+  const int64_t x = (int64_t)blk * 256 + threadIdx.x;
+  const double* g = G + x / GATE64 * GATE64;
+  const int w = (int)(x >> 10) & 3, kk = (int)(x >> 6) & 15, l = (int)x & 63;
+  GA[x] = g[(16 * w + (l & 15)) * N64 + 4 * kk + (l >> 4)];
+  GAT[x] = g[(4 * kk + (l >> 4)) * N64 + 16 * w + (l & 15)];
+  if (blk == 0) {
+    if (threadIdx.x < N64) FA[threadIdx.x] = rho[threadIdx.x];
+    if (threadIdx.x == 0 && nonpos) *nonpos = 0ull;
   }
-  if (k == 0 && threadIdx.x < N64) FA[threadIdx.x] = rho[threadIdx.x];
 }
 
-__global__ __launch_bounds__(256) void gate_prep64_kernel(const double* G, const double* rho, double* GA,
-                                                          double* GAT, double* FA) {
-  gate_prep64_body(G, rho, GA, GAT, FA, blockIdx.x);
+__global__ __launch_bounds__(256) void gate_prep64_kernel(const double* G, const double* rho, double* GA, double* GAT,
+                                                          double* FA, unsigned long long* nonpos) {
+  gate_prep64_body(G, rho, GA, GAT, FA, nonpos, blockIdx.x);
 }
 
 __device__ __forceinline__ void load_ops(double (&dst)[16], const double* base, int lane) {
@@ -472,21 +488,27 @@ __device__ __forceinline__ void plan64_fwd_body(const Plan64Launch& a, int64_t t
   __shared__ uint8_t Ws[CH_STEPS + 1];
   const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
   const int c = l & 15, r4 = l >> 4;
-  const int64_t anc = a.col_anchor[tile * 16 + c];
-  const auto* fa = as_global(a.FA);
-  LoadGates gs;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) Vs[0][(4 * w + v) * VST + l] = fa[anc * N64 + 4 * (4 * w + v) + r4];
+  // a tile of a few steps is a chain of memory round trips: its arrays, then the
+  // anchors' states and the word, then the first gate's operands
   const int len = uniform(a.tile_len[tile]);
   const auto* word = as_global(a.words + a.tile_word[tile]);
   const int64_t row0 = a.tile_row0[tile];
+  const int first = word[0];
+  const int64_t anc = a.col_anchor[tile * 16 + c];
+  const auto* fa = as_global(a.FA + anc * N64 + 16 * w + r4);
+  double f0[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) f0[v] = fa[4 * v];
+  LoadGates gs;
+  gs.start(a.GA, uniform(first), w, l);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Vs[0][(4 * w + v) * VST + l] = f0[v];
   int cur = 0;
   for (int t0 = 0; t0 < len; t0 += CH_STEPS) {
     const int n = len - t0 < CH_STEPS ? len - t0 : CH_STEPS;
     // word[t0 .. t0 + n], the last one the first gate of the next chunk
     for (int x = tid; x <= n && t0 + x < len; x += 256) Ws[x] = word[t0 + x];
     lds_barrier();
-    if (t0 == 0) gs.start(a.GA, uniform(Ws[0]), w, l);
     for (int x = 0; x < n; ++x) {
       const int t = t0 + x;
       const d4 acc = gs.product(a.GA, t + 1 < len ? uniform(Ws[x + 1]) : -1, Vs[cur], w, l);
@@ -604,18 +626,45 @@ __device__ __forceinline__ Chunk stage_chunk(ChunkLds& S, const Plan64Launch& a,
   const auto* cend = as_global(reinterpret_cast<const u32x4*>(a.ev_cend) + tev);
   const auto* evs = as_global(a.ev_src);
   int t0 = t1 - CH_STEPS > 0 ? t1 - CH_STEPS : 0;
-  const int64_t e1 = uniform64(evp[t1]);
-  while (t1 - t0 > 1 && uniform64(evp[t0 > 0 ? t0 - 1 : 0]) + CH_EVENTS < e1) t0 = t1 - (t1 - t0) / 2;
-  const int s0 = t0 > 0 ? t0 - 1 : 0;
-  const int64_t e0 = uniform64(evp[s0]);
-  for (int x = tid; x <= t1 - t0; x += 256)
-    if (x > 0 || t0 > 0) {
-      const int t = t0 - 1 + x;
-      S.Ws[x] = word[t] | (t > 0 && evp[t] > evp[t - 1] ? EV_FLAG : 0);
-    }
-  for (int x = tid; x <= t1 - s0; x += 256) S.Es[x] = (int32_t)(evp[s0 + x] - e0);
-  for (int x = tid; x < t1 - s0; x += 256) S.Cc[x] = cend[s0 + x];
+  // all of a thread's first loads at once (the guess t0 holds unless the chunk
+  // has more events than its list)
+  const int64_t e1 = evp[t1];
+  int s0 = t0 > 0 ? t0 - 1 : 0;
+  int64_t e0 = evp[s0];
+  struct Row {
+    uint8_t word;
+    int64_t before, here, ev;
+    u32x4 cols;
+  };
+  auto load = [&](int x) {
+    // step t0 - 1 + x: its gate, and whether the step before it has events
+    const int t = t0 - 1 + x < 0 ? 0 : (t0 - 1 + x < t1 ? t0 - 1 + x : t1 - 1);
+    Row r;
+    r.word = word[t];
+    r.before = evp[t > 0 ? t - 1 : 0];
+    r.here = evp[t];
+    // and step s0 + x
+    const int s = s0 + x < t1 ? s0 + x : t1 - 1;
+    r.ev = evp[s0 + x < t1 ? s0 + x : t1];
+    r.cols = cend[s];
+    return r;
+  };
+  Row r = load(tid);
+  if (uniform64(e0) + CH_EVENTS < uniform64(e1) && t1 - t0 > 1) {
+    while (t1 - t0 > 1 && uniform64(evp[t0 > 0 ? t0 - 1 : 0]) + CH_EVENTS < uniform64(e1)) t0 = t1 - (t1 - t0) / 2;
+    s0 = t0 > 0 ? t0 - 1 : 0;
+    e0 = evp[s0];
+    r = load(tid);
+  }
   for (int j = tid; j < (int)(e1 - e0); j += 256) S.Ev[j] = (int32_t)evs[e0 + j];
+  for (int x = tid;;) {
+    if (x <= t1 - t0 && (x > 0 || t0 > 0)) S.Ws[x] = r.word | (r.here > r.before ? EV_FLAG : 0);
+    if (x <= t1 - s0) S.Es[x] = (int32_t)(r.ev - e0);
+    if (x < t1 - s0) S.Cc[x] = r.cols;
+    x += 256;
+    if (x > t1 - s0) break;
+    r = load(x);
+  }
   lds_barrier();
   return Chunk{t0, s0};
 }
@@ -623,8 +672,8 @@ __device__ __forceinline__ Chunk stage_chunk(ChunkLds& S, const Plan64Launch& a,
 // Reverse sweep of a tile.  b_t, the adjoint of the node after step t, is
 // G_{t+1}^T b_{t+1} plus the node's seed and the adjoints of the chains anchored
 // there (in that order, summed first); it is stored, and G_t^T b_t with the
-// events of node t-1 added becomes b_{t-1}.  The events' rows are loaded while
-// the step's product runs, the next gate's operands a step ahead.  At the end each
+// events of node t-1 added becomes b_{t-1}.  The events' rows and the next gate's
+// operands are loaded a step ahead.  At the end each
 // chain delivers G_0^T b_0 to its anchor.
 constexpr int EV_WINDOW = 3;  // events of a node held at once (more cost occupancy)
 __device__ __forceinline__ void plan64_bwd_body(const Plan64Launch& a, int64_t tile) {
@@ -635,39 +684,46 @@ __device__ __forceinline__ void plan64_bwd_body(const Plan64Launch& a, int64_t t
   const int len = uniform(a.tile_len[tile]);
   const int64_t row0 = a.tile_row0[tile];
   LoadGates gs;
+  gs.start(a.GAT, uniform((int)as_global(a.words + a.tile_word[tile])[len - 1]), w, l);
   int cur = 0;
   for (int t1 = len; t1 > 0;) {
     const Chunk ck = stage_chunk(S, a, tile, t1, tid);
     const int t0 = ck.t0, s0 = ck.s0, n = t1 - t0;
+    // the events of node t - 1 of a step t, its first window loaded a step ahead
+    NodeAdds<EV_WINDOW, 4> q;
+    auto load = [&](int x) {
+      q.n = 0;
+      q.most = 0;
+      if (x >= 0 && (uniform(S.Ws[x + 1]) & EV_FLAG))
+        load_node_adds(q, S.Es, S.Ev, S.Cc, t0 + x - 1 - s0, 0, c, row, a.INJ);
+    };
     if (t1 == len) {
       // b of the last node: its events alone
-      NodeAdds<EV_WINDOW, 4> q;
-      load_node_adds(q, S.Es, S.Ev, S.Cc, t1 - 1 - s0, 0, c, row, a.INJ);
+      NodeAdds<EV_WINDOW, 4> last;
+      load_node_adds(last, S.Es, S.Ev, S.Cc, t1 - 1 - s0, 0, c, row, a.INJ);
+      load(n - 1);
       double add[4];
-      node_sum(q, S.Es, S.Ev, S.Cc, t1 - 1 - s0, c, row, a.INJ, add);
+      node_sum(last, S.Es, S.Ev, S.Cc, t1 - 1 - s0, c, row, a.INJ, add);
 #pragma unroll
       for (int v = 0; v < 4; ++v) Bs[0][(4 * w + v) * VST + l] = add[v];
-      gs.start(a.GAT, uniform(S.Ws[n]) & ~EV_FLAG, w, l);
       lds_barrier();
+    } else {
+      load(n - 1);
     }
     for (int x = n - 1; x >= 0; --x) {
       const int t = t0 + x;
-      NodeAdds<EV_WINDOW, 4> q;  // events of node t - 1 (the first window before the product)
-      q.n = 0;
-      q.most = 0;
       const bool ev = (uniform(S.Ws[x + 1]) & EV_FLAG) != 0;
-      if (ev) load_node_adds(q, S.Es, S.Ev, S.Cc, t - 1 - s0, 0, c, row, a.INJ);
+      NodeAdds<EV_WINDOW, 4> now = q;
+      load(x - 1);
       const d4 acc = gs.product(a.GAT, t > 0 ? uniform(S.Ws[x]) & ~EV_FLAG : -1, Bs[cur], w, l);
       store_tile_rows(Bs[cur], a.BA + (row0 + (int64_t)t * 16) * N64, tid);
+      double add[4] = {0.0, 0.0, 0.0, 0.0};
       if (ev) {
-        double add[4];
-        node_sum(q, S.Es, S.Ev, S.Cc, t - 1 - s0, c, row, a.INJ, add);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Bs[cur ^ 1][(4 * w + v) * VST + l] = acc[v] + add[v];
-      } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Bs[cur ^ 1][(4 * w + v) * VST + l] = acc[v] + 0.0;
+        asm volatile("" ::: "memory");  // (kept a branch: a step without events waits for no memory)
+        node_sum(now, S.Es, S.Ev, S.Cc, t - 1 - s0, c, row, a.INJ, add);
       }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Bs[cur ^ 1][(4 * w + v) * VST + l] = acc[v] + add[v];
       lds_barrier();
       cur ^= 1;
     }
@@ -681,7 +737,9 @@ __device__ __forceinline__ void plan64_bwd_body(const Plan64Launch& a, int64_t t
   }
 }
 
-__global__ __launch_bounds__(256) void plan64_bwd_kernel(const Plan64Launch a) {
+// Four workgroups per CU (at most 128 registers): the levels of 2,636 and 1,701
+// tiles 39.6 and 42.1 -> 35.9 and 40.3 us against three.
+__global__ __launch_bounds__(256, 4) void plan64_bwd_kernel(const Plan64Launch a) {
   plan64_bwd_body(a, a.t_begin + blockIdx.x);
 }
 
@@ -948,7 +1006,22 @@ __device__ __forceinline__ void gemm64_ts_body(const Gemm64TsLaunch& a, int64_t 
     }
 }
 
-__global__ __launch_bounds__(256) void gemm64_ts_kernel(const Gemm64TsLaunch a) { gemm64_ts_body(a, blockIdx.x); }
+// The root's adjoint: its seed and the chains anchored there.
+__device__ __forceinline__ void root64_body(const Root64Launch& a) {
+  const int j = threadIdx.x;
+  if (j >= N64) return;
+  double v = a.root_slot >= 0 ? a.INJ[a.root_slot * N64 + j] : 0.0;
+  for (int i = 0; i < a.n_root_chains; ++i) v += a.INJ[(a.n_slots + a.root_chains[i]) * N64 + j];
+  a.out[j] = v;
+}
+
+// The chunks, and in the last workgroup the root.
+__global__ __launch_bounds__(256) void gemm64_ts_kernel(const Gemm64TsLaunch a, const Root64Launch root) {
+  if ((int)blockIdx.x < a.n_chunks)
+    gemm64_ts_body(a, blockIdx.x);
+  else
+    root64_body(root);
+}
 
 // Readouts per seed slot (the sequences ending at one node): p = E f, the
 // objective, dL/dp, the seed E^T (sum of the slot's dL/dp), and dL/dE, for
@@ -1143,25 +1216,16 @@ __global__ __launch_bounds__(READOUT64_WAVES * 64) void readout64_kernel(const R
   readout64_body<PACK>(a, blockIdx.x, gridDim.x);
 }
 
-__device__ __forceinline__ void root64_body(const Root64Launch& a) {
-  const int j = threadIdx.x;
-  double v = a.root_slot >= 0 ? a.INJ[a.root_slot * N64 + j] : 0.0;
-  for (int i = 0; i < a.n_root_chains; ++i) v += a.INJ[(a.n_slots + a.root_chains[i]) * N64 + j];
-  a.out[j] = v;
-}
-
-__global__ __launch_bounds__(64) void root64_kernel(const Root64Launch a) { root64_body(a); }
-
 // ---------------------------------------------------------------------------
 // Batched forms of the grouped-chain plan kernels: request blockIdx.y (z for
 // the slab sum), its arguments read before anything is stored, its own grid.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void gate_prep64_batch(const Plan64Req* r) {
   const Plan64Req& q = r[blockIdx.y];
-  if ((int)blockIdx.x >= q.tiles.K) return;
+  if ((int)blockIdx.x >= q.tiles.K * PREP_WG) return;
   // the tile kernels read the operand layouts (const there); the prep writes them
   gate_prep64_body(q.G, q.rho, const_cast<double*>(q.tiles.GA), const_cast<double*>(q.tiles.GAT), q.tiles.FA,
-                   blockIdx.x);
+                   nullptr, blockIdx.x);  // (the batch clears its counts together)
 }
 
 // The tile of workgroup `blk` of a level, per_tile workgroups each; -1: the level
@@ -1188,7 +1252,7 @@ __global__ __launch_bounds__(256, 2) void plan64_fwd_long_batch(const Plan64Req*
   plan64_fwd_long(a, t, blockIdx.x % QWG);
 }
 
-__global__ __launch_bounds__(256) void plan64_bwd_batch(const Plan64Req* r, int level) {
+__global__ __launch_bounds__(256, 4) void plan64_bwd_batch(const Plan64Req* r, int level) {
   const Plan64Req& q = r[blockIdx.y];
   const int64_t t = q.want_grad ? batch_tile(q, level, 0, blockIdx.x, 1) : -1;
   if (t < 0) return;
@@ -1214,16 +1278,14 @@ __global__ __launch_bounds__(READOUT64_WAVES * 64) void readout64_batch(const Pl
 
 __global__ __launch_bounds__(256) void gemm64_ts_batch(const Plan64Req* r) {
   const Plan64Req& q = r[blockIdx.y];
-  if (!q.want_grad || (int)blockIdx.x >= q.gemm.n_chunks) return;
-  const Gemm64TsLaunch a = q.gemm;
-  gemm64_ts_body(a, blockIdx.x);
-}
-
-__global__ __launch_bounds__(64) void root64_batch(const Plan64Req* r) {
-  const Plan64Req& q = r[blockIdx.y];
-  if (!q.want_grad) return;
-  const Root64Launch a = q.root;
-  root64_body(a);
+  if (!q.want_grad || (int)blockIdx.x > q.gemm.n_chunks) return;
+  if ((int)blockIdx.x < q.gemm.n_chunks) {
+    const Gemm64TsLaunch a = q.gemm;
+    gemm64_ts_body(a, blockIdx.x);
+  } else {
+    const Root64Launch a = q.root;
+    root64_body(a);
+  }
 }
 
 __global__ __launch_bounds__(256) void slab_sum64_stage1_batch(const Plan64Req* r) {
@@ -1248,15 +1310,15 @@ __global__ __launch_bounds__(256) void reduce64_batch(const Plan64Req* r) {
 }  // namespace
 
 hipError_t launch_gate_prep64(const double* G, const double* rho, int K, double* GA, double* GAT, double* FA,
-                              hipStream_t stream) {
+                              unsigned long long* nonpos, hipStream_t stream) {
   if (K < 1) return hipErrorInvalidValue;
-  gst_launch(gate_prep64_kernel, dim3(K), dim3(256), 0, stream, G, rho, GA, GAT, FA);
+  gst_launch(gate_prep64_kernel, dim3(K * PREP_WG), dim3(256), 0, stream, G, rho, GA, GAT, FA, nonpos);
   return hipGetLastError();
 }
 
-hipError_t launch_gemm64_ts(const Gemm64TsLaunch& a, hipStream_t stream) {
-  if (a.n_chunks <= 0) return hipSuccess;
-  gst_launch(gemm64_ts_kernel, dim3(a.n_chunks), dim3(256), 0, stream, a);
+hipError_t launch_gemm64_ts(const Gemm64TsLaunch& a, const Root64Launch& root, hipStream_t stream) {
+  if (a.n_chunks < 0) return hipErrorInvalidValue;
+  gst_launch(gemm64_ts_kernel, dim3(a.n_chunks + 1), dim3(256), 0, stream, a, root);
   return hipGetLastError();
 }
 
@@ -1301,11 +1363,6 @@ hipError_t launch_readout64(const Readout64Launch& a, int n_blocks, hipStream_t 
   return hipGetLastError();
 }
 
-hipError_t launch_root64(const Root64Launch& a, hipStream_t stream) {
-  gst_launch(root64_kernel, dim3(1), dim3(64), 0, stream, a);
-  return hipGetLastError();
-}
-
 static bool chain64_ok(const Chain64Launch& a, int n_blocks) {
   return a.K >= 1 && a.K <= 5 && a.tile_seqs >= 1 && a.tile_seqs <= SCHED_CHAINS && a.tile_row >= 1 && n_blocks >= 1;
 }
@@ -1325,7 +1382,7 @@ hipError_t launch_chain64_bwd(const Chain64Launch& a, int n_blocks, hipStream_t 
 hipError_t launch_gate_prep64_batch(const Plan64Req* reqs, int n, int K_max, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
   if (K_max < 1 || K_max > 5) return hipErrorInvalidValue;
-  gst_launch(gate_prep64_batch, dim3(K_max, n), dim3(256), 0, stream, reqs);
+  gst_launch(gate_prep64_batch, dim3(K_max * PREP_WG, n), dim3(256), 0, stream, reqs);
   return hipGetLastError();
 }
 
@@ -1355,15 +1412,9 @@ hipError_t launch_readout64_batch(const Plan64Req* reqs, int n, int grid_x, hipS
   return hipGetLastError();
 }
 
-hipError_t launch_gemm64_ts_batch(const Plan64Req* reqs, int n, int grid_x, hipStream_t stream) {
-  if (n <= 0 || grid_x <= 0) return hipSuccess;
-  gst_launch(gemm64_ts_batch, dim3(grid_x, n), dim3(256), 0, stream, reqs);
-  return hipGetLastError();
-}
-
-hipError_t launch_root64_batch(const Plan64Req* reqs, int n, hipStream_t stream) {
+hipError_t launch_gemm64_ts_batch(const Plan64Req* reqs, int n, int chunks_max, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
-  gst_launch(root64_batch, dim3(1, n), dim3(64), 0, stream, reqs);
+  gst_launch(gemm64_ts_batch, dim3(chunks_max + 1, n), dim3(256), 0, stream, reqs);
   return hipGetLastError();
 }
 
