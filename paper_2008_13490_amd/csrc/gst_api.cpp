@@ -272,12 +272,12 @@ struct DevicePlan64 {
           *col_chain = nullptr, *ev_ptr = nullptr, *ev_src = nullptr, *slot_row = nullptr, *slot_ptr = nullptr,
           *slot_seq = nullptr, *slot_pack = nullptr, *root_chains = nullptr, *ts_tile = nullptr, *chunk_beg = nullptr,
           *chunk_end = nullptr, *gate_chunk_ptr = nullptr;
-  int32_t *tile_len = nullptr, *ts_step = nullptr, *slot_cnt = nullptr;
+  int32_t *tile_len = nullptr, *ts_step = nullptr;
   uint8_t* ev_cend = nullptr;
   uint8_t* words = nullptr;
   int64_t* lvl_tile = nullptr;   // device copies of level_tile_ptr and level_long
   uint8_t* lvl_long = nullptr;
-  double *FA = nullptr, *BA = nullptr, *INJ = nullptr, *GA = nullptr, *GAT = nullptr, *slab = nullptr,
+  double *FA = nullptr, *BA = nullptr, *INJ = nullptr, *GA = nullptr, *GAT = nullptr, *slot_cnt = nullptr, *slab = nullptr,
          *part = nullptr, *chunk_slab = nullptr, *root_vec = nullptr;
   int readout_blocks = 0;
   int n_root_chains = 0;
@@ -754,7 +754,7 @@ int upload_plan64(gst_req* r, gst::Plan64& P, const int32_t* counts_host) {
                o_evc = c.take<uint8_t>(TS * 16 + 16), o_evs = c.take<int64_t>(NE + 1),
                o_sr = c.take<int64_t>(P.n_slots + 1), o_sp = c.take<int64_t>(P.n_slots + 2),
                o_sq = c.take<int64_t>(P.S + 1), o_spk = c.take<int64_t>(P.n_slots * 4 + 4),
-               o_scn = c.take<int32_t>(P.n_slots * M + 1), o_rc = c.take<int64_t>(NRC + 1),
+               o_scn = c.take<double>(P.n_slots * M + 1), o_rc = c.take<int64_t>(NRC + 1),
                o_rb = c.take<int64_t>(NR + 1),
                o_rf = c.take<int32_t>(NR + 1), o_cb = c.take<int64_t>(NC + 1), o_ce = c.take<int64_t>(NC + 1),
                o_gcp = c.take<int64_t>(K + 1), o_fa = c.take<double>((size_t)P.n_rows * 64),
@@ -782,7 +782,7 @@ int upload_plan64(gst_req* r, gst::Plan64& P, const int32_t* counts_host) {
   d.slot_ptr = reinterpret_cast<int64_t*>(b + o_sp);
   d.slot_seq = reinterpret_cast<int64_t*>(b + o_sq);
   d.slot_pack = reinterpret_cast<int64_t*>(b + o_spk);
-  d.slot_cnt = reinterpret_cast<int32_t*>(b + o_scn);
+  d.slot_cnt = reinterpret_cast<double*>(b + o_scn);
   d.root_chains = reinterpret_cast<int64_t*>(b + o_rc);
   d.ts_tile = reinterpret_cast<int64_t*>(b + o_rb);
   d.ts_step = reinterpret_cast<int32_t*>(b + o_rf);
@@ -819,9 +819,9 @@ int upload_plan64(gst_req* r, gst::Plan64& P, const int32_t* counts_host) {
   if ((rc = put(d.slot_seq, P.slot_seq.data(), P.slot_seq.size() * 8))) return rc;
   {
     // per slot: its node row, its first sequence and its sequence range, and
-    // the first sequence's counts (the readout loads them together, by slot)
+    // its sequences' counts added up (the readout loads them together, by slot)
     std::vector<int64_t> pack((size_t)P.n_slots * 4);
-    std::vector<int32_t> cnt((size_t)P.n_slots * M, 0);
+    std::vector<double> cnt((size_t)P.n_slots * M, 0.0);
     for (int64_t x = 0; x < P.n_slots; ++x) {
       const int64_t q0 = P.slot_ptr[x], q1 = P.slot_ptr[x + 1];
       const int64_t seq0 = q1 > q0 ? P.slot_seq[q0] : 0;
@@ -829,11 +829,11 @@ int upload_plan64(gst_req* r, gst::Plan64& P, const int32_t* counts_host) {
       pack[4 * x + 1] = seq0;
       pack[4 * x + 2] = q0;
       pack[4 * x + 3] = q1;
-      if (counts_host && q1 > q0)
-        for (int m = 0; m < M; ++m) cnt[(size_t)x * M + m] = counts_host[seq0 * M + m];
+      for (int64_t q = q0; counts_host && q < q1; ++q)
+        for (int m = 0; m < M; ++m) cnt[(size_t)x * M + m] += counts_host[P.slot_seq[q] * M + m];
     }
     if ((rc = put(d.slot_pack, pack.data(), pack.size() * 8))) return rc;
-    if ((rc = put(d.slot_cnt, cnt.data(), cnt.size() * 4))) return rc;
+    if ((rc = put(d.slot_cnt, cnt.data(), cnt.size() * 8))) return rc;
   }
   if ((rc = put(d.root_chains, P.root_chains.data(), NRC * 8))) return rc;
   if ((rc = put(d.ts_tile, P.ts_tile.data(), NR * 8))) return rc;

@@ -337,7 +337,7 @@ struct Readout64Launch {
   const int64_t* slot_seq;
   const int64_t* slot_pack;  // [n_slots][4]: node row, first sequence, slot_ptr[s], slot_ptr[s + 1]
                              // (null: slot s is the one sequence slot_seq[s], its state row s)
-  const int32_t* slot_cnt;   // [n_slots][M]: the first sequence's counts
+  const double* slot_cnt;    // [n_slots][M]: the counts of the slot's sequences added up (null without a plan)
   const int32_t* counts;
   const double* W;
   double* probs;

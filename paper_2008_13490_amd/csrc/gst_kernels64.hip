@@ -1036,18 +1036,25 @@ __global__ __launch_bounds__(256) void gemm64_ts_kernel(const Gemm64TsLaunch a, 
 // small LDS tile per wave.  Lane l = 16 r4 + c owns, in an output block, rows
 // 4v + r4 (v = 0..3) of column c.  Each wave writes one partial row
 // [objective | 0 | dL/dE]; every sum has a fixed order.
+// Its bytes would take 40 us in the list of 200,960 sequences (180,107 slots:
+// their states, counts and seeds); it takes 48, 97 before the next group's loads
+// ran ahead of the seeds' stores and the counts of equal words came added up
+// (a second word's were three dependent loads, in most groups of sixteen).
 constexpr int RO_FST = 66;  // padded row stride (doubles) of a wave's staged states
 constexpr int RO_DST = 17;  // the same for its dL/dp tile
+constexpr int RO_EST = 80;  // the same for the effects
 
 // Workgroup blk of n_blocks (the waves' slot groups depend on the count, so a
 // request's sums are the same in any launch that gives it n_blocks workgroups).
 // PACK: the slots of a plan; otherwise slot s is the one sequence slot_seq[s],
 // its state row s (a variant of its own: the choice at run time cost the plan's
-// evaluation 18 us on the 200,960-sequence list).
+// evaluation 18 us on that list).
 template <bool PACK>
 __device__ __forceinline__ void readout64_body(const Readout64Launch& a, int64_t blk, int64_t n_blocks) {
-  __shared__ double Fs[READOUT64_WAVES][16 * RO_FST];
+  __shared__ __align__(16) double Fs[READOUT64_WAVES][16 * RO_FST];
   __shared__ double Ds[READOUT64_WAVES][16 * RO_DST];
+  __shared__ double Es[16 * RO_EST];
+  __shared__ double Ep[16 * 64];
   const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = l & 15, r4 = l >> 4;
   const int64_t wv = blk * READOUT64_WAVES + w;
@@ -1061,14 +1068,14 @@ __device__ __forceinline__ void readout64_body(const Readout64Launch& a, int64_t
   const auto* g_W = as_global(a.W);
   auto* g_probs = as_global(a.probs);
   const bool grad = a.want_grad != 0;
-  // E as B operands: eP[kk] = E[c][4kk + r4] for P^T, eS[kk][tc] = E[4kk + r4][16tc + c] for S^T
-  double eP[16], eS[4][4];
-#pragma unroll
-  for (int kk = 0; kk < 16; ++kk) eP[kk] = c < M ? gE[c * N64 + 4 * kk + r4] : 0.0;
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-    for (int tc = 0; tc < 4; ++tc) eS[kk][tc] = 4 * kk + r4 < M ? gE[(4 * kk + r4) * N64 + 16 * tc + c] : 0.0;
+  // E in LDS, rows beyond M zero: for S^T, and as the B operands of P^T, Ep[kk][l] = E[c][4kk + r4]
+  for (int x = threadIdx.x; x < 16 * N64; x += READOUT64_WAVES * 64) {
+    const int m = x >> 6, j = x & 63;
+    const double e = m < M ? gE[x] : 0.0;
+    Es[m * RO_EST + j] = e;
+    Ep[(j >> 2) * 64 + (j & 3) * 16 + m] = e;
+  }
+  __syncthreads();
   d4 dE[4];
 #pragma unroll
   for (int tc = 0; tc < 4; ++tc) dE[tc] = d4{0.0, 0.0, 0.0, 0.0};
@@ -1077,82 +1084,115 @@ __device__ __forceinline__ void readout64_body(const Readout64Launch& a, int64_t
   double* Fw = Fs[w];
   double* Dw = Ds[w];
   const int64_t n_groups = (a.n_slots + 15) / 16;
-  for (int64_t gi = wv; gi < n_groups; gi += nw) {
-    // slot 16 gi + c: its state row, the A operand of P^T (elements 4kk + r4)
+  // Slot 16 gi + c: its state row (groups past the end read a row that exists)
+  auto row_of = [&](int64_t gi) {
     const int64_t sc = gi * 16 + c;
-    const int64_t rowc = PACK ? g_pack[4 * (sc < a.n_slots ? sc : 0)] : (sc < a.n_slots ? sc : a.n_slots - 1);
-    // the sixteen rows read whole (two rows of 512 B per load, 16 B per lane)
-    // into the wave's tile, then the A operand from there
-    {
-      const auto* fa2 = as_global(reinterpret_cast<const d2*>(a.FA));
-      d2 rv[8];
+    return PACK ? g_pack[4 * (sc < a.n_slots ? sc : 0)] : (sc < a.n_slots ? sc : a.n_slots - 1);
+  };
+  // a group's sixteen rows, read whole: two rows of 512 B per load, 16 B per lane
+  d2 rv[8];
+  auto load_rows = [&](int64_t rowc) {
+    const auto* fa2 = as_global(reinterpret_cast<const d2*>(a.FA));
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int64_t rr = __shfl(rowc, 2 * i + (l >> 5));
-        rv[i] = fa2[rr * (N64 / 2) + (l & 31)];
-      }
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int i = 0; i < 8; ++i) *reinterpret_cast<d2*>(&Fw[(2 * i + (l >> 5)) * RO_FST + 2 * (l & 31)]) = rv[i];
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int i = 0; i < 8; ++i) {
+      const int64_t rr = __shfl(rowc, 2 * i + (l >> 5));
+      rv[i] = fa2[rr * (N64 / 2) + (l & 31)];
     }
-    double fA[16];
+  };
+  // Slots 16 gi + 4v + r4 of the output rows: the first sequence, the range of
+  // the sequences (low words, only their difference is used) and (plans) their
+  // counts of outcome c added up.  Raw loads, the conditions where they are used: a
+  // load whose value is used here would be waited for.
+  int64_t seq_n[4];
+  int beg_n[4], end_n[4];
+  double cnt_n[4];
+  const auto* g_pack32 = as_global(reinterpret_cast<const int32_t*>(a.slot_pack));
+  auto load_slots = [&](int64_t gi) {
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) fA[kk] = Fw[c * RO_FST + 4 * kk + r4];
-    // slots 16 gi + 4v + r4 of the output rows: first sequence, sequence range,
-    // the first sequence's count (or weight) of outcome c
-    int64_t seq0[4], q0[4], q1[4];
+    for (int v = 0; v < 4; ++v) {
+      const int64_t s = gi * 16 + 4 * v + r4, b = s < a.n_slots ? s : 0;
+      if (PACK) {
+        seq_n[v] = g_pack[4 * b + 1];
+        beg_n[v] = g_pack32[8 * b + 4];
+        end_n[v] = g_pack32[8 * b + 6];
+        cnt_n[v] = g_cnt[b * M + (c < M ? c : 0)];
+      } else {
+        seq_n[v] = g_seq[b];
+        beg_n[v] = 0;
+        end_n[v] = 1;
+        cnt_n[v] = 0.0;
+      }
+    }
+  };
+  int64_t row_next = 0;
+  if (wv < n_groups) {
+    load_rows(row_of(wv));
+    load_slots(wv);
+    row_next = row_of(wv + nw);
+  }
+  for (int64_t gi = wv; gi < n_groups; gi += nw) {
+    // the rows into the wave's tile, then the A operand of P^T (elements
+    // 4kk + r4) from there.  The next group's rows and slots are loaded now, and
+    // the one after's row numbers: a load issued behind the seeds' stores would
+    // wait for them
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<d2*>(&Fw[(2 * i + (l >> 5)) * RO_FST + 2 * (l & 31)]) = rv[i];
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int64_t seq0[4];
+    int many[4];
     double n0[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int64_t s = gi * 16 + 4 * v + r4;
-      const bool valid = s < a.n_slots;
-      n0[v] = 0.0;
-      if (PACK) {
-        const int64_t b = 4 * (valid ? s : 0);
-        seq0[v] = g_pack[b + 1];
-        q0[v] = g_pack[b + 2];
-        q1[v] = valid ? g_pack[b + 3] : q0[v];
-        if (a.mode == MODE_LOGLIK && valid && c < M) n0[v] = (double)g_cnt[s * M + c];
-      } else {  // one sequence per slot
-        seq0[v] = g_seq[valid ? s : 0];
-        q0[v] = 0;
-        q1[v] = valid ? 1 : 0;
-        if (a.mode == MODE_LOGLIK && valid && c < M) n0[v] = (double)g_counts[seq0[v] * M + c];
+      seq0[v] = seq_n[v];
+      many[v] = gi * 16 + 4 * v + r4 < a.n_slots ? end_n[v] - beg_n[v] : 0;
+      n0[v] = 0.0;  // the counts, or the first sequence's weight
+      if (many[v] > 0 && c < M) {
+        if (a.mode == MODE_LOGLIK) n0[v] = PACK ? cnt_n[v] : (double)g_counts[seq0[v] * M + c];
+        if (a.mode == MODE_VJP) n0[v] = g_W[seq0[v] * M + c];
       }
     }
-    if (a.mode == MODE_VJP) {
+    load_rows(row_next);
+    load_slots(gi + nw);
+    row_next = row_of(gi + 2 * nw);
+    double fA[16];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) n0[v] = q1[v] > q0[v] && c < M ? g_W[seq0[v] * M + c] : 0.0;
-    }
+    for (int kk = 0; kk < 16; ++kk) fA[kk] = Fw[c * RO_FST + 4 * kk + r4];
     d4 p = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) p = __builtin_amdgcn_mfma_f64_16x16x4f64(fA[kk], eP[kk], p, 0, 0, 0);
-    double dps[4];
+    for (int kk = 0; kk < 16; ++kk) p = __builtin_amdgcn_mfma_f64_16x16x4f64(fA[kk], Ep[kk * 64 + l], p, 0, 0, 0);
+    // sequence q of the slot of row v
+    auto seq_of = [&](int v, int q) {
+      return q == 0 ? seq0[v] : g_seq[g_pack[4 * (gi * 16 + 4 * v + r4) + 2] + q];
+    };
+    double dps[4] = {0.0, 0.0, 0.0, 0.0};
+    if (a.mode == MODE_LOGLIK) {
+      // the sequences of a slot have one probability: their counts count together
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      dps[v] = 0.0;
-      if (c >= M) continue;
-      for (int64_t q = q0[v]; q < q1[v]; ++q) {
-        const int64_t seq = q == q0[v] ? seq0[v] : g_seq[q];
-        const int64_t o = seq * M + c;
-        if (a.probs) g_probs[o] = p[v];
-        if (a.mode == MODE_LOGLIK) {
-          const double N = q == q0[v] ? n0[v] : (double)g_counts[o];
-          if (N > 0.0) {
-            if (p[v] <= 0.0) {
-              ++nonpos;
-              obj = INFINITY;
-            } else {
-              obj -= N * log(p[v]);
-              dps[v] += -N / p[v];
-            }
+      for (int v = 0; v < 4; ++v) {
+        const double N = n0[v], lp = log(p[v]), ratio = N / p[v];
+        if (N > 0.0) {
+          if (p[v] <= 0.0) {
+            obj = INFINITY;
+            for (int q = 0; q < many[v]; ++q) nonpos += g_counts[seq_of(v, q) * M + c] > 0;
+          } else {
+            obj -= N * lp;
+            dps[v] = -ratio;
           }
-        } else if (a.mode == MODE_VJP) {
-          dps[v] += q == q0[v] ? n0[v] : g_W[o];
         }
       }
+    } else if (a.mode == MODE_VJP && c < M) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        dps[v] = n0[v];
+        for (int q = 1; q < many[v]; ++q) dps[v] += g_W[seq_of(v, q) * M + c];
+      }
+    }
+    if (a.probs && c < M) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        for (int q = 0; q < many[v]; ++q) g_probs[seq_of(v, q) * M + c] = p[v];
     }
     if (!grad) continue;
 #pragma unroll
@@ -1166,7 +1206,7 @@ __device__ __forceinline__ void readout64_body(const Readout64Launch& a, int64_t
       for (int tc = 0; tc < 4; ++tc)
         dE[tc] = __builtin_amdgcn_mfma_f64_16x16x4f64(dps[kk], Fw[(4 * kk + r4) * RO_FST + 16 * tc + c], dE[tc], 0, 0,
                                                       0);
-    // S^T = D E: A = D[slot c][outcome 4kk + r4], B = eS
+    // S^T = D E: A = D[slot c][outcome 4kk + r4], B = E
     double dA[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) dA[kk] = Dw[c * RO_DST + 4 * kk + r4];
@@ -1175,7 +1215,10 @@ __device__ __forceinline__ void readout64_body(const Readout64Launch& a, int64_t
     for (int tc = 0; tc < 4; ++tc) {
       st[tc] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) st[tc] = __builtin_amdgcn_mfma_f64_16x16x4f64(dA[kk], eS[kk][tc], st[tc], 0, 0, 0);
+      for (int kk = 0; kk < 4; ++kk)
+        if (4 * kk < M)
+          st[tc] = __builtin_amdgcn_mfma_f64_16x16x4f64(dA[kk], Es[(4 * kk + r4) * RO_EST + 16 * tc + c], st[tc], 0, 0,
+                                                        0);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {

@@ -57,3 +57,41 @@ def test_partly_filled_tiles(oracle_lib, gpu, n_fid, spec, powers):
     bt.close()
     req.close()
     req2.close()
+
+
+@pytest.mark.parametrize("copies", [1, 2, 5])
+def test_sequences_of_one_slot(oracle_lib, gpu, copies):
+    """Equal words with counts of their own: summed for the objective, counted one by one where p <= 0."""
+    import torch
+    api, ctx = gpu
+    rng = np.random.default_rng(11)
+    m = W.noisy_gateset("3q", W.LAMBDA, W.SIGMA, rng)
+    fids = W.shortlex_words((1, 2), 6)
+    sl = W.structured_list(fids, fids, W.random_germs(m.K, [(2, 3)], rng), [1, 2, 4, 8, 16])
+    words = [list(sl.word(s)) for s in range(sl.S)]
+    for x in range(copies - 1):
+        words += words[x:sl.S:7]
+    sl = W.from_words(words)
+    counts = rng.integers(0, 3, size=(sl.S, m.M)).astype(np.int32)
+    counts[oracle_lib.probs(m.rho, m.effects, m.gates, sl.offsets, sl.gates) <= 0] = 0
+    F, p_or, g_or, _, rc = oracle_lib.loglik(m.rho, m.effects, m.gates, sl.offsets, sl.gates, counts)
+    assert rc == 0
+    gs = api.DeviceGateSet.from_numpy(m.n_qubits, m.rho, m.effects, m.gates)
+    req = api.Request(ctx, m.n_qubits, m.K, m.M, sl.offsets, sl.gates, counts)
+    assert req.plan_info()["grouped"] == 1
+    obj, p, g = req.eval(gs, want_probs=True)
+    ctx.sync()
+    assert np.array_equal(p.cpu().numpy(), p_or)
+    assert abs(float(obj.cpu()[0]) - F) <= 1e-10 * abs(F)
+    assert np.abs(g.cpu().numpy() - g_or).max() <= 1e-10 * np.abs(g_or).max()
+    w = rng.standard_normal((sl.S, m.M))
+    v = req.vjp(gs, torch.as_tensor(w, device="cuda"))
+    ctx.sync()
+    v_or = oracle_lib.vjp(m.rho, m.effects, m.gates, sl.offsets, sl.gates, w)
+    assert np.abs(v.cpu().numpy() - v_or).max() <= 1e-10 * np.abs(v_or).max()
+    none = m.effects.copy()
+    none[1] = 0.0
+    o, _, _ = req.eval(api.DeviceGateSet.from_numpy(m.n_qubits, m.rho, none, m.gates))
+    rc, _, nonpos = ctx.sync(raise_on_error=False)
+    assert rc == -3 and nonpos == int(np.count_nonzero(counts[:, 1] > 0)) and float(o.cpu()[0]) == float("inf")
+    req.close()
