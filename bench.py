@@ -1083,12 +1083,10 @@ def algorithmic_flops(family, D, M, S, sum_len, info):
     filled = ts - info.get("chain_steps", ts)   # trunk states / adjoints inside germ-power jumps
     if family == "leaf":   # items: forward + adjoint mat-vecs, readout, seed, dE; the forward fill tasks
         return 4.0 * D * D * its + 6.0 * D * M * S + 2.0 * D * D * filled
-    if family == "fill":   # reverse fill tasks
-        return 2.0 * D * D * filled
     if family in ("trunk_fwd", "trunk_bwd"):   # the chain's mat-vecs (a germ-power jump counts once)
         return 2.0 * D * D * info.get("chain_steps", ts) / lv
-    if family == "grad_gemm":
-        return 2.0 * D * D * (ts + its)
+    if family == "grad_gemm":   # every step's rank-one update; the adjoints inside germ-power jumps
+        return 2.0 * D * D * (ts + its + filled)
     return 0.0
 
 

@@ -234,10 +234,10 @@ struct DevicePlan {
   int64_t* item_step_ptr = nullptr;
   int64_t* rec_b = nullptr;
   int64_t* rec_f = nullptr;
-  int64_t* chunk_gate = nullptr;
+  int64_t* chunk_tile = nullptr;
   int64_t* chunk_beg = nullptr;
   int64_t* chunk_end = nullptr;
-  double* FA = nullptr;         // state arena [1 + trunk_steps + item_steps][D]
+  double* FA = nullptr;         // state arena [1 + trunk_steps + item_steps][D], then rows of zeros
   double* BA = nullptr;         // adjoint arena [trunk_steps + item_steps][D]
   double* src_adj = nullptr;    // [source rows][D]: adjoints arriving at stored states, slot by slot
   double* inj = nullptr;        // [n_inj][D]
@@ -251,6 +251,12 @@ struct DevicePlan {
   int32_t* fill_n = nullptr;
   uint32_t* fill_pattern = nullptr;
   uint8_t* fill_gate3 = nullptr;
+  // the gradient's record chunks, its jump groups, and the tiles of each gate
+  int64_t n_chunks = 0, n_jump_groups = 0, zero_row = 0;
+  std::vector<int64_t> tile_ptr;  // [K + 1]
+  int64_t* jump_first = nullptr;
+  int64_t* jump_in = nullptr;
+  int32_t* jump_meta = nullptr;
 };
 
 // Levels whose longest chain has at least this many steps run the sweeps four
@@ -410,7 +416,7 @@ struct gst_batch {
     int D = 0, n = 0, K_max = 1, M_max = 1, jl_max = 0, n_levels = 0;
     bool any_grad = false, any_slab = false;
     std::vector<int> fwd_grid, bwd_grid, inj_grid;  // per level
-    int item_grid = 0, fill_grid = 0, gemm_grid = 0, red_x = 0, red_parts = 1;
+    int item_grid = 0, gemm_grid = 0, red_x = 0, red_parts = 1;
     gst::PlanBatch dev{};
   } pgroup[2];
   DevBuf plan_ws;                       // the batched plans' scratch, one region per request
@@ -634,7 +640,9 @@ int upload_plan(gst_req* r, const gst::HostPlan& P, const int32_t* counts_host) 
   d.host = P;
   const int D = r->D;
   const int64_t nI = P.n_items(), nT = P.n_trunks(), nTS = P.trunk_steps(), nJ = (int64_t)P.inj_loc.size(),
-                nIS = P.item_steps(), nR = (int64_t)P.rec_b.size(), nC = P.n_chunks();
+                nIS = P.item_steps();
+  const gst::GradWork gw(P, r->K);
+  const int64_t nR = (int64_t)gw.rec_b.size(), nC = (int64_t)gw.chunk_beg.size();
   // injection list of each trunk, steps descending
   Carver c;
   const size_t nOp = P.op_desc.size();
@@ -645,13 +653,14 @@ int upload_plan(gst_req* r, const gst::HostPlan& P, const int32_t* counts_host) 
                o_icnt = c.take<int32_t>((size_t)nI * r->M + 1), o_tsrc = c.take<int32_t>(nT + 1), o_isp = c.take<int64_t>(nI + 1),
                o_rb = c.take<int64_t>(nR + 1), o_rf = c.take<int64_t>(nR + 1), o_cg = c.take<int64_t>(nC + 1),
                o_cb = c.take<int64_t>(nC + 1), o_ce = c.take<int64_t>(nC + 1),
-               o_fa = c.take<double>((size_t)(1 + nTS + nIS) * D), o_ba = c.take<double>((size_t)(nTS + nIS + 1) * D),
+               o_fa = c.take<double>((size_t)(1 + nTS + nIS + gst::JUMP_STEPS_MAX + 1) * D), o_ba = c.take<double>((size_t)(nTS + nIS + 1) * D),
                o_src = c.take<double>((size_t)(P.n_src_rows() + 1) * D), o_inj = c.take<double>((size_t)(nJ + 1) * D);
   const size_t nF = P.fill_first.size();
   const size_t o_jp = c.take<uint32_t>(nT + 1), o_jg3 = c.take<uint8_t>(nT + 1), o_jlv = c.take<uint8_t>(nT + 1),
                o_jt = c.take<double>((size_t)nT * std::max(P.jump_levels, 1) * 256 + 1), o_ff = c.take<int64_t>(nF + 1),
                o_fi = c.take<int64_t>(nF + 1), o_fn = c.take<int32_t>(nF + 1), o_fp = c.take<uint32_t>(nF + 1),
-               o_fg3 = c.take<uint8_t>(nF + 1);
+               o_fg3 = c.take<uint8_t>(nF + 1), o_jf = c.take<int64_t>(gw.jump_first.size() + 1),
+               o_ji = c.take<int64_t>(gw.jump_in.size() + 1), o_jm = c.take<int32_t>(gw.jump_meta.size() + 1);
   int rc = d.buf.reserve(c.off + 256, r->ctx->stream);
   if (rc) return rc;
   char* b = reinterpret_cast<char*>(d.buf.p);
@@ -669,7 +678,7 @@ int upload_plan(gst_req* r, const gst::HostPlan& P, const int32_t* counts_host) 
   d.item_step_ptr = reinterpret_cast<int64_t*>(b + o_isp);
   d.rec_b = reinterpret_cast<int64_t*>(b + o_rb);
   d.rec_f = reinterpret_cast<int64_t*>(b + o_rf);
-  d.chunk_gate = reinterpret_cast<int64_t*>(b + o_cg);
+  d.chunk_tile = reinterpret_cast<int64_t*>(b + o_cg);
   d.chunk_beg = reinterpret_cast<int64_t*>(b + o_cb);
   d.chunk_end = reinterpret_cast<int64_t*>(b + o_ce);
   d.FA = reinterpret_cast<double*>(b + o_fa);
@@ -685,6 +694,13 @@ int upload_plan(gst_req* r, const gst::HostPlan& P, const int32_t* counts_host) 
   d.fill_n = reinterpret_cast<int32_t*>(b + o_fn);
   d.fill_pattern = reinterpret_cast<uint32_t*>(b + o_fp);
   d.fill_gate3 = reinterpret_cast<uint8_t*>(b + o_fg3);
+  d.jump_first = reinterpret_cast<int64_t*>(b + o_jf);
+  d.jump_in = reinterpret_cast<int64_t*>(b + o_ji);
+  d.jump_meta = reinterpret_cast<int32_t*>(b + o_jm);
+  d.n_chunks = nC;
+  d.n_jump_groups = (int64_t)gw.jump_meta.size() / 8;
+  d.zero_row = 1 + nTS + nIS;
+  d.tile_ptr = gw.tile_ptr;
   auto put = [&](void* dst, const void* src, size_t bytes) -> int {
     if (bytes) HIP_TRY(hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice));
     return GST_OK;
@@ -706,11 +722,15 @@ int upload_plan(gst_req* r, const gst::HostPlan& P, const int32_t* counts_host) 
   }
   if ((rc = put(d.trunk_src, P.trunk_src.data(), (size_t)nT * 4))) return rc;
   if ((rc = put(d.item_step_ptr, P.item_step_ptr.data(), P.item_step_ptr.size() * 8))) return rc;
-  if ((rc = put(d.rec_b, P.rec_b.data(), P.rec_b.size() * 8))) return rc;
-  if ((rc = put(d.rec_f, P.rec_f.data(), P.rec_f.size() * 8))) return rc;
-  if ((rc = put(d.chunk_gate, P.chunk_gate.data(), P.chunk_gate.size() * 8))) return rc;
-  if ((rc = put(d.chunk_beg, P.chunk_beg.data(), P.chunk_beg.size() * 8))) return rc;
-  if ((rc = put(d.chunk_end, P.chunk_end.data(), P.chunk_end.size() * 8))) return rc;
+  if ((rc = put(d.rec_b, gw.rec_b.data(), nR * 8))) return rc;
+  if ((rc = put(d.rec_f, gw.rec_f.data(), nR * 8))) return rc;
+  if ((rc = put(d.chunk_tile, gw.chunk_tile.data(), nC * 8))) return rc;
+  if ((rc = put(d.chunk_beg, gw.chunk_beg.data(), nC * 8))) return rc;
+  if ((rc = put(d.chunk_end, gw.chunk_end.data(), nC * 8))) return rc;
+  HIP_TRY(hipMemset(d.FA + d.zero_row * D, 0, (size_t)(gst::JUMP_STEPS_MAX + 1) * D * 8));
+  if ((rc = put(d.jump_first, gw.jump_first.data(), gw.jump_first.size() * 8))) return rc;
+  if ((rc = put(d.jump_in, gw.jump_in.data(), gw.jump_in.size() * 8))) return rc;
+  if ((rc = put(d.jump_meta, gw.jump_meta.data(), gw.jump_meta.size() * 4))) return rc;
   if ((rc = put(d.trunk_jpat, P.trunk_jump_pattern.data(), P.trunk_jump_pattern.size() * 4))) return rc;
   if ((rc = put(d.trunk_jg3, P.trunk_jump_gate3.data(), P.trunk_jump_gate3.size()))) return rc;
   if ((rc = put(d.trunk_jlev, P.trunk_jump_levels.data(), P.trunk_jump_levels.size()))) return rc;
@@ -1063,7 +1083,7 @@ void plan_setup(gst_req* r, const gst_gateset* th, int mode, const double* w, do
     s.tb_at[l] = n_head;
     if (s.want_grad) n_head += s.tb_blocks[l];
   }
-  const int64_t n_chunks = s.want_grad ? P.n_chunks() : 0;
+  const int64_t n_tiles = s.want_grad ? d.tile_ptr[r->K] : 0;
   gst::PlanReduce& red = s.red;
   red.D = D;
   red.M = r->M;
@@ -1072,7 +1092,7 @@ void plan_setup(gst_req* r, const gst_gateset* th, int mode, const double* w, do
   red.P = s.need_slab ? Pw : 0;
   red.n_part = gst::reduce_parts(n_head);
   for (int k = 0; k <= red.K; ++k) {
-    red.chunk_ptr[k] = std::lower_bound(P.chunk_gate.begin(), P.chunk_gate.end(), (int64_t)k) - P.chunk_gate.begin();
+    red.chunk_ptr[k] = red.K > 0 ? d.tile_ptr[k] : 0;
     if (k > 0) {
       const int64_t nk = red.chunk_ptr[k] - red.chunk_ptr[k - 1];
       red.n_part = std::max(red.n_part, gst::reduce_parts((int)std::min<int64_t>(nk, 1 << 20)));
@@ -1081,7 +1101,7 @@ void plan_setup(gst_req* r, const gst_gateset* th, int mode, const double* w, do
   red.objective = objective;
   red.grad = grad;
   s.head_bytes = (size_t)n_head * s.H * 8;
-  s.tile_bytes = (size_t)n_chunks * D * D * 8;
+  s.tile_bytes = (size_t)n_tiles * D * D * 8;
   s.part_bytes = s.need_slab ? (size_t)red.n_part * Pw * 8 : 0;
 
   gst::PlanArgs& a = s.a;
@@ -1142,12 +1162,18 @@ void plan_setup(gst_req* r, const gst_gateset* th, int mode, const double* w, do
   g.D = D;
   g.M = r->M;
   g.K = r->K;
-  g.n_chunks = n_chunks;
-  g.chunk_gate = d.chunk_gate;
+  g.n_chunks = s.want_grad ? d.n_chunks : 0;
+  g.chunk_tile = d.chunk_tile;
   g.chunk_beg = d.chunk_beg;
   g.chunk_end = d.chunk_end;
   g.rec_b = d.rec_b;
   g.rec_f = d.rec_f;
+  g.n_jump_groups = s.want_grad ? d.n_jump_groups : 0;
+  g.jump_first = d.jump_first;
+  g.jump_in = d.jump_in;
+  g.jump_meta = d.jump_meta;
+  g.G = th->gates;
+  g.zero_row = d.zero_row;
   g.FA = d.FA;
   g.BA = d.BA;
 }
@@ -1188,10 +1214,6 @@ int run_plan(gst_req* r, const gst_gateset* th, int mode, const double* w, doubl
       a.slab = slab + (size_t)s.tb_at[l] * s.H;
       ProfScope ps(ctx, FAM_TRUNK_BWD);
       HIP_TRY(gst::launch_trunk_bwd(a, ctx->stream));
-    }
-    if (a.n_fill > 0) {
-      ProfScope ps(ctx, FAM_FILL);
-      HIP_TRY(gst::launch_fill_rev(a, ctx->stream));
     }
     ProfScope ps(ctx, FAM_GEMM);
     HIP_TRY(gst::launch_grad_gemm(s.g, ctx->stream));
@@ -1944,10 +1966,6 @@ static int batch_enqueue(gst_batch* b, hipStream_t stream, bool eager) {
         ProfScope ps(pc, FAM_TRUNK_BWD);
         HIP_TRY(gst::launch_trunk_bwd_batch(pg.dev, pg.D, pg.n, l, pg.bwd_grid[l], pg.K_max, pg.jl_max, stream));
       }
-      if (pg.fill_grid > 0) {
-        ProfScope ps(pc, FAM_FILL);
-        HIP_TRY(gst::launch_fill_rev_batch(pg.dev, pg.D, pg.n, pg.fill_grid, pg.K_max, pg.M_max, stream));
-      }
       ProfScope ps(pc, FAM_GEMM);
       HIP_TRY(gst::launch_grad_gemm_batch(pg.dev, pg.D, pg.n, pg.gemm_grid, stream));
     }
@@ -2141,7 +2159,7 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
       }
       if (st.want_grad) {
         pg.any_grad = true;
-        pg.gemm_grid = (int)std::max<int64_t>(pg.gemm_grid, st.g.n_chunks);
+        pg.gemm_grid = (int)std::max<int64_t>(pg.gemm_grid, gst::grad_blocks_for(st.g));
       }
       if (st.need_slab) {
         pg.any_slab = true;
@@ -2167,7 +2185,6 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
       if (st.a.fill_blocks > 0)
         st.a.fill_blocks = (int)std::max<int64_t>(1, (st.a.fill_blocks + per_wg - 1) / per_wg);
       pg.item_grid = std::max(pg.item_grid, st.a.item_blocks + st.a.fill_blocks);
-      if (st.want_grad && st.a.n_fill > 0) pg.fill_grid = std::max(pg.fill_grid, st.a.fill_blocks);
     }
   }
   if (ws_total > 0) {

@@ -114,7 +114,7 @@ struct PlanArgs {
   double* jump_t;                // [n_trunks][jump_levels][16][16]: the forward sweep's jump
                                  // matrices, transposed, for the reverse sweep
   int item_blocks;               // item workgroups; the item launch adds the forward fill workgroups
-  // fill tasks: states (forward) or adjoints (reverse) inside each jump
+  // fill tasks: the states inside each jump
   int64_t n_fill;
   const int64_t* fill_first;
   const int64_t* fill_in;
@@ -144,25 +144,39 @@ struct InjectLaunch {
   const int64_t* lvl_inj;
 };
 
-// dG from the reverse-sweep records: chunk c adds, for gate chunk_gate[c],
-// sum over records r in [chunk_beg[c], chunk_end[c]) of BA[rec_b[r]] FA[rec_f[r]]^T.
+constexpr int JUMP_STEPS_MAX = 255;  // steps of a germ-power jump (8 bits of its op)
+// dG from the reverse sweep, as D x D tiles of one gate each.  Record chunk c adds
+// sum over records r in [chunk_beg[c], chunk_end[c]) of BA[rec_b[r]] FA[rec_f[r]]^T
+// into tile chunk_tile[c].  The steps inside germ-power jumps have no records: a
+// jump group is up to sixteen jumps of one pattern and length n (column c the
+// arena rows jump_first[16 g + c] .. + n - 1, from the state row jump_in[16 g + c];
+// column 0 always exists, -1: none); its adjoints run from the jump's end back
+// through the pattern, and phase ph of the pattern goes to tile jump_meta[8 g + 4 + ph].
 struct GemmLaunch {
   int D, M, K;
-  int64_t n_chunks;
-  const int64_t* chunk_gate;
+  int64_t n_chunks;            // record chunks
+  const int64_t* chunk_tile;
   const int64_t* chunk_beg;
   const int64_t* chunk_end;
   const int64_t* rec_b;
   const int64_t* rec_f;
+  int64_t n_jump_groups;
+  const int64_t* jump_first;   // [n_jump_groups][16]
+  const int64_t* jump_in;      // [n_jump_groups][16]
+  const int32_t* jump_meta;    // [n_jump_groups][8]: steps, pattern, fourth gate, 0, the phases' tiles
+  const double* G;
   const double* FA;
   const double* BA;
-  double* tiles;  // [n_chunks][D*D]: the chunk's contribution to its gate's gradient tile
+  int64_t zero_row;            // FA rows of zeros: this one and JUMP_STEPS_MAX after it
+  double* tiles;  // [tiles][D*D]: each a contribution to its gate's gradient
 };
+// Workgroups of the gradient launch: four jump groups each, then a record chunk each.
+__host__ __device__ inline int64_t grad_blocks_for(const GemmLaunch& g) { return (g.n_jump_groups + 3) / 4 + g.n_chunks; }
 
 // Ordered sum of the sharing plan's partial results.  Head rows hold
-// [objective | dL/drho | dL/dE] (width H = 1 + D + M*D); each gradient chunk
-// holds one D x D tile of gate chunk_gate, the chunks of gate k being rows
-// chunk_ptr[k] .. chunk_ptr[k+1] of `tiles`.  Output column x of the width
+// [objective | dL/drho | dL/dE] (width H = 1 + D + M*D); the gradient
+// kernel leaves D x D tiles, those of gate k being rows chunk_ptr[k] ..
+// chunk_ptr[k+1] of `tiles`.  Output column x of the width
 // P = H + K*D*D result (0: objective, x >= 1: grad[x-1]) adds the rows of its
 // own region in two fixed stages.  `part` holds n_part * P doubles.
 struct PlanReduce {
@@ -423,7 +437,7 @@ hipError_t launch_reduce_plan(const PlanReduce& a, hipStream_t stream);
 // takes args[y], inject[y], gemm[y], reduce[y] (device arrays).  Each launch
 // spans the most workgroups any request's standalone launch has (grid_x);
 // K_max and jl_max size the LDS.  The sequence is: trunk_fwd per level
-// ascending, items, then (inject, trunk_bwd) per level descending, fill_rev,
+// ascending, items, then (inject, trunk_bwd) per level descending,
 // grad_gemm, reduce.
 struct PlanBatch {
   const PlanArgs* args;
@@ -438,8 +452,6 @@ hipError_t launch_items_batch(const PlanBatch& b, int D, int n, int grid_x, int 
 hipError_t launch_inject_batch(const PlanBatch& b, int n, int level, int grid_x, hipStream_t stream);
 hipError_t launch_trunk_bwd_batch(const PlanBatch& b, int D, int n, int level, int grid_x, int K_max, int jl_max,
                                   hipStream_t stream);
-hipError_t launch_fill_rev_batch(const PlanBatch& b, int D, int n, int grid_x, int K_max, int M_max,
-                                 hipStream_t stream);
 hipError_t launch_grad_gemm_batch(const PlanBatch& b, int D, int n, int grid_x, hipStream_t stream);
 hipError_t launch_reduce_plan_batch(const PlanBatch& b, int n, int grid_x, int parts, hipStream_t stream);
 // Predictions of repeated gate applications: V = block-start states
@@ -483,7 +495,6 @@ hipError_t launch_param_forward(const ParamLaunch& a, hipStream_t stream);
 hipError_t launch_param_backward(const ParamLaunch& a, hipStream_t stream);
 
 // reverse fill tasks (adjoints inside the jumps into BA)
-hipError_t launch_fill_rev(const PlanArgs& a, hipStream_t stream);
 int fill_blocks_for(int64_t n_fill);
 
 // The allocation-free evaluation (gst_noalloc.hip): the scratch array's address

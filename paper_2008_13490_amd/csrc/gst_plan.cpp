@@ -2,6 +2,7 @@
 #include "gst_plan.h"
 
 #include <algorithm>
+#include <tuple>
 #include <cstring>
 #include <numeric>
 
@@ -550,6 +551,53 @@ bool build_plan(const int64_t* off, const uint8_t* gates, int64_t S, int K, cons
     }
   }
   return true;
+}
+
+GradWork::GradWork(const HostPlan& P, int K) {
+  constexpr int64_t kChunk = 128;  // records per chunk (the kernel takes no more)
+  std::vector<int64_t> jumps;  // the tasks with steps inside (the plan pads with empty ones)
+  std::vector<uint8_t> inside((size_t)P.trunk_steps(), 0);
+  for (int64_t x = 0; x < (int64_t)P.fill_first.size(); ++x) {
+    if (P.fill_n[x] < 2) continue;
+    jumps.push_back(x);
+    for (int64_t j = 0; j < P.fill_n[x]; ++j) inside[P.fill_first[x] + j] = 1;
+  }
+  auto key = [&](int64_t x) { return std::make_tuple(-P.fill_n[x], P.fill_pattern[x], P.fill_gate3[x]); };
+  std::stable_sort(jumps.begin(), jumps.end(), [&](int64_t x, int64_t y) { return key(x) < key(y); });
+  for (size_t b = 0; b < jumps.size();) {
+    size_t e = b;
+    while (e < jumps.size() && e < b + 16 && key(jumps[e]) == key(jumps[b])) ++e;
+    for (size_t c = 0; c < 16; ++c) {
+      jump_first.push_back(b + c < e ? P.fill_first[jumps[b + c]] : -1);
+      jump_in.push_back(b + c < e ? P.fill_in[jumps[b + c]] : 0);
+    }
+    const int64_t x = jumps[b];
+    for (int32_t v : {P.fill_n[x], (int32_t)P.fill_pattern[x], (int32_t)P.fill_gate3[x], 0, -1, -1, -1, -1})
+      jump_meta.push_back(v);
+    b = e;
+  }
+  int64_t tiles = 0;
+  tile_ptr.push_back(0);
+  for (int k = 0; k < K; ++k) {
+    const int64_t r0 = (int64_t)rec_b.size();
+    for (int64_t r = P.rec_gate_ptr[k]; r < P.rec_gate_ptr[k + 1]; ++r) {
+      if (P.rec_b[r] < P.trunk_steps() && inside[P.rec_b[r]]) continue;
+      rec_b.push_back(P.rec_b[r]);
+      rec_f.push_back(P.rec_f[r]);
+    }
+    for (int64_t c = r0; c < (int64_t)rec_b.size(); c += kChunk) {
+      chunk_tile.push_back(tiles++);
+      chunk_beg.push_back(c);
+      chunk_end.push_back(std::min<int64_t>(c + kChunk, (int64_t)rec_b.size()));
+    }
+    for (size_t g = 0; g < jump_meta.size() / 8; ++g) {
+      int32_t* m = &jump_meta[8 * g];
+      const uint32_t pat = (uint32_t)m[1];
+      for (int ph = 0; ph < (int)(pat & 0xffu); ++ph)
+        if ((ph < 3 ? (int)((pat >> (8 * (ph + 1))) & 0xffu) : m[2]) == k) m[4 + ph] = (int32_t)tiles++;
+    }
+    tile_ptr.push_back(tiles);
+  }
 }
 
 }  // namespace gst

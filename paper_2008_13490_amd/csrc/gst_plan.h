@@ -135,4 +135,14 @@ struct PlanOptions {
 bool build_plan(const int64_t* offsets, const uint8_t* gates, int64_t S, int K, const PlanOptions& opt,
                 HostPlan* out);
 
+// The gradient's work of a sharing plan, for the device: the records of the
+// steps outside jumps in chunks of one gate, the jumps in groups of sixteen with
+// one pattern and length (the longest first), and every partial's tile, the
+// tiles of a gate consecutive.
+struct GradWork {
+  std::vector<int64_t> rec_b, rec_f, chunk_tile, chunk_beg, chunk_end, jump_first, jump_in, tile_ptr;
+  std::vector<int32_t> jump_meta;
+  GradWork(const HostPlan& P, int K);
+};
+
 }  // namespace gst

@@ -17,10 +17,11 @@
 //   trunk_bwd_kernel  reverse sweep of the trunks, adding the injected
 //                     adjoints; adjoints after each step go to the arena;
 //   grad_gemm_kernel  dG_k = sum over all steps with gate k of b f^T, as FP64
-//                     MFMA 16x16x4 rank-4 updates over the stored pairs.
+//                     MFMA 16x16x4 rank-4 updates: over the stored pairs, and
+//                     inside the jumps over adjoints made on the way.
 // The two chains (forward and reverse) are latency bound; the gradient GEMM
 // runs over all stored steps at once.  The records that only the gradient GEMM
-// reads (the items' states and adjoints, the states and adjoints filled inside
+// reads (the items' states and adjoints, the states filled inside
 // jumps) are stored non-temporally: written through to memory instead of
 // being held in the L2, whose write-back at the end of each kernel otherwise
 // lengthens the item and fill launches.
@@ -280,13 +281,7 @@ __device__ __forceinline__ FillTask fill_task_desc(const PlanArgs& a, int64_t gr
   t.v = 0.0;
   return t;
 }
-template <int D, bool REV>
-__device__ __forceinline__ void fill_task_start(const PlanArgs& a, FillTask& t, int i) {
-  const int c = i < D ? i : 0;
-  t.v = REV ? a.BA[(t.first + t.n - 1) * D + c] : a.FA[t.in * D + c];
-}
-
-template <int D, bool REV>
+template <int D>
 __device__ void run_fills(const PlanArgs& a, const Lds& s, int64_t blk, int64_t n_blk, FillTask t0);
 
 // Workgroups from a.item_blocks on run the forward fill tasks instead (they
@@ -326,7 +321,7 @@ __device__ __forceinline__ void item_body(const PlanArgs& a, int64_t blk, int64_
   if ((int)blk >= a.item_blocks && a.n_fill > 0) t0 = fill_task_desc(a, (blk - a.item_blocks) * WAVES + wave, team);
   stage_gateset<D>(s, a.G, a.E, a.rho, K, M);
   if ((int)blk >= a.item_blocks) {
-    run_fills<D, false>(a, s, blk - a.item_blocks, nblk - a.item_blocks, t0);
+    run_fills<D>(a, s, blk - a.item_blocks, nblk - a.item_blocks, t0);
     return;
   }
   const bool grad = a.want_grad != 0;
@@ -620,27 +615,25 @@ __global__ __launch_bounds__(64) void trunk_bwd_kernel(const PlanArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// fill tasks: the states (forward) or adjoints (reverse) inside one jump, one
-// task per 16-lane team, from the stored value at the jump's start (forward)
-// or end (reverse).  Step j of a task applies gate pattern[j % period].
+// fill tasks: the states inside one jump, one task per 16-lane team, from the
+// stored value at the jump's start.  Step j of a task applies gate
+// pattern[j % period].  (The adjoints inside the jumps go straight into the
+// gradient, see jump_grad.)
 // ---------------------------------------------------------------------------
 // Workgroup blk of n_blk runs groups blk * WAVES + wave, + n_blk * WAVES, ...;
 // `t0` is the first group's task, its descriptors already loaded.
-template <int D, bool REV>
+template <int D>
 __device__ void run_fills(const PlanArgs& a, const Lds& s, int64_t blk, int64_t n_blk, FillTask t0) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, team = lane >> 4;
-  const double* gl = (REV ? s.GTs : s.Gs) + i * ROW;
+  const double* gl = s.Gs + i * ROW;
   const int64_t n_groups = (a.n_fill + TPW - 1) / TPW;
   FillTask t = t0;
   for (int64_t grp = blk * WAVES + wave; grp < n_groups; grp += n_blk * WAVES) {
     if (grp != blk * WAVES + wave) t = fill_task_desc(a, grp, team);
-    fill_task_start<D, REV>(a, t, i);
+    t.v = a.FA[t.in * D + (i < D ? i : 0)];
     const bool has = grp * TPW + team < a.n_fill;
-    const int64_t first = t.first, in = t.in;
     const int n = has ? t.n : 1;
     const uint32_t pat = has ? t.pat : (t.pat & 0xffu);
-    const int g3 = t.g3;
-    (void)in;
     // the four tasks of a wave share their period (the plan groups them):
     // the pattern rows stay in registers and the phase is uniform
     const int per = __builtin_amdgcn_readfirstlane((int)(pat & 0xffu));
@@ -650,50 +643,24 @@ __device__ void run_fills(const PlanArgs& a, const Lds& s, int64_t blk, int64_t 
     Row16 R1 = R0, R2 = R0, R3 = R0;
     if (per > 1) R1 = load_row(gl + (int)((pat >> 16) & 0xffu) * GATE_STRIDE);
     if (per > 2) R2 = load_row(gl + (int)((pat >> 24) & 0xffu) * GATE_STRIDE);
-    if (per > 3) R3 = load_row(gl + g3 * GATE_STRIDE);
+    if (per > 3) R3 = load_row(gl + t.g3 * GATE_STRIDE);
     auto apply = [&](double v, int ph) {
       if (ph == 0) return dot16(v, R0);
       if (ph == 1) return dot16(v, R1);
       if (ph == 2) return dot16(v, R2);
       return dot16(v, R3);
     };
-    if (!REV) {
-      // states after steps 0 .. n-2 (the one after step n-1 is the jump's);
-      // step j applies pattern gate j % per
-      double f = i < D ? t.v : 0.0;
-      double* o = a.FA + (1 + first) * D + i;
-      int ph = 0;
-      for (int j = 0; j + 1 < nw; ++j) {
-        f = apply(f, ph);
-        if (st && j + 1 < n) __builtin_nontemporal_store(f, &o[(int64_t)j * D]);
-        ph = ph + 1 == per ? 0 : ph + 1;
-      }
-    } else {
-      // adjoints after steps n-2 .. 0, from the one after step n-1
-      double b = st ? t.v : 0.0;
-      double* o = a.BA + first * D + i;
-      int ph = (nw - 1) % per;
-      for (int j = nw - 1; j >= 1; --j) {
-        const double nb = apply(b, ph);
-        if (j < n) {
-          b = nb;
-          if (st) __builtin_nontemporal_store(b, &o[(int64_t)(j - 1) * D]);
-        }
-        ph = ph == 0 ? per - 1 : ph - 1;
-      }
+    // states after steps 0 .. n-2 (the one after step n-1 is the jump's);
+    // step j applies pattern gate j % per
+    double f = i < D ? t.v : 0.0;
+    double* o = a.FA + (1 + t.first) * D + i;
+    int ph = 0;
+    for (int j = 0; j + 1 < nw; ++j) {
+      f = apply(f, ph);
+      if (st && j + 1 < n) __builtin_nontemporal_store(f, &o[(int64_t)j * D]);
+      ph = ph + 1 == per ? 0 : ph + 1;
     }
   }
-}
-
-// reverse fill tasks (the forward ones run in the item kernel's extra workgroups)
-template <int D>
-__global__ __launch_bounds__(256) void fill_rev_kernel(const PlanArgs a) {
-  extern __shared__ double lds_raw[];
-  const Lds s = carve(lds_raw, a.K);
-  // the first group's descriptors load while the gate set is staged
-  const FillTask t0 = fill_task_desc(a, (int64_t)blockIdx.x * WAVES + (threadIdx.x >> 6), (threadIdx.x & 63) >> 4);
-  stage_gateset<D, 256, STAGE_GT>(s, a.G, a.E, a.rho, a.K, a.M);
-  run_fills<D, true>(a, s, blockIdx.x, gridDim.x, t0);
 }
 
 // One wave per injection slot: its sources are consecutive rows of the
@@ -727,15 +694,117 @@ __global__ __launch_bounds__(64) void inject_kernel(const InjectLaunch a) {
 }
 
 // ---------------------------------------------------------------------------
-// gradient GEMM over the stored (adjoint, state) pairs, one chunk of records
-// of one gate per workgroup; four records per MFMA 16x16x4
+// the gate gradient, one launch of two kinds of workgroups
 // ---------------------------------------------------------------------------
+// A jump group: sixteen jumps of one pattern and length, a wave's columns.  The
+// adjoints are a 16 x 16 block in the output layout of the MFMA 16x16x4 (register
+// v of lane 16 r4 + c: row 4v + r4 of jump c), which is the layout of its B operand:
+// a step back is b <- G^T b, D/4 dependent MFMAs on registers alone.  For
+// dG += b f^T the adjoints change layout through the wave's LDS tile (rows 17
+// doubles apart: no bank conflicts) while the step's MFMAs run; the states before the step
+// are read as stored, four 128-byte rows per load, six or eight steps ahead.
+// Sixteen jumps' step costs 8 MFMAs, 512 cycles.  Run by 16-lane teams that stored
+// the adjoints for the gradient GEMM to read again, the reverse fill and the
+// gradient of sixteen fits of 13,189 sequences (843,000 steps in jumps of 1.24 M)
+// took 31 and 74 us, now together 58, where the rows' bytes would take 44; those
+// of one such fit 8 and 9 us, now 11.
+// U steps' states are on their way (n is a multiple of U); absent columns have
+// adjoints of zero and read rows of zeros, so that no step selects anything.
+typedef const __attribute__((address_space(1))) double* gdoubles;
+constexpr int JT = 17;  // row stride (doubles) of a wave's tile
+template <int D, int PER, int U>
+__device__ __forceinline__ void jump_grad(const GemmLaunch& a, int64_t grp, double* T) {
+  static_assert(U % PER == 0, "whole patterns");
+  constexpr int KK = D / 4;
+  const int lane = threadIdx.x & 63, c = lane & 15, r4 = lane >> 4;
+  const int cd = c < D ? c : 0;
+  const int32_t* meta = a.jump_meta + grp * 8;
+  int64_t first = a.jump_first[grp * 16 + c], in = a.jump_in[grp * 16 + c];
+  const int n = uniform(meta[0]);
+  const uint32_t pat = (uint32_t)uniform(meta[1]);
+  const int g3 = uniform(meta[2]);
+  const bool has = first >= 0;
+  const int64_t first0 = __shfl(first, 0);
+  double b[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    const double v = as_global(a.BA)[((has ? first : first0) + n - 1) * D + 4 * kk + r4];
+    b[kk] = has ? v : 0.0;
+  }
+  first = has ? first : a.zero_row;
+  in = has ? in : a.zero_row;
+  // component c of the state before step x of jump 4q + r4: f_at[q] at step x = U - 1
+  // of the block under way, f_in[q] at the jump's first step
+  gdoubles f_at[4], f_in[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    f_at[q] = as_global(a.FA) + (__shfl(first, 4 * q + r4) + n - 1) * D + cd;
+    f_in[q] = as_global(a.FA) + __shfl(in, 4 * q + r4) * D + cd;
+  }
+  double f[U][4];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[u][q] = (u == U - 1 && n == U ? f_in[q] : f_at[q] - u * D)[0];
+  // G^T of the pattern's gates as A operands: element (c, 4kk + r4)
+  double at[PER][KK];
+#pragma unroll
+  for (int ph = 0; ph < PER; ++ph) {
+    const int k = ph < 3 ? (int)((pat >> (8 * (ph + 1))) & 0xffu) : g3;
+    const auto* g = as_global(a.G + (int64_t)k * D * D);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      const double v = g[(4 * kk + r4) * D + cd];
+      at[ph][kk] = c < D ? v : 0.0;
+    }
+  }
+  d4 dG[PER];
+#pragma unroll
+  for (int ph = 0; ph < PER; ++ph) dG[ph] = d4{0.0, 0.0, 0.0, 0.0};
+  double* put = T + c * JT + r4;
+  const double* get = T + r4 * JT + cd;
+  for (int j = n; j > 0; j -= U) {
+    const int next = j - U;  // steps of the blocks after this one
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f_at[q] -= next > 0 ? U * D : 0;  // (the last block reads its own again)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int ph = PER - 1 - u % PER;
+      wave_sync();  // the last step's tile has been read
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) put[4 * kk] = b[kk];
+      wave_sync();
+      double bt[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bt[q] = get[4 * q * JT];
+      d4 nb = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) nb = __builtin_amdgcn_mfma_f64_16x16x4f64(at[ph][kk], b[kk], nb, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        // (D = 4: rows and columns past the fourth are not stored)
+        dG[ph] = __builtin_amdgcn_mfma_f64_16x16x4f64(bt[q], f[u][q], dG[ph], 0, 0, 0);
+      }
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) b[kk] = nb[kk];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) f[u][q] = (u == U - 1 && next == U ? f_in[q] : f_at[q] - u * D)[0];
+    }
+  }
+#pragma unroll
+  for (int ph = 0; ph < PER; ++ph) {
+    double* out = a.tiles + (int64_t)uniform(meta[4 + ph]) * D * D;
+#pragma unroll
+    for (int v = 0; v < KK; ++v)
+      if (c < D) out[(4 * v + r4) * D + c] = dG[ph][v];
+  }
+}
+
+// A chunk of records, of one gate: four records per MFMA 16x16x4.
 template <int D>
-__device__ __forceinline__ void grad_gemm_body(const GemmLaunch& a, int64_t c) {
-  __shared__ double tile[WAVES][256];
+__device__ __forceinline__ void record_grad(const GemmLaunch& a, int64_t c, double (*tile)[16 * JT]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, z = lane >> 4;
-  const int64_t r0 = a.chunk_beg[c], r1 = a.chunk_end[c];
-  const int k = (int)a.chunk_gate[c];
+  const int64_t r0 = a.chunk_beg[c], r1 = a.chunk_end[c], out = a.chunk_tile[c];
   d4 acc = {0.0, 0.0, 0.0, 0.0};
   // records r0 + 16*u + 4*wave + z, u = 0..7 (chunks hold at most 128 records)
   int64_t rb[8], rf[8];
@@ -758,13 +827,38 @@ __device__ __forceinline__ void grad_gemm_body(const GemmLaunch& a, int64_t c) {
   __syncthreads();
   if (tid < D * D) {
     const int r = tid / D, cc = tid % D;
-    a.tiles[c * D * D + tid] =
+    a.tiles[out * D * D + tid] =
         (tile[0][r * 16 + cc] + tile[1][r * 16 + cc]) + (tile[2][r * 16 + cc] + tile[3][r * 16 + cc]);
   }
 }
 
+// Workgroup blk: four jump groups (the longer work, first), then a record chunk.
 template <int D>
-__global__ __launch_bounds__(256) void grad_gemm_kernel(const GemmLaunch a) {
+__device__ __forceinline__ void grad_gemm_body(const GemmLaunch& a, int64_t blk) {
+  __shared__ double tile[WAVES][16 * JT];
+  const int64_t jump_blocks = (a.n_jump_groups + WAVES - 1) / WAVES;
+  if (blk >= jump_blocks) {
+    record_grad<D>(a, blk - jump_blocks, tile);
+    return;
+  }
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t grp = blk * WAVES + wave;
+  if (grp >= a.n_jump_groups) return;
+  // jumps of few steps (at most four patterns) have no states to read ahead of
+  const int n = uniform(a.jump_meta[grp * 8]), per = uniform(a.jump_meta[grp * 8 + 1]) & 0xff;
+  double* T = tile[wave];
+  if (per == 1)
+    n % 8 == 0 ? jump_grad<D, 1, 8>(a, grp, T) : jump_grad<D, 1, 1>(a, grp, T);
+  else if (per == 2)
+    n % 8 == 0 ? jump_grad<D, 2, 8>(a, grp, T) : jump_grad<D, 2, 2>(a, grp, T);
+  else if (per == 3)
+    n % 6 == 0 ? jump_grad<D, 3, 6>(a, grp, T) : jump_grad<D, 3, 3>(a, grp, T);
+  else
+    n % 8 == 0 ? jump_grad<D, 4, 8>(a, grp, T) : jump_grad<D, 4, 4>(a, grp, T);
+}
+
+template <int D>
+__global__ __launch_bounds__(256, 2) void grad_gemm_kernel(const GemmLaunch a) {
   grad_gemm_body<D>(a, blockIdx.x);
 }
 
@@ -912,20 +1006,9 @@ __global__ __launch_bounds__(64) void inject_batch(const PlanBatch b, int level)
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void fill_rev_batch(const PlanBatch b) {
-  const PlanArgs a = b.args[blockIdx.y];
-  if (!a.want_grad || a.n_fill <= 0 || (int64_t)blockIdx.x >= a.fill_blocks) return;
-  extern __shared__ double lds_raw[];
-  const Lds s = carve(lds_raw, a.K);
-  const FillTask t0 = fill_task_desc(a, (int64_t)blockIdx.x * WAVES + (threadIdx.x >> 6), (threadIdx.x & 63) >> 4);
-  stage_gateset<D, 256, STAGE_GT>(s, a.G, a.E, a.rho, a.K, a.M);
-  run_fills<D, true>(a, s, blockIdx.x, a.fill_blocks, t0);
-}
-
-template <int D>
-__global__ __launch_bounds__(256) void grad_gemm_batch(const PlanBatch b) {
+__global__ __launch_bounds__(256, 2) void grad_gemm_batch(const PlanBatch b) {
   const GemmLaunch g = b.gemm[blockIdx.y];
-  if ((int64_t)blockIdx.x >= g.n_chunks) return;
+  if ((int64_t)blockIdx.x >= grad_blocks_for(g)) return;
   grad_gemm_body<D>(g, blockIdx.x);
 }
 
@@ -1012,19 +1095,6 @@ hipError_t launch_inject(const InjectLaunch& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_fill_rev(const PlanArgs& a, hipStream_t stream) {
-  if (a.n_fill <= 0) return hipSuccess;
-  const int blocks = fill_blocks_for(a.n_fill);
-  const size_t bytes = item_lds_bytes(a.K, a.M);
-  if (a.D == 16)
-    gst_launch(fill_rev_kernel<16>, dim3((unsigned)blocks), dim3(256), bytes, stream, a);
-  else if (a.D == 4)
-    gst_launch(fill_rev_kernel<4>, dim3((unsigned)blocks), dim3(256), bytes, stream, a);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
 hipError_t launch_reduce_plan(const PlanReduce& a, hipStream_t stream) {
   if (a.P <= 0 || a.n_part < 1 || a.n_part > 64 || a.K < 0 || a.K > 8) return hipErrorInvalidValue;
   const unsigned xb = (unsigned)((a.P + 63) / 64);
@@ -1034,11 +1104,12 @@ hipError_t launch_reduce_plan(const PlanReduce& a, hipStream_t stream) {
 }
 
 hipError_t launch_grad_gemm(const GemmLaunch& a, hipStream_t stream) {
-  if (a.n_chunks <= 0) return hipSuccess;
+  const int64_t blocks = grad_blocks_for(a);
+  if (blocks <= 0) return hipSuccess;
   if (a.D == 16)
-    gst_launch(grad_gemm_kernel<16>, dim3((unsigned)a.n_chunks), dim3(256), 0, stream, a);
+    gst_launch(grad_gemm_kernel<16>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
   else if (a.D == 4)
-    gst_launch(grad_gemm_kernel<4>, dim3((unsigned)a.n_chunks), dim3(256), 0, stream, a);
+    gst_launch(grad_gemm_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -1080,14 +1151,6 @@ hipError_t launch_trunk_bwd_batch(const PlanBatch& b, int D, int n, int level, i
   if (n <= 0 || grid_x <= 0) return hipSuccess;
   GST_BATCH_D(trunk_bwd_batch, dim3((unsigned)grid_x, (unsigned)n), dim3(64), trunk_lds_bytes(K_max, jl_max), stream,
               b, level);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_rev_batch(const PlanBatch& b, int D, int n, int grid_x, int K_max, int M_max,
-                                 hipStream_t stream) {
-  if (n <= 0 || grid_x <= 0) return hipSuccess;
-  GST_BATCH_D(fill_rev_batch, dim3((unsigned)grid_x, (unsigned)n), dim3(256), item_lds_bytes(K_max, M_max), stream,
-              b);
   return hipGetLastError();
 }
 
