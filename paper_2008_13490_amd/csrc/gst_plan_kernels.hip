@@ -232,16 +232,16 @@ __device__ __forceinline__ void trunk_fwd_body(const PlanArgs& a, int64_t t_begi
       const uint32_t dc = dl;
       if (ob + OPW < o1) dl = op_descs(a, ob + OPW, o1, lane);  // the next batch, during this chain
       // three ops per iteration, the rows of the next two ops in flight
-      auto rows = [&](int x) { return load_row(op_row(s.Gs, js, lane_u32(dc, x < n ? x : n - 1), i)); };
-      auto step = [&](const Row16& R, int x) {
-        f = dot16(f, R);
+      auto rows = [&](int x) { return load_row_d<D>(op_row(s.Gs, js, lane_u32(dc, x < n ? x : n - 1), i)); };
+      auto step = [&](const RowD<D>& R, int x) {
+        f = dot_row(f, R);
         pos += (lane_u32(dc, x) >> 8) & 0xffu;
         if (st) out[(pos - 1) * D] = f;
       };
-      Row16 R0 = rows(0), R1 = rows(1);
+      RowD<D> R0 = rows(0), R1 = rows(1);
       int x = 0;
       for (; x + 3 <= n; x += 3) {
-        const Row16 R2 = rows(x + 2);
+        const RowD<D> R2 = rows(x + 2);
         step(R0, x);
         R0 = rows(x + 3);
         step(R1, x + 1);
@@ -394,7 +394,7 @@ __device__ __forceinline__ void item_body(const PlanArgs& a, int64_t blk, int64_
     const int x = t0 + R;                                                \
     const int k = bcast_i32<R>(kv);                                      \
     if (grad && x < L && i < D) __builtin_nontemporal_store(f, &fa[(int64_t)x * D + i]);            \
-    const double fn = dot16(f, load_row(s.Gs + k * GATE_STRIDE + i * ROW)); \
+    const double fn = dot_row(f, load_row_d<D>(s.Gs + k * GATE_STRIDE + i * ROW)); \
     f = x < L ? fn : f;                                                  \
   }
       GST_IF(0) GST_IF(1) GST_IF(2) GST_IF(3) GST_IF(4) GST_IF(5) GST_IF(6) GST_IF(7)
@@ -403,7 +403,7 @@ __device__ __forceinline__ void item_body(const PlanArgs& a, int64_t blk, int64_
     }
 
     // ---- readout, objective, seeds ----
-    const double p = dot16(f, load_row(s.Es + i * ROW));
+    const double p = dot_row(f, load_row_d<D>(s.Es + i * ROW));
     double dp = 0.0;
     if (has && i < M) {
       const int64_t o = seq * M + i;
@@ -441,7 +441,7 @@ __device__ __forceinline__ void item_body(const PlanArgs& a, int64_t blk, int64_
     const int x = t0 + R;                                                 \
     const int k = bcast_i32<R>(kv);                                       \
     if (x < L && i < D) __builtin_nontemporal_store(b, &ba[(int64_t)x * D + i]);                  \
-    const double bn = dot16(b, load_row(s.GTs + k * GATE_STRIDE + i * ROW)); \
+    const double bn = dot_row(b, load_row_d<D>(s.GTs + k * GATE_STRIDE + i * ROW)); \
     b = x < L ? bn : b;                                                   \
   }
         GST_IB(15) GST_IB(14) GST_IB(13) GST_IB(12) GST_IB(11) GST_IB(10) GST_IB(9) GST_IB(8)
@@ -580,17 +580,17 @@ __device__ __forceinline__ void trunk_bwd_body(const PlanArgs& a, int64_t t_begi
         }
       }
       // three ops per iteration (descending), the rows of the next two in flight
-      auto rows = [&](int x) { return load_row(op_row(s.GTs, js, lane_u32(dc, x >= 0 ? x : 0), i)); };
-      auto step = [&](const Row16& R, int x) {
+      auto rows = [&](int x) { return load_row_d<D>(op_row(s.GTs, js, lane_u32(dc, x >= 0 ? x : 0), i)); };
+      auto step = [&](const RowD<D>& R, int x) {
         b += inj_st[x * 16 + i];
         if (st) ba[(pos - 1) * D] = b;
-        b = dot16(b, R);
+        b = dot_row(b, R);
         pos -= (lane_u32(dc, x) >> 8) & 0xffu;
       };
-      Row16 R0 = rows(n - 1), R1 = rows(n - 2);
+      RowD<D> R0 = rows(n - 1), R1 = rows(n - 2);
       int x = n - 1;
       for (; x >= 2; x -= 3) {
-        const Row16 R2 = rows(x - 2);
+        const RowD<D> R2 = rows(x - 2);
         step(R0, x);
         R0 = rows(x - 3);
         step(R1, x - 1);
@@ -639,16 +639,16 @@ __device__ void run_fills(const PlanArgs& a, const Lds& s, int64_t blk, int64_t 
     const int per = __builtin_amdgcn_readfirstlane((int)(pat & 0xffu));
     const int nw = wave_max4(n);
     const bool st = has && i < D;
-    const Row16 R0 = load_row(gl + (int)((pat >> 8) & 0xffu) * GATE_STRIDE);
-    Row16 R1 = R0, R2 = R0, R3 = R0;
-    if (per > 1) R1 = load_row(gl + (int)((pat >> 16) & 0xffu) * GATE_STRIDE);
-    if (per > 2) R2 = load_row(gl + (int)((pat >> 24) & 0xffu) * GATE_STRIDE);
-    if (per > 3) R3 = load_row(gl + t.g3 * GATE_STRIDE);
+    const RowD<D> R0 = load_row_d<D>(gl + (int)((pat >> 8) & 0xffu) * GATE_STRIDE);
+    RowD<D> R1 = R0, R2 = R0, R3 = R0;
+    if (per > 1) R1 = load_row_d<D>(gl + (int)((pat >> 16) & 0xffu) * GATE_STRIDE);
+    if (per > 2) R2 = load_row_d<D>(gl + (int)((pat >> 24) & 0xffu) * GATE_STRIDE);
+    if (per > 3) R3 = load_row_d<D>(gl + t.g3 * GATE_STRIDE);
     auto apply = [&](double v, int ph) {
-      if (ph == 0) return dot16(v, R0);
-      if (ph == 1) return dot16(v, R1);
-      if (ph == 2) return dot16(v, R2);
-      return dot16(v, R3);
+      if (ph == 0) return dot_row(v, R0);
+      if (ph == 1) return dot_row(v, R1);
+      if (ph == 2) return dot_row(v, R2);
+      return dot_row(v, R3);
     };
     // states after steps 0 .. n-2 (the one after step n-1 is the jump's);
     // step j applies pattern gate j % per

@@ -40,14 +40,14 @@ __global__ __launch_bounds__(64) void predict_chain_kernel(const PredictLaunch a
     double f = s.rho[i];
     for (int x = 0; x < (int)L; ++x) {
       const int k = __builtin_amdgcn_readlane(kw, x);
-      f = dot16(f, load_row(s.Gs + k * GATE_STRIDE + i * ROW));
+      f = dot_row(f, load_row_d<D>(s.Gs + k * GATE_STRIDE + i * ROW));
     }
     build_jumps(js, s.Gs, 1u | (uint32_t)g << 8, 0, a.levels, false, lane);
-    const Row16 RJ = load_row(js + (a.levels - 1) * GATE_STRIDE + i * ROW);
+    const RowD<D> RJ = load_row_d<D>(js + (a.levels - 1) * GATE_STRIDE + i * ROW);
     double* v = a.V + (int64_t)pair * a.Q * D;
     if (lane < D) v[i] = f;
     for (int q = 1; q < a.Q; ++q) {
-      f = dot16(f, RJ);
+      f = dot_row(f, RJ);
       if (lane < D) v[(int64_t)q * D + i] = f;
     }
     wave_sync();  // js is rebuilt for the next pair
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void predict_fill_kernel(const PredictLaunch a
   const Lds s = carve(lds_raw, K);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, team = lane >> 4;
   stage_gateset<D, 256, STAGE_G | STAGE_E>(s, a.G, a.E, a.rho, K, M);
-  const Row16 ER = load_row(s.Es + i * ROW);
+  const RowD<D> ER = load_row_d<D>(s.Es + i * ROW);
   const int64_t n_tasks = (int64_t)a.n_pairs * a.Q;
   const int64_t n_groups = (n_tasks + TPW - 1) / TPW;
   const int B = 1 << (a.levels - 1);
@@ -73,14 +73,14 @@ __global__ __launch_bounds__(256) void predict_fill_kernel(const PredictLaunch a
     const int64_t pair = has ? t / a.Q : 0;
     const int q = has ? (int)(t % a.Q) : 0;
     const int g = a.gate_of[pair % a.n_gates];
-    const Row16 R = load_row(s.Gs + g * GATE_STRIDE + i * ROW);
+    const RowD<D> R = load_row_d<D>(s.Gs + g * GATE_STRIDE + i * ROW);
     double f = i < D ? a.V[(pair * a.Q + q) * D + i] : 0.0;
     double* out = a.probs + pair * (int64_t)(a.r_max + 1) * M;
     for (int k = 0; k < B; ++k) {
       const int r = q * B + k;
-      const double pm = dot16(f, ER);
+      const double pm = dot_row(f, ER);
       if (has && i < M && r <= a.r_max) out[(int64_t)r * M + i] = pm;
-      if (k + 1 < B) f = dot16(f, R);
+      if (k + 1 < B) f = dot_row(f, R);
     }
   }
 }

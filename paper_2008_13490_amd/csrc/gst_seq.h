@@ -116,9 +116,9 @@ __device__ __forceinline__ void add_pairs(const Pairs& st, int gate, int K, d4 (
 
 // Lane i's row (of the gates or of their transposes, `base` at row i of the
 // first) of the gate whose byte offset lane R of the DPP row holds.
-template <int R>
-__device__ __forceinline__ Row16 step_row(const double* base, int koff) {
-  return load_row(reinterpret_cast<const double*>(reinterpret_cast<const char*>(base) + bcast_i32<R>(koff)));
+template <int D, int R>
+__device__ __forceinline__ RowD<D> step_row(const double* base, int koff) {
+  return load_row_d<D>(reinterpret_cast<const double*>(reinterpret_cast<const char*>(base) + bcast_i32<R>(koff)));
 }
 
 // One sequence per row: `seq` (its row of the counts, weights and
@@ -149,19 +149,19 @@ __device__ __forceinline__ void seq_group(const SeqArgs& a, const Lds& s, Pairs*
       kv = 0;
     }
     const int koff = kv * KB;
-    Row16 ra, rb;
-    if (PRE) ra = step_row<0>(grow0, koff);
+    RowD<D> ra, rb;
+    if (PRE) ra = step_row<D, 0>(grow0, koff);
     if (t0 + 16 <= Lmin) {
 #define GST_FWD_STEP(R, ROW_)                                        \
   {                                                                  \
     if (a.grad && ((R) % C) == 0) a.ck[((t0 + R) / C) * 16 + i] = f;   \
-    f = dot16(f, ROW_);                                              \
+    f = dot_row(f, ROW_);                                              \
   }
 #define GST_FWD_TWO(R)                                                           \
-  if (PRE) rb = step_row<R + 1>(grow0, koff); else ra = step_row<R>(grow0, koff); \
+  if (PRE) rb = step_row<D, R + 1>(grow0, koff); else ra = step_row<D, R>(grow0, koff); \
   GST_FWD_STEP(R, ra)                                                            \
-  if (PRE && R < 14) ra = step_row<(R + 2) & 15>(grow0, koff);                   \
-  if (!PRE) rb = step_row<R + 1>(grow0, koff);                                   \
+  if (PRE && R < 14) ra = step_row<D, (R + 2) & 15>(grow0, koff);                   \
+  if (!PRE) rb = step_row<D, R + 1>(grow0, koff);                                   \
   GST_FWD_STEP(R + 1, rb)
       GST_FWD_TWO(0) GST_FWD_TWO(2) GST_FWD_TWO(4) GST_FWD_TWO(6)
       GST_FWD_TWO(8) GST_FWD_TWO(10) GST_FWD_TWO(12) GST_FWD_TWO(14)
@@ -172,7 +172,7 @@ __device__ __forceinline__ void seq_group(const SeqArgs& a, const Lds& s, Pairs*
   {                                                                      \
     const int t = t0 + R;                                                \
     if (a.grad && ((R) % C) == 0 && t < L) a.ck[(t / C) * 16 + i] = f;     \
-    const double fn = dot16(f, ROW_);                                    \
+    const double fn = dot_row(f, ROW_);                                    \
     f = t < L ? fn : f;                                                  \
   }
     for (;;) {
@@ -256,33 +256,33 @@ __device__ __forceinline__ void seq_group(const SeqArgs& a, const Lds& s, Pairs*
       kv_nx = *(kv_in ? word + (c - 1) * C + i : a.base);
       ck_nx = *(seg ? a.ck + (c - 1) * 16 + i : a.ck);
     }
-    Row16 ra, rb;
-    if (PRE) ra = step_row<0>(grow0, koff);
+    RowD<D> ra, rb;
+    if (PRE) ra = step_row<D, 0>(grow0, koff);
 #define GST_REC_TWO(R)                                                           \
-  if (PRE) rb = step_row<R + 1>(grow0, koff); else ra = step_row<R>(grow0, koff); \
-  fs[R + 1] = dot16(fs[R], ra);                                                  \
-  if (PRE) ra = step_row<R + 2>(grow0, koff); else rb = step_row<R + 1>(grow0, koff); \
-  fs[R + 2] = dot16(fs[R + 1], rb);
+  if (PRE) rb = step_row<D, R + 1>(grow0, koff); else ra = step_row<D, R>(grow0, koff); \
+  fs[R + 1] = dot_row(fs[R], ra);                                                  \
+  if (PRE) ra = step_row<D, R + 2>(grow0, koff); else rb = step_row<D, R + 1>(grow0, koff); \
+  fs[R + 2] = dot_row(fs[R + 1], rb);
     GST_REC_TWO(0) GST_REC_TWO(2) GST_REC_TWO(4)
 #undef GST_REC_TWO
-    if (PRE) rb = step_row<7>(gtrow0, koff); else ra = step_row<6>(grow0, koff);
-    fs[7] = dot16(fs[6], ra);
+    if (PRE) rb = step_row<D, 7>(gtrow0, koff); else ra = step_row<D, 6>(grow0, koff);
+    fs[7] = dot_row(fs[6], ra);
     const bool full = base + C <= Lmin;
 #define GST_BWD(R, ROW_)                                     \
   {                                                          \
     st->b[((R) % HALF) * TPW + team][i] = b;                   \
     st->f[((R) % HALF) * TPW + team][i] = fs[R];               \
-    const double bn = dot16(b, ROW_);                        \
+    const double bn = dot_row(b, ROW_);                        \
     if (full)                                                \
       b = bn;                                                \
     else                                                     \
       b = act && base + R < L ? bn : b;                      \
   }
 #define GST_BWD_TWO(R)                                                              \
-  if (PRE) ra = step_row<R - 1>(gtrow0, koff); else rb = step_row<R>(gtrow0, koff);  \
+  if (PRE) ra = step_row<D, R - 1>(gtrow0, koff); else rb = step_row<D, R>(gtrow0, koff);  \
   GST_BWD(R, rb)                                                                    \
-  if (PRE && R > 1) rb = step_row<(R - 2) & 15>(gtrow0, koff);                      \
-  if (!PRE) ra = step_row<R - 1>(gtrow0, koff);                                     \
+  if (PRE && R > 1) rb = step_row<D, (R - 2) & 15>(gtrow0, koff);                      \
+  if (!PRE) ra = step_row<D, R - 1>(gtrow0, koff);                                     \
   GST_BWD(R - 1, ra)
 #define GST_PAIRS(H)                                                      \
   {                                                                       \
