@@ -34,6 +34,10 @@ namespace gst {
 namespace {
 
 constexpr int TAYLOR = 16;  // degree of the Taylor polynomial, for ||X|| <= 1/2
+// 1 / k (a division in each of the polynomial's steps costs 150 cycles)
+__constant__ const double kRecip[TAYLOR + 1] = {0.0,      1.0 / 1,  1.0 / 2,  1.0 / 3,  1.0 / 4,  1.0 / 5,
+                                                1.0 / 6,  1.0 / 7,  1.0 / 8,  1.0 / 9,  1.0 / 10, 1.0 / 11,
+                                                1.0 / 12, 1.0 / 13, 1.0 / 14, 1.0 / 15, 1.0 / 16};
 
 // ---------------------------------------------------------------------------
 // TP: affine maps, one thread per output entry
@@ -299,10 +303,22 @@ constexpr size_t GATE_LDS_DOUBLES = 4 * 256 + 16 + 8 * (size_t)GATE_STRIDE + 16;
 
 // T and h from the gate's parameters, C = T T^dagger, then L (and L^T) from the
 // structure tables.  All 256 threads; ends with a barrier.
+// The tables come from global memory before the first barrier, and the barriers
+// wait for LDS alone.
 template <int D>
 __device__ void build_generator(const ParamLaunch& a, const double* tg, const GateLds& s) {
   constexpr int m = D - 1;
   const int tid = threadIdx.x;
+  const int r = tid >> 4, c = tid & 15;
+  const int rt = r < D ? r : 0, ct = c < D ? c : 0;
+  // all table loads in flight together (z by j, then entry: coalesced)
+  double zr[D], zi[D];
+#pragma unroll
+  for (int j = 1; j < D; ++j) {
+    zr[j] = a.tzr[(size_t)j * D * D + rt * D + ct];
+    zi[j] = a.tzi[(size_t)j * D * D + rt * D + ct];
+  }
+  const double y = a.ty[rt * D + ct];
   {
     const int j = tid >> 4, k = tid & 15;
     double tr = 0.0, ti = 0.0;
@@ -319,7 +335,7 @@ __device__ void build_generator(const ParamLaunch& a, const double* tg, const Ga
     s.Ti[tid] = ti;
     if (tid < 16) s.hs[tid] = (tid >= 1 && tid < D) ? tg[tid - 1] : 0.0;
   }
-  __syncthreads();
+  lds_sync();
   {
     const int j = tid >> 4, k = tid & 15;
     double cr = 0.0, ci = 0.0;
@@ -336,20 +352,11 @@ __device__ void build_generator(const ParamLaunch& a, const double* tg, const Ga
     s.Cr[tid] = cr;
     s.Ci[tid] = ci;
   }
-  __syncthreads();
+  lds_sync();
   {
-    const int r = tid >> 4, c = tid & 15;
     double l = 0.0;
     if (r < D && c < D) {
       const int rc = r ^ c;
-      // all table loads in flight together (z by j, then entry: coalesced)
-      double zr[D], zi[D];
-#pragma unroll
-      for (int j = 1; j < D; ++j) {
-        zr[j] = a.tzr[(size_t)j * D * D + r * D + c];
-        zi[j] = a.tzi[(size_t)j * D * D + r * D + c];
-      }
-      const double y = a.ty[r * D + c];
       if (rc) l = s.hs[rc] * y;
       // the term j = r^c has a zero coefficient (k = 0): it adds exact zeros
 #pragma unroll
@@ -368,7 +375,7 @@ __device__ void build_generator(const ParamLaunch& a, const double* tg, const Ga
       s.LT[r * ROW + 16 + c] = 0.0;
     }
   }
-  __syncthreads();
+  lds_sync();
 }
 
 // Register result of A B (16 x 16, LDS, stride ROW) on the matrix cores: lane l
@@ -440,6 +447,14 @@ __device__ inline void store_frag(double* C, const Frag& f, int lane) {
   for (int v = 0; v < 4; ++v) C[(4 * v + t) * ROW + i] = f.v[v];
 }
 
+// x of the lane eight below in the row of sixteen, zero in its first eight
+__device__ inline double row_shr8(double x) {
+  const long long u = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, 0x118, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), 0x118, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(unsigned)lo | ((long long)hi << 32));
+}
+
 __device__ inline Frag identity_frag(int lane) {
   const int i = lane & 15, t = lane >> 4;
   Frag f;
@@ -457,7 +472,7 @@ __device__ Frag expm_wave(const double* L, double* W, int lane) {
   const Frag X = load_left(L, ldexp(1.0, -sc), lane);
   Frag P = identity_frag(lane);
   for (int k = TAYLOR; k >= 1; --k) {
-    const double rk = 1.0 / (double)k;  // uniform: off the chain of dependent products
+    const double rk = kRecip[k];
     const d4 q = mfma_left(X, P, d4{0.0, 0.0, 0.0, 0.0});
 #pragma unroll
     for (int v = 0; v < 4; ++v) P.v[v] = fma(q[v], rk, 4 * v + t == i ? 1.0 : 0.0);
@@ -484,15 +499,17 @@ __global__ __launch_bounds__(256) void cptp_forward_kernel(const ParamLaunch a) 
   }
   const int g = blockIdx.x;
   const GateLds s = carve_gate(lds_raw);
+  const int tr = (tid >> 4) % D, tc = (tid & 15) % D;
+  const double target = a.targets[((int64_t)g * D + tr) * D + tc];
   build_generator<D>(a, gth + (int64_t)g * D * (D - 1), s);
   // target into W[3] (zero-padded)
   double* G0 = s.W[3];
   {
     const int r = tid >> 4, c = tid & 15;
-    G0[r * ROW + c] = (r < D && c < D) ? a.targets[((int64_t)g * D + r) * D + c] : 0.0;
+    G0[r * ROW + c] = (r < D && c < D) ? target : 0.0;
     if (c < ROW - 16) G0[r * ROW + 16 + c] = 0.0;
   }
-  __syncthreads();
+  lds_sync();
   if (wave == 0) {
     const Frag Ex = expm_wave(s.L, s.W[0], lane);
     store_frag(s.W[1], Ex, lane);
@@ -519,88 +536,108 @@ __global__ __launch_bounds__(256) void cptp_backward_kernel(const ParamLaunch a)
   }
   const int g = blockIdx.x;
   const GateLds s = carve_gate(lds_raw);
+  constexpr int m = D - 1;
+  const int j = tid >> 4, k = tid & 15;
+  const double target = a.targets[((int64_t)g * D + j % D) * D + k % D];
+  const double grad = gg[((int64_t)g * D + j % D) * D + k % D];
+  // the tables of the last steps: y of label tid + 1, z of the pair (j, k)
+  const int jl = (j < m ? j : 0) + 1, kl = (k < m ? k : 0) + 1, hl = (tid < m ? tid : 0) + 1;
+  double y[D], zr[D], zi[D];
+#pragma unroll
+  for (int r = 0; r < D; ++r) {
+    const size_t x = (size_t)jl * D * D + r * D + (r ^ jl ^ kl);
+    zr[r] = a.tzr[x];
+    zi[r] = a.tzi[x];
+    y[r] = a.ty[r * D + (r ^ hl)];
+  }
   build_generator<D>(a, a.theta + g_off + (int64_t)g * D * (D - 1), s);
   // W[3] = dF/dG, W[4] = G0^T
   {
     const int r = tid >> 4, c = tid & 15;
     const bool in = r < D && c < D;
-    s.W[3][r * ROW + c] = in ? gg[((int64_t)g * D + r) * D + c] : 0.0;
-    s.W[4][c * ROW + r] = in ? a.targets[((int64_t)g * D + r) * D + c] : 0.0;
+    s.W[3][r * ROW + c] = in ? grad : 0.0;
+    s.W[4][c * ROW + r] = in ? target : 0.0;
     if (c < ROW - 16) {
       s.W[3][r * ROW + 16 + c] = 0.0;
       s.W[4][r * ROW + 16 + c] = 0.0;
     }
   }
-  __syncthreads();
-  if (wave == 0) {
-    const int i = lane & 15, t = lane >> 4;
+  lds_sync();
+  // exp of [[A, Xs], [0, A]], A = L^T / 2^s, by block Horner on [[P11, P12], [0, P11]]:
+  // wave h < 2 holds columns 8h .. 8h + 7 of P11 (lanes i < 8) and of P12 (the others)
+  // as one right operand, so that A times both is one product; P11 moves to the other
+  // half for Xs P11.  (One wave held both blocks whole, twelve MFMAs a step, not eight:
+  // the chain rule of six two-qubit gates took 16.6 us, now 14.5, of which 5.2 are the
+  // launch and what every workgroup waits for; unrolled loops are slower here, their
+  // instructions come from memory.)
+  {
+    const int i = lane & 15, t = lane >> 4, col = 8 * wave + (i & 7);
+    const bool low = i < 8;
     const int sc = scaling_of(s.L, lane);
     const double f = ldexp(1.0, -sc);
-    // X = dF/dG G0^T into W[5] (a left operand below)
-    store_acc(s.W[5], mm_acc(s.W[3], s.W[4], d4{0.0, 0.0, 0.0, 0.0}, lane), lane);
-    wave_sync();
-    const Frag A = load_left(s.LT, f, lane);   // L^T / 2^s
-    const Frag Xs = load_left(s.W[5], f, lane);
-    // block Horner: [[P11, P12], [0, P11]] <- I + [[A, Xs], [0, A]] [[P11, P12], [0, P11]] / k
-    Frag P11 = identity_frag(lane), P12;
+    if (wave == 0) store_acc(s.W[5], mm_acc(s.W[3], s.W[4], d4{0.0, 0.0, 0.0, 0.0}, lane), lane);  // dF/dG G0^T
+    lds_sync();
+    Frag P;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) P12.v[v] = 0.0;
-    for (int k = TAYLOR; k >= 1; --k) {
-      const double rk = 1.0 / (double)k;
-      const d4 q11 = mfma_left(A, P11, d4{0.0, 0.0, 0.0, 0.0});
-      const d4 q12 = mfma_left(Xs, P11, mfma_left(A, P12, d4{0.0, 0.0, 0.0, 0.0}));
+    for (int v = 0; v < 4; ++v) P.v[v] = low && 4 * v + t == col ? 1.0 : 0.0;
+    auto shifted = [&]() {  // lane i + 8 <- lane i of its row of sixteen, zero below
+      Frag q;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        P11.v[v] = fma(q11[v], rk, 4 * v + t == i ? 1.0 : 0.0);
-        P12.v[v] = q12[v] * rk;
+      for (int v = 0; v < 4; ++v) q.v[v] = row_shr8(P.v[v]);
+      return q;
+    };
+    if (wave < 2) {
+      const Frag A = load_left(s.LT, f, lane);
+      const Frag Xs = load_left(s.W[5], f, lane);
+      for (int n = TAYLOR; n >= 1; --n) {
+        const double rn = kRecip[n];
+        const Frag S = shifted();
+        const d4 q = mfma_left(Xs, S, mfma_left(A, P, d4{0.0, 0.0, 0.0, 0.0}));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) P.v[v] = fma(q[v], rn, low && 4 * v + t == col ? 1.0 : 0.0);
       }
     }
     // squarings: P11 <- P11 P11, P12 <- P11 P12 + P12 P11
     for (int e = 0; e < sc; ++e) {
-      store_frag(s.W[0], P11, lane);
-      store_frag(s.W[1], P12, lane);
-      wave_sync();
-      const Frag L11 = load_left(s.W[0], 1.0, lane), L12 = load_left(s.W[1], 1.0, lane);
-      wave_sync();
-      const d4 q11 = mfma_left(L11, P11, d4{0.0, 0.0, 0.0, 0.0});
-      const d4 q12 = mfma_left(L12, P11, mfma_left(L11, P12, d4{0.0, 0.0, 0.0, 0.0}));
+      if (wave < 2) {
+        double* W = low ? s.W[0] : s.W[1];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        P11.v[v] = q11[v];
-        P12.v[v] = q12[v];
+        for (int v = 0; v < 4; ++v) W[(4 * v + t) * ROW + col] = P.v[v];
+      }
+      lds_sync();
+      Frag L11, L12;
+      if (wave < 2) {
+        L11 = load_left(s.W[0], 1.0, lane);
+        L12 = load_left(s.W[1], 1.0, lane);
+      }
+      lds_sync();
+      if (wave < 2) {
+        const Frag S = shifted();
+        const d4 q = mfma_left(L12, S, mfma_left(L11, P, d4{0.0, 0.0, 0.0, 0.0}));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) P.v[v] = q[v];
       }
     }
-    // dF/dL into L's slot
-    store_frag(s.L, P12, lane);
+    // dF/dL = P12 into L's slot
+    if (wave < 2 && !low) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s.L[(4 * v + t) * ROW + col] = P.v[v];
+    }
   }
-  __syncthreads();
+  lds_sync();
   const double* Lb = s.L;
   double* out = a.grad_theta + g_off + (int64_t)g * D * (D - 1);
-  constexpr int m = D - 1;
   // dF/dh_k = sum_a dF/dL[a][a^k] y[a][a^k]
   if (tid < m) {
-    const int k = tid + 1;
-    double y[D];
-#pragma unroll
-    for (int r = 0; r < D; ++r) y[r] = a.ty[r * D + (r ^ k)];
     double v = 0.0;
 #pragma unroll
-    for (int r = 0; r < D; ++r) v = fma(Lb[r * ROW + (r ^ k)], y[r], v);
+    for (int r = 0; r < D; ++r) v = fma(Lb[r * ROW + (r ^ hl)], y[r], v);
     out[tid] = v;
   }
   // Chat_jk = sum_a dF/dL[a][b] z[j][a][b], b = a ^ j ^ k  (into Cr / Ci)
   {
-    const int j = tid >> 4, k = tid & 15;
     double cr = 0.0, ci = 0.0;
     if (j < m && k < m) {
-      const int jl = j + 1, kl = k + 1;
-      double zr[D], zi[D];
-#pragma unroll
-      for (int r = 0; r < D; ++r) {
-        const size_t x = (size_t)jl * D * D + r * D + (r ^ jl ^ kl);
-        zr[r] = a.tzr[x];
-        zi[r] = a.tzi[x];
-      }
 #pragma unroll
       for (int r = 0; r < D; ++r) {
         const double lb = Lb[r * ROW + (r ^ jl ^ kl)];
@@ -608,11 +645,11 @@ __global__ __launch_bounds__(256) void cptp_backward_kernel(const ParamLaunch a)
         ci = fma(lb, zi[r], ci);
       }
     }
-    __syncthreads();  // C is no longer needed
+    lds_sync();  // C is no longer needed
     s.Cr[tid] = cr;
     s.Ci[tid] = ci;
   }
-  __syncthreads();
+  lds_sync();
   // Gamma_jl = sum_{k >= l} (conj(Chat_jk) + Chat_kj) T_kl for l <= j
   {
     const int j = tid >> 4, l = tid & 15;
