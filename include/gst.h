@@ -253,7 +253,7 @@ int gst_set_plan_jump(gst_ctx* ctx, int reps);
  * block with (G_s)^32 (built per call by repeated squaring) and every block then
  * takes single steps, so the probabilities for r < 32 equal the plain evaluation of
  * the word bit for bit and later ones agree to rounding.  The host arrays are read
- * before the call returns (copied into pinned staging memory); the evaluation is
+ * before the call returns (copied); the evaluation is
  * stream-ordered on the context's stream and the call does not wait for it.  The
  * context's workspace holds the block-start states until the next call.  GST_EINVAL for
  * three qubits, a word longer than 64 gates, a gate index out of range,

@@ -1367,20 +1367,31 @@ int gst_predict(gst_ctx* ctx, const gst_gateset* theta, int n_prep, const int64_
   const int B = 1 << (levels - 1);
   const int Q = (r_max + 1 + B - 1) / B;
   const int n_pairs = n_prep * n_gates;
+  // the words travel in the kernels' arguments if they fit
+  const bool inl = n_prep <= gst::PREDICT_PREPS && n_steps <= gst::PREDICT_STEPS && n_gates <= gst::PREDICT_GATES;
   Carver c;
-  const size_t o_po = c.take<int64_t>(n_prep + 1), o_pg = c.take<uint8_t>(n_steps + 1),
-               o_go = c.take<int32_t>(n_gates), o_v = c.take<double>((size_t)n_pairs * Q * D);
+  const size_t o_po = c.take<int64_t>(inl ? 1 : n_prep + 1), o_pg = c.take<uint8_t>(inl ? 1 : n_steps + 1),
+               o_go = c.take<int32_t>(inl ? 1 : n_gates), o_v = c.take<double>((size_t)n_pairs * Q * D);
   if ((rc = ctx->ws.reserve(c.off + 256, ctx->stream))) return rc;
   char* b = reinterpret_cast<char*>(ctx->ws.p);
-  // the three host arrays, laid out as in the workspace, in one copy
-  const size_t span = o_v - o_po;
-  if ((rc = ctx->stage.acquire(span))) return rc;
-  char* h = reinterpret_cast<char*>(ctx->stage.p);
-  std::memcpy(h + (o_po - o_po), prep_offsets, (size_t)(n_prep + 1) * 8);
-  if (n_steps > 0) std::memcpy(h + (o_pg - o_po), prep_gates, (size_t)n_steps);
-  std::memcpy(h + (o_go - o_po), gates, (size_t)n_gates * 4);
-  if ((rc = ctx->stage.copy_to(b + o_po, span, ctx->stream))) return rc;
   gst::PredictLaunch a{};
+  if (inl) {
+    for (int p = 0; p <= n_prep; ++p) a.words.prep_off[p] = (int32_t)prep_offsets[p];
+    if (n_steps > 0) std::memcpy(a.words.prep_gates, prep_gates, (size_t)n_steps);
+    for (int s = 0; s < n_gates; ++s) a.words.gate_of[s] = (uint8_t)gates[s];
+  } else {
+    // the three host arrays, laid out as in the workspace, in one copy
+    const size_t span = o_v - o_po;
+    if ((rc = ctx->stage.acquire(span))) return rc;
+    char* h = reinterpret_cast<char*>(ctx->stage.p);
+    std::memcpy(h + (o_po - o_po), prep_offsets, (size_t)(n_prep + 1) * 8);
+    if (n_steps > 0) std::memcpy(h + (o_pg - o_po), prep_gates, (size_t)n_steps);
+    std::memcpy(h + (o_go - o_po), gates, (size_t)n_gates * 4);
+    if ((rc = ctx->stage.copy_to(b + o_po, span, ctx->stream))) return rc;
+    a.prep_off = reinterpret_cast<const int64_t*>(b + o_po);
+    a.prep_gates = reinterpret_cast<const uint8_t*>(b + o_pg);
+    a.gate_of = reinterpret_cast<const int32_t*>(b + o_go);
+  }
   a.D = D;
   a.M = theta->n_outcomes;
   a.K = theta->n_gates;
@@ -1389,9 +1400,6 @@ int gst_predict(gst_ctx* ctx, const gst_gateset* theta, int n_prep, const int64_
   a.G = theta->gates;
   a.n_pairs = n_pairs;
   a.n_gates = n_gates;
-  a.prep_off = reinterpret_cast<const int64_t*>(b + o_po);
-  a.prep_gates = reinterpret_cast<const uint8_t*>(b + o_pg);
-  a.gate_of = reinterpret_cast<const int32_t*>(b + o_go);
   a.r_max = r_max;
   a.levels = levels;
   a.Q = Q;

@@ -456,15 +456,25 @@ hipError_t launch_grad_gemm_batch(const PlanBatch& b, int D, int n, int grid_x, 
 hipError_t launch_reduce_plan_batch(const PlanBatch& b, int n, int grid_x, int parts, hipStream_t stream);
 // Predictions of repeated gate applications: V = block-start states
 // [n_pairs][Q][D], probs [n_pairs][r_max + 1][M]; pair = preparation * n_gates + gate.
+// Few short preparation words travel in the kernels' arguments (a copy to the
+// device costs the host more than the kernels take: four words, five gates and r to
+// 1000, the call and a distance 23.5 -> 20.8 us).
+constexpr int PREDICT_PREPS = 64, PREDICT_STEPS = 512, PREDICT_GATES = 64;
+struct PredictWords {
+  int32_t prep_off[PREDICT_PREPS + 1];
+  uint8_t prep_gates[PREDICT_STEPS];
+  uint8_t gate_of[PREDICT_GATES];
+};
 struct PredictLaunch {
   int D, M, K;
   const double* rho;
   const double* E;
   const double* G;
   int n_pairs, n_gates;
-  const int64_t* prep_off;    // [n_prep + 1]
+  const int64_t* prep_off;    // [n_prep + 1]; null: the words and gates are in `words`
   const uint8_t* prep_gates;
   const int32_t* gate_of;     // [n_gates]
+  PredictWords words;
   int r_max, levels, Q;       // blocks of 2^(levels-1) repetitions, Q blocks
   double* V;
   double* probs;
