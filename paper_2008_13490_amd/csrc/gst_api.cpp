@@ -2404,7 +2404,7 @@ namespace {
 
 // Context-level calls with a three-qubit gate set: the list (and counts) are
 // read back to the host and evaluated as a temporary resident request, whose
-// per-gate step positions the gate-gradient kernel needs.
+// grouped schedule (or plan) the kernels need.
 int plain_eval64(gst_ctx* ctx, const gst_gateset* gs, const gst_seqlist* sl, int mode, const int32_t* counts,
                  const double* w, double* probs, double* objective, double* grad) {
   const int64_t S = sl->n_seq;
