@@ -416,7 +416,7 @@ struct gst_batch {
     int D = 0, n = 0, K_max = 1, M_max = 1, jl_max = 0, n_levels = 0;
     bool any_grad = false, any_slab = false;
     std::vector<int> fwd_grid, bwd_grid, inj_grid;  // per level
-    int item_grid = 0, gemm_grid = 0, red_x = 0, red_parts = 1;
+    int item_grid = 0, gemm_grid = 0, red_x = 0, red_stage1 = 1;
     gst::PlanBatch dev{};
   } pgroup[2];
   DevBuf plan_ws;                       // the batched plans' scratch, one region per request
@@ -1091,11 +1091,13 @@ void plan_setup(gst_req* r, const gst_gateset* th, int mode, const double* w, do
   red.n_head = n_head;
   red.P = s.need_slab ? Pw : 0;
   red.n_part = gst::reduce_parts(n_head);
+  red.n_part_tiles = 1;
   for (int k = 0; k <= red.K; ++k) {
     red.chunk_ptr[k] = red.K > 0 ? d.tile_ptr[k] : 0;
     if (k > 0) {
       const int64_t nk = red.chunk_ptr[k] - red.chunk_ptr[k - 1];
-      red.n_part = std::max(red.n_part, gst::reduce_parts((int)std::min<int64_t>(nk, 1 << 20)));
+      red.n_part_tiles = std::max(red.n_part_tiles, gst::reduce_parts((int)std::min<int64_t>(nk, 1 << 20)));
+      red.n_part = std::max(red.n_part, red.n_part_tiles);
     }
   }
   red.objective = objective;
@@ -1992,7 +1994,7 @@ static int batch_enqueue(gst_batch* b, hipStream_t stream, bool eager) {
     }
     if (pg.any_slab) {
       ProfScope ps(pc, FAM_REDUCE);
-      HIP_TRY(gst::launch_reduce_plan_batch(pg.dev, pg.n, pg.red_x, pg.red_parts, stream));
+      HIP_TRY(gst::launch_reduce_plan_batch(pg.dev, pg.n, pg.red_x, pg.red_stage1, stream));
     }
   }
   const gst_batch::P64Group& g = b->p64;
@@ -2185,7 +2187,7 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
       if (st.need_slab) {
         pg.any_slab = true;
         pg.red_x = (int)std::max<int64_t>(pg.red_x, (st.red.P + 63) / 64);
-        pg.red_parts = std::max(pg.red_parts, st.red.n_part);
+        pg.red_stage1 = std::max(pg.red_stage1, (int)gst::reduce_stage1_blocks(st.red));
       }
     }
   }

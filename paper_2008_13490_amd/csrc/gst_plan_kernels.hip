@@ -914,9 +914,18 @@ __device__ __forceinline__ void reduce_stage1_body(const PlanReduce& a, int64_t 
   if (ty == 0 && x < a.P && g < G) a.part[(int64_t)g * a.P + x] = (red[0][tx] + red[1][tx]) + (red[2][tx] + red[3][tx]);
 }
 
-__global__ __launch_bounds__(256) void plan_reduce_stage1(const PlanReduce a) {
-  reduce_stage1_body(a, blockIdx.x, blockIdx.y);
+// Workgroup blk of reduce_stage1_blocks(a).
+__device__ __forceinline__ void reduce_stage1_at(const PlanReduce& a, int64_t blk) {
+  const int64_t head = reduce_head_blocks(a), first = head * a.n_part;
+  if (blk < first) {
+    reduce_stage1_body(a, blk % head, (int)(blk / head));
+  } else {
+    const int64_t tiles = (a.P + 63) / 64 - head, y = blk - first;
+    reduce_stage1_body(a, head + y % tiles, (int)(y / tiles));
+  }
 }
+
+__global__ __launch_bounds__(256) void plan_reduce_stage1(const PlanReduce a) { reduce_stage1_at(a, blockIdx.x); }
 
 // Column x adds its region's stage-1 partials in ascending g.  A +inf
 // objective partial marks p <= 0 with N > 0: the objective is then +inf and
@@ -1014,8 +1023,8 @@ __global__ __launch_bounds__(256, 2) void grad_gemm_batch(const PlanBatch b) {
 
 __global__ __launch_bounds__(256) void reduce_stage1_batch(const PlanBatch b) {
   const PlanReduce& r = b.reduce[blockIdx.z];  // chunk_ptr is indexed at run time: no register copy
-  if (r.P <= 0 || (int64_t)blockIdx.x * 64 >= r.P || (int)blockIdx.y >= r.n_part) return;
-  reduce_stage1_body(r, blockIdx.x, blockIdx.y);
+  if (r.P <= 0 || (int64_t)blockIdx.x >= reduce_stage1_blocks(r)) return;
+  reduce_stage1_at(r, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void reduce_stage2_batch(const PlanBatch b) {
@@ -1096,9 +1105,10 @@ hipError_t launch_inject(const InjectLaunch& a, hipStream_t stream) {
 }
 
 hipError_t launch_reduce_plan(const PlanReduce& a, hipStream_t stream) {
-  if (a.P <= 0 || a.n_part < 1 || a.n_part > 64 || a.K < 0 || a.K > 8) return hipErrorInvalidValue;
+  if (a.P <= 0 || a.n_part < 1 || a.n_part > 64 || a.n_part_tiles < 1 || a.n_part_tiles > a.n_part || a.K < 0 || a.K > 8)
+    return hipErrorInvalidValue;
   const unsigned xb = (unsigned)((a.P + 63) / 64);
-  gst_launch(plan_reduce_stage1, dim3(xb, (unsigned)a.n_part), dim3(256), 0, stream, a);
+  gst_launch(plan_reduce_stage1, dim3((unsigned)reduce_stage1_blocks(a)), dim3(256), 0, stream, a);
   gst_launch(plan_reduce_stage2, dim3(xb), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
@@ -1160,10 +1170,10 @@ hipError_t launch_grad_gemm_batch(const PlanBatch& b, int D, int n, int grid_x, 
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_plan_batch(const PlanBatch& b, int n, int grid_x, int parts, hipStream_t stream) {
+hipError_t launch_reduce_plan_batch(const PlanBatch& b, int n, int grid_x, int stage1_x, hipStream_t stream) {
   if (n <= 0 || grid_x <= 0) return hipSuccess;
-  if (parts < 1 || parts > 64) return hipErrorInvalidValue;
-  gst_launch(reduce_stage1_batch, dim3((unsigned)grid_x, (unsigned)parts, (unsigned)n), dim3(256), 0, stream, b);
+  if (stage1_x < 1) return hipErrorInvalidValue;
+  gst_launch(reduce_stage1_batch, dim3((unsigned)stage1_x, 1u, (unsigned)n), dim3(256), 0, stream, b);
   gst_launch(reduce_stage2_batch, dim3((unsigned)grid_x, 1u, (unsigned)n), dim3(256), 0, stream, b);
   return hipGetLastError();
 }
