@@ -134,6 +134,12 @@ __host__ __device__ inline size_t trunk_lds_bytes(int K, int levels) {
   const size_t r = head_red_bytes(1, 0);
   return a > r ? a : r;
 }
+// The forward trunks stage no injected vectors: their jump matrices follow rho
+// (25 KB with six gates and five levels, six workgroups to a CU instead of four;
+// sixteen fits 29.0 -> 27.6 us).
+__host__ __device__ inline size_t trunk_fwd_lds_bytes(int K, int levels) {
+  return (trunk_inj_doubles(K) + (size_t)(levels > 2 ? levels : 2) * GATE_STRIDE) * 8 + 64;
+}
 
 // Lane i's row of the matrix of op `od`: a gate (of the gate set or its
 // transpose) or a jump matrix slot.
@@ -203,7 +209,7 @@ __device__ __forceinline__ void trunk_fwd_body(const PlanArgs& a, int64_t t_begi
   }
   stage_gateset<D, 64, STAGE_G>(s, a.G, a.E, a.rho, K, a.M);
   if (blk == 0 && lane < D) a.FA[lane] = a.rho[lane];
-  double* js = lds_raw + trunk_jump_doubles(K);
+  double* js = lds_raw + trunk_inj_doubles(K);
   const bool st = (D == 16) || lane < D;  // rows 1..3 store the same values as row 0
   for (; t < t_end; t += nblk) {
     if (t != t_begin + blk) {
@@ -1061,7 +1067,7 @@ int trunk_blocks_for(int64_t n) {
 
 hipError_t launch_trunk_fwd(const PlanArgs& a, hipStream_t stream) {
   const int blocks = trunk_blocks_for(a.t_end - a.t_begin);
-  const size_t bytes = trunk_lds_bytes(a.K, a.jump_levels);
+  const size_t bytes = trunk_fwd_lds_bytes(a.K, a.jump_levels);
   if (a.D == 16)
     gst_launch(trunk_fwd_kernel<16>, dim3(blocks), dim3(64), bytes, stream, a);
   else if (a.D == 4)
@@ -1138,7 +1144,7 @@ hipError_t launch_grad_gemm(const GemmLaunch& a, hipStream_t stream) {
 hipError_t launch_trunk_fwd_batch(const PlanBatch& b, int D, int n, int level, int grid_x, int K_max, int jl_max,
                                   hipStream_t stream) {
   if (n <= 0 || grid_x <= 0) return hipSuccess;
-  GST_BATCH_D(trunk_fwd_batch, dim3((unsigned)grid_x, (unsigned)n), dim3(64), trunk_lds_bytes(K_max, jl_max), stream,
+  GST_BATCH_D(trunk_fwd_batch, dim3((unsigned)grid_x, (unsigned)n), dim3(64), trunk_fwd_lds_bytes(K_max, jl_max), stream,
               b, level);
   return hipGetLastError();
 }
