@@ -249,10 +249,12 @@ int gst_set_plan_jump(gst_ctx* ctx, int reps);
  * prep_gates in time order, at most 64 gates each, gate indices < n_gates of theta)
  * and every gate index gates[s] (host array of n_gates).  One or two qubits; theta
  * and probs are device pointers, probs holds n_prep * n_gates * (r_max + 1) * M
- * doubles.  The powers run in blocks of 32 repetitions: a chain steps from block to
- * block with (G_s)^32 (built per call by repeated squaring) and every block then
- * takes single steps, so the probabilities for r < 32 equal the plain evaluation of
- * the word bit for bit and later ones agree to rounding.  The host arrays are read
+ * doubles.  The powers run in blocks of 32 repetitions: the first four blocks are
+ * reached one from the other with (G_s)^32, every later one from the block 128
+ * repetitions before it with (G_s)^128 (both built per call by repeated squaring), and
+ * every block then takes single steps, so the probabilities for r < 32 equal the plain
+ * evaluation of the word bit for bit, later ones agree to rounding, and those of
+ * an r are the same for every r_max >= r.  The host arrays are read
  * before the call returns (copied); the evaluation is
  * stream-ordered on the context's stream and the call does not wait for it.  The
  * context's workspace holds the block-start states until the next call.  GST_EINVAL for

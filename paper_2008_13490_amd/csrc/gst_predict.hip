@@ -27,14 +27,13 @@ __device__ __forceinline__ int gate_of(const PredictLaunch& a, int s) {
   return a.prep_off ? a.gate_of[s] : (int)a.words.gate_of[s];
 }
 
-// From this many blocks on the wave's four teams take every fourth block each.
-constexpr int WIDE_BLOCKS = 8;
-
 // One single-wave workgroup per (preparation, gate) pair.  The block starts are a
-// chain of dependent products, and all of the kernel's work: with Q >= WIDE_BLOCKS
-// the wave's four 16-lane teams step through blocks t, t + 4, ... with (G_s)^(4B), two
-// squarings more against a quarter of the chain (32 blocks: 9.2 -> 7.9 us); with fewer
-// blocks every team repeats the one chain.
+// chain of dependent products, and all of the kernel's work: block t < 4 is reached
+// from block t - 1 with (G_s)^B, and from there the wave's four 16-lane teams step
+// through blocks t, t + 4, ... with (G_s)^(4B), two squarings more against a quarter
+// of the chain (32 blocks: 9.2 -> 7.9 us).  The way to a block is the same whatever Q
+// is, so a prediction does not depend on how many follow it; with at most four
+// blocks the two squarings are left out, and every team repeats the one chain.
 template <int D>
 __global__ __launch_bounds__(64) void predict_chain_kernel(const PredictLaunch a) {
   extern __shared__ double lds_raw[];
@@ -54,7 +53,7 @@ __global__ __launch_bounds__(64) void predict_chain_kernel(const PredictLaunch a
       const int k = __builtin_amdgcn_readlane(kw, x);
       f = dot_row(f, load_row_d<D>(s.Gs + k * GATE_STRIDE + i * ROW));
     }
-    const bool wide = a.Q >= WIDE_BLOCKS;
+    const bool wide = a.Q > TPW;
     build_jumps(js, s.Gs, 1u | (uint32_t)g << 8, 0, wide ? a.levels + 2 : a.levels, false, lane);
     const RowD<D> RJ = load_row_d<D>(js + (a.levels - 1) * GATE_STRIDE + i * ROW);
     double* v = a.V + (int64_t)pair * a.Q * D;
