@@ -56,6 +56,12 @@ struct LeafLaunch {
   int64_t ckpt_per_team;
   unsigned long long* status;  // [0] bad gate indices, [1] p <= 0 with N > 0
 };
+// The byte that the sequence kernel reads in place of a gate index past the end
+// of a word: the gate set's, which exists whatever the list is (the indices of a
+// list of empty words have no first byte).
+__host__ __device__ inline const uint8_t* pad_index(const LeafLaunch& a) {
+  return reinterpret_cast<const uint8_t*>(a.rho);
+}
 
 // Kernels of the shared-prefix plan.  Row conventions:
 //   state arena FA: row 0 = rho, row 1 + j = state after trunk step j,

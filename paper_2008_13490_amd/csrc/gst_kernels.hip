@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256, seq_waves(PRE)) void leaf_kernel(const LeafLau
                   M,
                   a.mode,
                   a.want_grad != 0,
-                  g_gates,
+                  as_global(pad_index(a)),
                   as_global(a.counts),
                   as_global(a.W),
                   as_global(a.probs),

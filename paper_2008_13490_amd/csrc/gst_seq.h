@@ -62,7 +62,7 @@ typedef const __attribute__((address_space(1))) double* gdoubles;
 struct SeqArgs {
   int K, M, mode;
   bool grad;
-  gbytes base;         // the list's first gate index (always exists)
+  gbytes base;         // a byte that always exists, read in place of indices past the end of a word
   gcounts counts;
   gdoubles W;
   __attribute__((address_space(1))) double* probs;  // or null
@@ -135,7 +135,7 @@ __device__ __forceinline__ void seq_group(const SeqArgs& a, const Lds& s, Pairs*
   double f = s.rho[i];
   // ---- forward chain, a checkpoint every C steps.  Gate indices are loaded
   // one chunk of 16 steps ahead; the loads are unconditional (past the end of
-  // the word they read the first index of the list) so that the compiler can
+  // the word they read a byte that always exists) so that the compiler can
   // wait for the previous load alone ----
   int kv_next = *(i < L ? word + i : a.base);
   kv_next = i < L ? kv_next : 0;
