@@ -158,7 +158,7 @@ __device__ __forceinline__ bool sched_empty(uint32_t en) { return (en & 0xffffff
 // Eight waves, two per SIMD: waves 0 .. 3 step a round's first entry, waves
 // 4 .. 7 its second.
 __global__ __launch_bounds__(512, 2) void chain64_fwd_kernel(const Chain64Launch a) {
-  __shared__ double V[SLOTS * SST];
+  __shared__ __align__(16) double V[SLOTS * SST];
   const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3, z = wave >> 2;
   SchedGates<false> gates;
   gates.load(a.G, a.K, w, l);
@@ -212,7 +212,7 @@ __device__ __forceinline__ void add_outer(d4 (&dg)[4], double b, const double (&
 
 // Waves 0 .. 3: the adjoints.  Waves 4 .. 7: dG.  Both pass the same barriers.
 __global__ __launch_bounds__(512, 2) void chain64_bwd_kernel(const Chain64Launch a) {
-  __shared__ double V[SLOTS * SST];
+  __shared__ __align__(16) double V[SLOTS * SST];
   __shared__ double F[2][2][SCHED_COLS * SFS];  // the recorded states of a round's entries, double-buffered
   const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3;
   const auto* entries = as_global(a.entries);
@@ -948,8 +948,8 @@ __device__ __forceinline__ void gemm64_ts_body(const Gemm64TsLaunch& a, int64_t 
   __shared__ int64_t Rb[TS_CHUNK_MAX];       // adjoint row of column 0 at each tile-step
   __shared__ int32_t Rf[TS_CHUNK_MAX][16];   // the columns' state rows before it (a row is 512 bytes)
   __shared__ int Rn[TS_CHUNK_MAX];           // its columns, rounded up to whole quarters
-  __shared__ double Sb[2][16 * TS_SST];      // a tile-step's adjoint rows, double-buffered
-  __shared__ double Sf[2][16 * TS_SST];      // its state rows
+  __shared__ __align__(16) double Sb[2][16 * TS_SST];  // a tile-step's adjoint rows, double-buffered
+  __shared__ __align__(16) double Sf[2][16 * TS_SST];  // its state rows
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int z = lane >> 4, ii = lane & 15;
   const int64_t x0 = a.chunk_beg[ch];
