@@ -312,6 +312,7 @@ struct Schedule {
   int64_t n_tiles = 0, n_entries = 0;
   DevBuf buf;
   int64_t* tile_ptr = nullptr;
+  int64_t* tile_rec = nullptr;
   uint32_t* entries = nullptr;
 };
 
@@ -358,13 +359,14 @@ static int readout_blocks_of(const gst_ctx* ctx, int64_t n) {
 static int head_rows64(const gst_req* r) { return r->readout_blocks64 * gst::READOUT64_WAVES + r->blocks64; }
 static size_t chain64_ws_bytes(const gst_req* r, bool want_grad) {
   size_t d = (size_t)r->S * 64;
-  if (want_grad) d += (size_t)r->K * r->blocks64 * 4096 + (size_t)(r->sched.n_entries + 1) * gst::SCHED_COLS * 64;
+  if (want_grad) d += (size_t)r->K * r->blocks64 * 4096 + (size_t)(r->n_steps + 1) * 64;
   return d * 8 + 256;
 }
 
-// The grouped schedule of a request's words: counted, then written (on the
-// null stream, like the request's uploads).
-static int build_schedule(gst_req* r) {
+// The grouped schedule of a request's words (tile_rec: the steps of the tiles
+// before each): counted, then written (on the null stream, like the request's
+// uploads).
+static int build_schedule(gst_req* r, const std::vector<int64_t>& tile_rec) {
   Schedule& d = r->sched;
   DevBuf count;
   int rc = count.reserve((size_t)(d.n_tiles + 1) * 8, nullptr);
@@ -383,12 +385,15 @@ static int build_schedule(gst_req* r) {
   for (int64_t t = 0; t < d.n_tiles; ++t) ptr[t + 1] += ptr[t];
   d.n_entries = ptr[d.n_tiles];
   Carver cv;
-  const size_t o_p = cv.take<int64_t>(ptr.size()), o_e = cv.take<uint32_t>((size_t)d.n_entries + 1);
+  const size_t o_p = cv.take<int64_t>(ptr.size()), o_r = cv.take<int64_t>(tile_rec.size()),
+               o_e = cv.take<uint32_t>((size_t)d.n_entries + 1);
   rc = d.buf.reserve(cv.off, nullptr);
   if (rc) return rc;
   d.tile_ptr = reinterpret_cast<int64_t*>((char*)d.buf.p + o_p);
   d.entries = reinterpret_cast<uint32_t*>((char*)d.buf.p + o_e);
+  d.tile_rec = reinterpret_cast<int64_t*>((char*)d.buf.p + o_r);
   HIP_TRY(hipMemcpy(d.tile_ptr, ptr.data(), ptr.size() * 8, hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpy(d.tile_rec, tile_rec.data(), tile_rec.size() * 8, hipMemcpyHostToDevice));
   b.tile_n = nullptr;
   b.tile_ptr = d.tile_ptr;
   b.entries = d.entries;
@@ -1674,7 +1679,7 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   Carver cv;
   const size_t o_off = cv.take<int64_t>(S + 1), o_g = cv.take<uint8_t>(std::max<int64_t>(n_steps, 1)),
                o_c = cv.take<int32_t>(counts_host ? S * n_outcomes : 1), o_ord = cv.take<int64_t>(S + 1),
-               o_sl = cv.take<double>((size_t)std::max<int64_t>(r->n_tiles(), 1) * Pw),
+               o_sl = cv.take<double>(D == 64 ? 1 : (size_t)std::max<int64_t>(r->n_tiles(), 1) * Pw),
                o_t = cv.take<gst::BatchTile>(tiles.size() + 1), o_q = cv.take<unsigned>(kQueueWords + 2),
                o_gc64 = cv.take<int64_t>(gcp64.size() + 1),
                o_hd64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)head_rows64(r.get()) * Pc64),
@@ -1719,7 +1724,11 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
     if (rc) return rc;
   }
   if (r->sched.tile_seqs > 0) {
-    rc = build_schedule(r.get());
+    std::vector<int64_t> tile_rec((size_t)r->sched.n_tiles + 1, 0);
+    for (int64_t q = 0; q < S; ++q)
+      tile_rec[(size_t)(q / r->sched.tile_seqs) + 1] += sl->offsets[order[q] + 1] - sl->offsets[order[q]];
+    for (int64_t t = 0; t < r->sched.n_tiles; ++t) tile_rec[t + 1] += tile_rec[t];
+    rc = build_schedule(r.get(), tile_rec);
     if (rc) return rc;
     if (D == 64) r->eval_ws_bytes = chain64_ws_bytes(r.get(), true);
   }
@@ -1874,6 +1883,8 @@ static int run64(gst_req* r, const gst_gateset* th, int mode, const double* w, d
   a.tile_row = std::max(r->blocks64, 1);
   a.tile_ptr = r->sched.tile_ptr;
   a.entries = r->sched.entries;
+  a.tile_rec = r->sched.tile_rec;
+  a.zero_rec = (int)r->n_steps;
   a.rec_f = want_grad ? rec : nullptr;
   a.fin = fin;
   a.head = r->head64 + (size_t)ro_rows * Pc;

@@ -302,10 +302,13 @@ struct Chain64Launch {
   int64_t S;
   int tile_seqs;             // chains per tile (consecutive in `order`)
   int n_tiles;
-  int tile_row;          // workgroups take the tiles there and back in rows of this many
+  int tile_row;              // workgroups take the tiles there and back in rows of this many
   const int64_t* tile_ptr;   // [n_tiles + 1]
   const uint32_t* entries;
-  double* rec_f;             // [entries][4][64]: the states before each step (null: not recorded)
+  const int64_t* tile_rec;   // [n_tiles + 1]: the chain-steps of the tiles before
+  int zero_rec;              // all of them
+  double* rec_f;             // [zero_rec + 1][64]: the states before each entry's columns with a chain, entry
+                             // by entry, then a row of zeros (null: not recorded)
   double* fin;               // [S][64], in `order`: final states (forward), seeds (reverse)
   int M;                     // reverse: width of the head rows, 1 + 64 + 64 M
   double* head;              // reverse: [gridDim.x] head rows, [0 | dL/drho | 0]

@@ -55,7 +55,8 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // Both kernels run eight waves, two per SIMD.  Forward: four waves per entry of
 // the round, so the two products fill each other's latencies (302 -> 170 us
 // below, against one entry after the other on two workgroups of four waves per
-// CU); each entry's four states before it are recorded (2 KB in a row).
+// CU); the states before each entry are recorded one after the other, so that a
+// chain-step takes 512 bytes whatever its entry holds.
 // Reverse: four waves step the adjoints of both entries, at a raised priority,
 // and the other four load the recorded states two rounds ahead and add
 // dG += b f^T, one 16x16x4 MFMA per 16 x 16 tile and entry, in accumulators for
@@ -155,6 +156,24 @@ __device__ __forceinline__ void sched_step(const SchedGates<TR>& gates, double* 
 // An entry without chains (the second of a round, or padding).
 __device__ __forceinline__ bool sched_empty(uint32_t en) { return (en & 0xffffffu) == SCHED_NONE; }
 
+// Its chains: columns 0 .. n - 1 (the others' fields hold chain 16).
+__device__ __forceinline__ int sched_live(uint32_t en) { return SCHED_COLS - __popc(en & SCHED_NONE); }
+
+// A lane's entry's chains, those of the lanes before it, and of all lanes.
+struct LiveSum {
+  int own, before, all;
+};
+__device__ __forceinline__ LiveSum sched_live_sum(int own) {
+  LiveSum s{own, 0, 0};
+#pragma unroll
+  for (int bit = 0; bit < 3; ++bit) {
+    const unsigned long long m = __ballot(own >> bit & 1);
+    s.before += (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)) << bit;
+    s.all += __popcll(m) << bit;
+  }
+  return s;
+}
+
 // Eight waves, two per SIMD: waves 0 .. 3 step a round's first entry, waves
 // 4 .. 7 its second.
 __global__ __launch_bounds__(512, 2) void chain64_fwd_kernel(const Chain64Launch a) {
@@ -166,12 +185,14 @@ __global__ __launch_bounds__(512, 2) void chain64_fwd_kernel(const Chain64Launch
   const auto* entries = as_global(a.entries);
   auto* rec = as_global(a.rec_f);
   auto* fin = as_global(a.fin);
+  if (a.rec_f && blockIdx.x == 0 && wave == 0) rec[(int64_t)a.zero_rec * N64 + l] = 0.0;
   int at = blockIdx.x;
   for (int tile = next_tile(at, a.tile_row, a.n_tiles); tile < a.n_tiles; tile = next_tile(at, a.tile_row, a.n_tiles)) {
     const int64_t q0 = (int64_t)tile * a.tile_seqs;
     const int n = (int)(q0 + a.tile_seqs < a.S ? a.tile_seqs : a.S - q0);
     const int64_t e0 = uniform64(a.tile_ptr[tile]);
     const int ne = (int)(uniform64(a.tile_ptr[tile + 1]) - e0);
+    int done = (int)uniform64(a.tile_rec[tile]);  // records of the entries before
     for (int c = wave; c <= SCHED_CHAINS; c += 8) {
       V[2 * c * SST + state_at(l)] = c < n ? rho : 0.0;
       if (c == SCHED_CHAINS) V[(2 * c + 1) * SST + state_at(l)] = 0.0;
@@ -182,12 +203,17 @@ __global__ __launch_bounds__(512, 2) void chain64_fwd_kernel(const Chain64Launch
       const uint32_t cur = next;
       const int m = min(ne - eb, 64);
       next = entries[e0 + min(eb + 64 + l, ne - 1)];
+      // lane x: the record of column w before entry x, or none
+      const LiveSum live = sched_live_sum(l < m ? sched_live(cur) : 0);
+      const int rows = a.rec_f && w < live.own ? done + live.before + w : -1;
+      done += live.all;
       for (int x = 0; x < m; x += 2) {
         const uint32_t en = (uint32_t)__builtin_amdgcn_readlane((int)cur, x + z);
+        const int row = __builtin_amdgcn_readlane(rows, x + z);
         if (!sched_empty(en)) {
           sched_step<false, 0>(gates, V, en, w, l);
           // the state before the entry is still there: the step wrote the other parity
-          if (a.rec_f) rec[((e0 + eb + x + z) * SCHED_COLS + w) * N64 + l] = V[entry_field(en, w) * SST + state_at(l)];
+          if (row >= 0) rec[(int64_t)row * N64 + l] = V[entry_field(en, w) * SST + state_at(l)];
         }
         lds_barrier();
       }
@@ -230,7 +256,7 @@ __global__ __launch_bounds__(512, 2) void chain64_bwd_kernel(const Chain64Launch
       const int64_t q0 = (int64_t)tile * a.tile_seqs;
       const int n = (int)(q0 + a.tile_seqs < a.S ? a.tile_seqs : a.S - q0);
       const int64_t e0 = uniform64(a.tile_ptr[tile]);
-    const int ne = (int)(uniform64(a.tile_ptr[tile + 1]) - e0);
+      const int ne = (int)(uniform64(a.tile_ptr[tile + 1]) - e0);
       uint32_t next = entries[e0 + max(ne - 1 - l, 0)];
       for (int c = w; c <= SCHED_CHAINS; c += 4) {
         if (c < n) {
@@ -279,29 +305,44 @@ __global__ __launch_bounds__(512, 2) void chain64_bwd_kernel(const Chain64Launch
   for (int tile = next_tile(at, a.tile_row, a.n_tiles); tile < a.n_tiles; tile = next_tile(at, a.tile_row, a.n_tiles)) {
     const int64_t e0 = uniform64(a.tile_ptr[tile]);
     const int ne = (int)(uniform64(a.tile_ptr[tile + 1]) - e0);
-    // column w's state of the entry x before the last one
-    auto state = [&](int x) { return rec[((e0 + max(ne - 1 - x, 0)) * SCHED_COLS + w) * N64 + l]; };
-    uint32_t next = entries[e0 + max(ne - 1 - l, 0)];
+    // The records of 64 entries, backwards from the tile's last one: lane x has the
+    // row of column w's state before entry x of them (no chain there: the row of
+    // zeros), `end` moves to the first entry's.
+    int end = (int)uniform64(a.tile_rec[tile + 1]);
+    auto entry = [&](int xb) { return entries[e0 + max(ne - 1 - xb - l, 0)]; };
+    auto records = [&](uint32_t en, int xb) {
+      const LiveSum live = sched_live_sum(xb + l < ne ? sched_live(en) : 0);
+      const int row = w < live.own ? end - live.before - live.own + w : a.zero_rec;
+      end -= live.all;
+      return row;
+    };
+    uint32_t cur = entry(0), next = entry(64);
+    int rows = records(cur, 0), rows_next = records(next, 64);
+    auto state = [&](int rows, int x) {
+      return rec[(int64_t)(uint32_t)__builtin_amdgcn_readlane(rows, x) * N64 + l];
+    };
     double ring[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) ring[u] = state(u);
+    for (int u = 0; u < 4; ++u) ring[u] = state(rows, u);
     F[0][0][w * SFS + l] = ring[0];
     F[0][1][w * SFS + l] = ring[1];
-    ring[0] = state(4);
-    ring[1] = state(5);
+    ring[0] = state(rows, 4);
+    ring[1] = state(rows, 5);
     lds_barrier();
     for (int xb = 0; xb < ne; xb += 64) {
-      const uint32_t cur = next;
       const int m = min(ne - xb, 64);
-      next = entries[e0 + max(ne - 65 - xb - l, 0)];
+      const uint32_t later = entry(xb + 128);
+      // the rows of the loads, six entries ahead
+      const int here = __shfl(rows, (l + 6) & 63), there = __shfl(rows_next, (l + 6) & 63);
+      const int ahead = l < 58 ? here : there;
       for (int x0 = 0; x0 < m; x0 += 4) {
 #pragma unroll
         for (int y = 0; y < 2; ++y) {
           // the next round's states, loaded two rounds ago, and the loads that replace them
           F[y ^ 1][0][w * SFS + l] = ring[2 - 2 * y];
           F[y ^ 1][1][w * SFS + l] = ring[3 - 2 * y];
-          ring[2 - 2 * y] = state(xb + x0 + 2 * y + 6);
-          ring[3 - 2 * y] = state(xb + x0 + 2 * y + 7);
+          ring[2 - 2 * y] = state(ahead, x0 + 2 * y);
+          ring[3 - 2 * y] = state(ahead, x0 + 2 * y + 1);
 #pragma unroll
           for (int z = 0; z < 2; ++z) {
             const uint32_t en = (uint32_t)__builtin_amdgcn_readlane((int)cur, x0 + 2 * y + z);
@@ -321,6 +362,10 @@ __global__ __launch_bounds__(512, 2) void chain64_bwd_kernel(const Chain64Launch
           lds_barrier();
         }
       }
+      cur = next;
+      next = later;
+      rows = rows_next;
+      rows_next = records(next, xb + 128);
     }
     lds_barrier();  // the adjoints have been read
   }
