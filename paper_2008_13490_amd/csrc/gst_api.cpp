@@ -337,6 +337,7 @@ struct gst_req {
   Schedule sched;
   int readout_blocks64 = 0, blocks64 = 0;
   int64_t* gate_chunk_ptr64 = nullptr;  // [K + 1]: the gates' ranges of the reverse workgroups' tiles
+  double* fin64 = nullptr;              // [S][64]: final states, in place their seeds
   double* head64 = nullptr;             // [readout waves + reverse workgroups][1 + 64 + 64 M]
   double* part64 = nullptr;             // scratch of the ordered head sum
   size_t eval_ws_bytes = 0;             // context workspace one evaluation with gradient needs
@@ -355,12 +356,11 @@ static int readout_blocks_of(const gst_ctx* ctx, int64_t n) {
 }
 
 // A three-qubit request without a plan: its head rows, and the context
-// workspace of an evaluation.
+// workspace of an evaluation with the gradient (the workgroups' dL/dG, the
+// recorded states).
 static int head_rows64(const gst_req* r) { return r->readout_blocks64 * gst::READOUT64_WAVES + r->blocks64; }
-static size_t chain64_ws_bytes(const gst_req* r, bool want_grad) {
-  size_t d = (size_t)r->S * 64;
-  if (want_grad) d += (size_t)r->K * r->blocks64 * 4096 + (size_t)(r->n_steps + 1) * 64;
-  return d * 8 + 256;
+static size_t chain64_ws_bytes(const gst_req* r) {
+  return ((size_t)r->K * r->blocks64 * 4096 + (size_t)(r->n_steps + 1) * 64) * 8 + 256;
 }
 
 // The grouped schedule of a request's words (tile_rec: the steps of the tiles
@@ -1682,6 +1682,7 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
                o_sl = cv.take<double>(D == 64 ? 1 : (size_t)std::max<int64_t>(r->n_tiles(), 1) * Pw),
                o_t = cv.take<gst::BatchTile>(tiles.size() + 1), o_q = cv.take<unsigned>(kQueueWords + 2),
                o_gc64 = cv.take<int64_t>(gcp64.size() + 1),
+               o_fin64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)S * 64 + 1),
                o_hd64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)head_rows64(r.get()) * Pc64),
                o_pt64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)gst::reduce_parts(head_rows64(r.get())) * Pc64);
   rc = r->data.reserve(cv.off + 256, ctx->stream);
@@ -1697,6 +1698,7 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   r->n_steps = n_steps;
   if (D == 64) {
     r->gate_chunk_ptr64 = reinterpret_cast<int64_t*>(base + o_gc64);
+    r->fin64 = reinterpret_cast<double*>(base + o_fin64);
     r->head64 = reinterpret_cast<double*>(base + o_hd64);
     r->part64 = reinterpret_cast<double*>(base + o_pt64);
     if (!gcp64.empty())
@@ -1730,7 +1732,7 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
     for (int64_t t = 0; t < r->sched.n_tiles; ++t) tile_rec[t + 1] += tile_rec[t];
     rc = build_schedule(r.get(), tile_rec);
     if (rc) return rc;
-    if (D == 64) r->eval_ws_bytes = chain64_ws_bytes(r.get(), true);
+    if (D == 64) r->eval_ws_bytes = chain64_ws_bytes(r.get());
   }
   r->resident_bytes = r->data.bytes + r->plan.buf.bytes + r->plan64.buf.bytes + r->sched.buf.bytes;
   (void)o_off;
@@ -1860,13 +1862,15 @@ static int run64(gst_req* r, const gst_gateset* th, int mode, const double* w, d
   const bool want_grad = grad != nullptr;
   const bool need_head = objective || grad;
   unsigned long long* np = nonpos ? nonpos : reinterpret_cast<unsigned long long*>(r->queue + kQueueWords);
-  // final states (in place: seeds), the gate tiles and the recorded states in
-  // the context workspace (calls on a context are stream ordered)
-  int rc = ctx->ws.reserve(chain64_ws_bytes(r, want_grad), ctx->stream);
-  if (rc) return rc;
-  double* fin = reinterpret_cast<double*>(ctx->ws.p);
-  double* dg = fin + (size_t)r->S * 64;
-  double* rec = dg + (size_t)r->K * r->blocks64 * 4096;
+  // the gate tiles and the recorded states in the context workspace (calls on a
+  // context are stream ordered); without the gradient nothing is allocated
+  double *fin = r->fin64, *dg = nullptr, *rec = nullptr;
+  if (want_grad) {
+    int rc = ctx->ws.reserve(chain64_ws_bytes(r), ctx->stream);
+    if (rc) return rc;
+    dg = reinterpret_cast<double*>(ctx->ws.p);
+    rec = dg + (size_t)r->K * r->blocks64 * 4096;
+  }
   HIP_TRY(gst::launch_queue_reset(r->queue, np, 1, ctx->stream));
   const int64_t Pc = 1 + 64 + (int64_t)r->M * 64;
   const int ro_rows = r->readout_blocks64 * gst::READOUT64_WAVES;
@@ -1885,7 +1889,7 @@ static int run64(gst_req* r, const gst_gateset* th, int mode, const double* w, d
   a.entries = r->sched.entries;
   a.tile_rec = r->sched.tile_rec;
   a.zero_rec = (int)r->n_steps;
-  a.rec_f = want_grad ? rec : nullptr;
+  a.rec_f = rec;
   a.fin = fin;
   a.head = r->head64 + (size_t)ro_rows * Pc;
   a.dg = dg;
