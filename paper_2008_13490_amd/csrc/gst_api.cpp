@@ -1871,7 +1871,6 @@ static int run64(gst_req* r, const gst_gateset* th, int mode, const double* w, d
     dg = reinterpret_cast<double*>(ctx->ws.p);
     rec = dg + (size_t)r->K * r->blocks64 * 4096;
   }
-  HIP_TRY(gst::launch_queue_reset(r->queue, np, 1, ctx->stream));
   const int64_t Pc = 1 + 64 + (int64_t)r->M * 64;
   const int ro_rows = r->readout_blocks64 * gst::READOUT64_WAVES;
   gst::Chain64Launch a{};
@@ -1891,11 +1890,14 @@ static int run64(gst_req* r, const gst_gateset* th, int mode, const double* w, d
   a.zero_rec = (int)r->n_steps;
   a.rec_f = rec;
   a.fin = fin;
+  a.nonpos = np;
   a.head = r->head64 + (size_t)ro_rows * Pc;
   a.dg = dg;
   if (a.n_tiles > 0) {
     ProfScope ps(ctx, FAM_CHAIN64);
     HIP_TRY(gst::launch_chain64_fwd(a, r->blocks64, ctx->stream));
+  } else {
+    HIP_TRY(gst::launch_queue_reset(r->queue, np, 1, ctx->stream));  // no forward sweep clears the count
   }
   {
     ProfScope ps(ctx, FAM_P64_READ);
@@ -1922,10 +1924,17 @@ static int run64(gst_req* r, const gst_gateset* th, int mode, const double* w, d
   }
   if (need_head) {
     ProfScope ps(ctx, FAM_REDUCE64);
-    // [objective | rho | E] from the head rows (two ordered stages) ...
-    HIP_TRY(gst::launch_reduce(r->head64, ro_rows + (want_grad ? r->blocks64 : 0), Pc, objective, grad, nullptr, 64,
-                               r->part64, ctx->stream));
-    // ... and the gate columns from the reverse workgroups' sums
+    // [objective | rho | E] from the head rows, and the gate columns from the
+    // reverse workgroups' sums
+    gst::HeadSum64 h{};
+    h.head = r->head64;
+    h.n_rows = ro_rows + (want_grad ? r->blocks64 : 0);
+    h.n_part = gst::reduce_parts(h.n_rows);
+    h.per = (h.n_rows + h.n_part - 1) / h.n_part;
+    h.P = Pc;
+    h.part = r->part64;
+    h.objective = objective;
+    h.grad = grad;
     gst::Reduce64Launch red{};
     red.M = r->M;
     red.K = r->K;
@@ -1933,7 +1942,7 @@ static int run64(gst_req* r, const gst_gateset* th, int mode, const double* w, d
     red.gate_chunk_ptr = r->gate_chunk_ptr64;
     red.grad = grad;
     red.nonpos = np;
-    HIP_TRY(gst::launch_reduce64(red, ctx->stream));
+    HIP_TRY(gst::launch_head_sum64(h, red, ctx->stream));
   }
   return GST_OK;
 }

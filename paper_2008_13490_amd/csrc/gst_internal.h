@@ -310,6 +310,7 @@ struct Chain64Launch {
   double* rec_f;             // [zero_rec + 1][64]: the states before each entry's columns with a chain, entry
                              // by entry, then a row of zeros (null: not recorded)
   double* fin;               // [S][64], in `order`: final states (forward), seeds (reverse)
+  unsigned long long* nonpos;  // forward: cleared
   int M;                     // reverse: width of the head rows, 1 + 64 + 64 M
   double* head;              // reverse: [gridDim.x] head rows, [0 | dL/drho | 0]
   double* dg;                // reverse: [K][gridDim.x][4096]: each workgroup's dL/dG
@@ -402,6 +403,15 @@ int readout64_blocks_per_cu();
 hipError_t launch_chain64_fwd(const Chain64Launch& a, int n_blocks, hipStream_t stream);
 hipError_t launch_chain64_bwd(const Chain64Launch& a, int n_blocks, hipStream_t stream);
 hipError_t launch_reduce64(const Reduce64Launch& a, hipStream_t stream);
+struct HeadSum64 {           // ordered sum of head rows [objective | rho | E]
+  const double* head;        // [n_rows][P]
+  int n_rows, n_part, per;   // n_part parts of `per` rows
+  int64_t P;
+  double* part;              // [n_part][P]
+  double* objective;
+  double* grad;
+};
+hipError_t launch_head_sum64(const HeadSum64& a, const Reduce64Launch& gates, hipStream_t stream);
 
 // One request of a batched launch of three-qubit grouped-chain plans: the
 // arguments of its standalone launch sequence.  The batched kernels take

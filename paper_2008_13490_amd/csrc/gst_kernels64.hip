@@ -81,19 +81,46 @@ constexpr int SLOTS = 2 * (SCHED_CHAINS + 1);
 __device__ __forceinline__ int state_at(int j) { return (j & 3) * SKS + (j >> 2); }
 
 // Operands of G (or, TR, of its transpose) for the 4x4x4 MFMA: lane 16k + 4b + i
-// holds rows 16w + 4b + i, columns 4s + k, s = 0 .. 15.
+// holds rows 16w + 4b + i, columns 4s + k, s = 0 .. 15.  Columns of G^T are read from
+// memory as they are; rows of G through LDS, since one load of sixteen rows takes
+// sixteen cache lines (that alone was 12 us of the launch, for a list of one word of
+// 16 gates as for one of 8,000: 20 -> 9 and 174 -> 163 us).
+constexpr int GST = N64 + 2;  // stride (doubles) of a staged gate's rows
 template <bool TR>
 struct SchedGates {
   double g[5][16];
-  __device__ __forceinline__ void load(const double* G, int K, int w, int l) {
+  __device__ __forceinline__ void load_columns(const double* G, int K, int w, int l) {
+    static_assert(TR, "the transposed gates");
     const auto* p = as_global(G);
-    const int row = 16 * w + (l & 15), k = l >> 4;
 #pragma unroll
     for (int x = 0; x < 5; ++x)
       if (x < K) {
 #pragma unroll
-        for (int s = 0; s < 16; ++s)
-          g[x][s] = TR ? p[x * GATE64 + (4 * s + k) * N64 + row] : p[x * GATE64 + row * N64 + 4 * s + k];
+        for (int s = 0; s < 16; ++s) g[x][s] = p[x * GATE64 + (4 * s + (l >> 4)) * N64 + 16 * w + (l & 15)];
+      }
+  }
+  // 512 threads; T: a gate in LDS
+  __device__ __forceinline__ void load_rows(const double* G, int K, int w, int l, double* T) {
+    static_assert(!TR, "the gates themselves");
+    const auto* p = as_global(reinterpret_cast<const d2*>(G));
+    const int t = threadIdx.x;
+    d2 in[5][4];
+#pragma unroll
+    for (int x = 0; x < 5; ++x)
+      if (x < K) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) in[x][u] = p[x * (GATE64 / 2) + t + 512 * u];
+      }
+#pragma unroll
+    for (int x = 0; x < 5; ++x)
+      if (x < K) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          *reinterpret_cast<d2*>(T + ((t + 512 * u) >> 5) * GST + 2 * (t & 31)) = in[x][u];
+        lds_barrier();
+#pragma unroll
+        for (int s = 0; s < 16; ++s) g[x][s] = T[(16 * w + (l & 15)) * GST + 4 * s + (l >> 4)];
+        lds_barrier();
       }
   }
 };
@@ -178,14 +205,18 @@ __device__ __forceinline__ LiveSum sched_live_sum(int own) {
 // 4 .. 7 its second.
 __global__ __launch_bounds__(512, 2) void chain64_fwd_kernel(const Chain64Launch a) {
   __shared__ __align__(16) double V[SLOTS * SST];
+  __shared__ __align__(16) double T[N64 * GST];  // a gate on its way into registers
   const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3, z = wave >> 2;
   SchedGates<false> gates;
-  gates.load(a.G, a.K, w, l);
+  gates.load_rows(a.G, a.K, w, l, T);
   const double rho = as_global(a.rho)[l];
   const auto* entries = as_global(a.entries);
   auto* rec = as_global(a.rec_f);
   auto* fin = as_global(a.fin);
-  if (a.rec_f && blockIdx.x == 0 && wave == 0) rec[(int64_t)a.zero_rec * N64 + l] = 0.0;
+  if (blockIdx.x == 0 && wave == 0) {
+    if (a.rec_f) rec[(int64_t)a.zero_rec * N64 + l] = 0.0;
+    if (l == 0) *a.nonpos = 0ull;  // (the readout counts)
+  }
   int at = blockIdx.x;
   for (int tile = next_tile(at, a.tile_row, a.n_tiles); tile < a.n_tiles; tile = next_tile(at, a.tile_row, a.n_tiles)) {
     const int64_t q0 = (int64_t)tile * a.tile_seqs;
@@ -247,7 +278,7 @@ __global__ __launch_bounds__(512, 2) void chain64_bwd_kernel(const Chain64Launch
   if (wave < 4) {
     __builtin_amdgcn_s_setprio(2);  // the chains are what a round waits for
     SchedGates<true> gates;
-    gates.load(a.G, a.K, w, l);
+    gates.load_columns(a.G, a.K, w, l);
     const auto* fin = as_global(a.fin);
     double drho = 0.0;
     int at = blockIdx.x;
@@ -418,6 +449,20 @@ __device__ __forceinline__ void reduce64_body(const Reduce64Launch& a, int64_t b
 }
 
 __global__ __launch_bounds__(256) void reduce64_kernel(const Reduce64Launch a) { reduce64_body(a, blockIdx.x); }
+
+// Word lists: the head rows in two ordered stages, the second one's launch with the
+// gate columns too (a list of one word of 16 gates 41.0 -> 39.3 us).
+__global__ __launch_bounds__(256) void head_sum64_stage1(const HeadSum64 a) {
+  slab_sum_stage1(a.head, a.n_rows, a.P, a.per, a.part, blockIdx.x, blockIdx.y);
+}
+
+__global__ __launch_bounds__(256) void head_sum64_stage2(const HeadSum64 a, const Reduce64Launch gates) {
+  const int64_t head = (a.P + 63) / 64;
+  if ((int64_t)blockIdx.x < head)
+    slab_sum_stage2(a.part, a.n_part, a.P, a.objective, a.grad, nullptr, N64, blockIdx.x);
+  else
+    reduce64_body(gates, blockIdx.x - head);
+}
 
 // ---------------------------------------------------------------------------
 // The grouped-chain plan (gst_plan64.h).
@@ -1456,7 +1501,7 @@ static bool chain64_ok(const Chain64Launch& a, int n_blocks) {
 }
 
 hipError_t launch_chain64_fwd(const Chain64Launch& a, int n_blocks, hipStream_t stream) {
-  if (!chain64_ok(a, n_blocks)) return hipErrorInvalidValue;
+  if (!chain64_ok(a, n_blocks) || !a.nonpos) return hipErrorInvalidValue;
   gst_launch(chain64_fwd_kernel, dim3(n_blocks), dim3(512), 0, stream, a);
   return hipGetLastError();
 }
@@ -1517,6 +1562,14 @@ hipError_t launch_slab_sum64_batch(const Plan64Req* reqs, int n, int grid_x, int
 hipError_t launch_reduce64_batch(const Plan64Req* reqs, int n, int grid_x, hipStream_t stream) {
   if (n <= 0 || grid_x <= 0) return hipSuccess;
   gst_launch(reduce64_batch, dim3(grid_x, n), dim3(256), 0, stream, reqs);
+  return hipGetLastError();
+}
+
+hipError_t launch_head_sum64(const HeadSum64& a, const Reduce64Launch& gates, hipStream_t stream) {
+  if (a.n_rows < 1 || a.n_part < 1 || a.n_part > 64 || (int64_t)a.per * a.n_part < a.n_rows) return hipErrorInvalidValue;
+  const unsigned head = (unsigned)((a.P + 63) / 64);
+  gst_launch(head_sum64_stage1, dim3(head, (unsigned)a.n_part), dim3(256), 0, stream, a);
+  gst_launch(head_sum64_stage2, dim3(head + (gates.grad ? gates.K * (GATE64 / 64) : 0)), dim3(256), 0, stream, a, gates);
   return hipGetLastError();
 }
 
