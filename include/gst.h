@@ -166,6 +166,12 @@ int gst_req_create(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes, cons
                    const int32_t* counts, gst_req** out);
 /* Device bytes held by the request (plan, copies of the inputs, workspace). */
 int gst_req_footprint(const gst_req* req, size_t* bytes);
+/* At most this many bytes will a request with counts of n_seq sequences and n_steps
+   gates in all hold, if the list gets no sharing plan (admission before anything is
+   allocated).  With `ctx` under its tile policy, with NULL the default one; needs no
+   device. */
+int gst_req_estimate(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes, int64_t n_seq, int64_t n_steps,
+                     size_t* bytes);
 /* Evaluate at gate set `theta`; same outputs and conventions as gst_loglik. */
 int gst_req_eval(gst_req* req, const gst_gateset* theta, double* probs, double* objective,
                  double* grad);

@@ -355,12 +355,28 @@ static int readout_blocks_of(const gst_ctx* ctx, int64_t n) {
                                 (int64_t)gst::readout64_blocks_per_cu() * ctx->n_cu);
 }
 
-// A three-qubit request without a plan: its head rows, and the context
-// workspace of an evaluation with the gradient (the workgroups' dL/dG, the
-// recorded states).
+// A three-qubit request without a plan: the tiles of its schedule, its head rows, and
+// the context workspace of an evaluation with the gradient (the workgroups' dL/dG,
+// the recorded states).
+struct Shape64 {
+  int tile_seqs, blocks;
+  int64_t n_tiles;
+};
+// Tiles of a grouped schedule, two per CU (there and back over the lengths) until
+// the tiles are full.
+static Shape64 shape64(const gst_ctx* ctx, int64_t S) {
+  const int n_cu = ctx ? ctx->n_cu : 256;
+  const int64_t per = (S + 2 * n_cu - 1) / (2 * n_cu);
+  const int64_t want = ctx && ctx->tune_tile[3] > 0 ? ctx->tune_tile[3] : per;
+  Shape64 s;
+  s.tile_seqs = (int)std::min<int64_t>(std::max<int64_t>(want, 1), gst::SCHED_CHAINS);
+  s.n_tiles = (S + s.tile_seqs - 1) / s.tile_seqs;
+  s.blocks = (int)std::min<int64_t>(s.n_tiles, n_cu);
+  return s;
+}
 static int head_rows64(const gst_req* r) { return r->readout_blocks64 * gst::READOUT64_WAVES + r->blocks64; }
-static size_t chain64_ws_bytes(const gst_req* r) {
-  return ((size_t)r->K * r->blocks64 * 4096 + (size_t)(r->n_steps + 1) * 64) * 8 + 256;
+static size_t chain64_ws_bytes(int K, int blocks, int64_t n_steps) {
+  return ((size_t)K * blocks * 4096 + (size_t)(n_steps + 1) * 64) * 8 + 256;
 }
 
 // The grouped schedule of a request's words (tile_rec: the steps of the tiles
@@ -460,7 +476,7 @@ static bool group_is_lane(int g) { return g >= 2; }
 // granularity: 64 for the lane kernel, 16 for the team kernels) or the
 // default.  Fixed into the request when it is created.
 static int64_t tile_seqs_of_group(const gst_ctx* ctx, int g, int64_t S) {
-  const int t = ctx->tune_tile[g == 0 ? 2 : 1];
+  const int t = ctx ? ctx->tune_tile[g == 0 ? 2 : 1] : 0;
   const int64_t gran = group_is_lane(g) ? 64 : 16;
   if (t > 0) return (t + gran - 1) / gran * gran;
   return group_is_lane(g) ? 64 : tile_seqs_for(S);
@@ -1658,8 +1674,7 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   }
   std::vector<gst::BatchTile> tiles = gst::batch_tiles({&r->tile_q}, {&r->tile_cost}, {0});
   const int64_t Pw = gst::slab_width(D, n_outcomes, n_gates);
-  // three-qubit requests without deep sharing: tiles of a grouped schedule, two
-  // per CU (there and back over the lengths) until the tiles are full
+  // three-qubit requests without deep sharing: tiles of a grouped schedule
   std::vector<int64_t> gcp64;
   // three-qubit lists with deep sharing: the grouped-chain plan instead
   gst::Plan64 p64;
@@ -1667,11 +1682,10 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   if (D == 64) opt64.ts_blocks = gst::gemm64_ts_blocks_per_cu() * ctx->n_cu;
   const bool use_p64 = D == 64 && S > 0 && gst::build_plan64(sl->offsets, sl->gate_idx, S, n_gates, opt64, &p64);
   if (D == 64 && !use_p64) {
-    const int64_t per = (S + 2 * ctx->n_cu - 1) / (2 * ctx->n_cu);
-    const int64_t want = ctx->tune_tile[3] > 0 ? ctx->tune_tile[3] : per;
-    r->sched.tile_seqs = (int)std::min<int64_t>(std::max<int64_t>(want, 1), gst::SCHED_CHAINS);
-    r->sched.n_tiles = (S + r->sched.tile_seqs - 1) / r->sched.tile_seqs;
-    r->blocks64 = (int)std::min<int64_t>(r->sched.n_tiles, ctx->n_cu);
+    const Shape64 shape = shape64(ctx, S);
+    r->sched.tile_seqs = shape.tile_seqs;
+    r->sched.n_tiles = shape.n_tiles;
+    r->blocks64 = shape.blocks;
     r->readout_blocks64 = readout_blocks_of(ctx, S);
     for (int k = 0; k <= n_gates; ++k) gcp64.push_back((int64_t)k * r->blocks64);
   }
@@ -1732,7 +1746,7 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
     for (int64_t t = 0; t < r->sched.n_tiles; ++t) tile_rec[t + 1] += tile_rec[t];
     rc = build_schedule(r.get(), tile_rec);
     if (rc) return rc;
-    if (D == 64) r->eval_ws_bytes = chain64_ws_bytes(r.get());
+    if (D == 64) r->eval_ws_bytes = chain64_ws_bytes(r->K, r->blocks64, r->n_steps);
   }
   r->resident_bytes = r->data.bytes + r->plan.buf.bytes + r->plan64.buf.bytes + r->sched.buf.bytes;
   (void)o_off;
@@ -1774,6 +1788,34 @@ int gst_req_create(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes, cons
   const int32_t zero = 0;
   return gst_req_create_host(ctx, n_qubits, n_gates, n_outcomes, &h,
                              counts ? (c.empty() ? &zero : c.data()) : nullptr, out);
+}
+
+// The arrays of gst_req_create_host (and build_schedule) for a list that gets no
+// plan, each at its largest; a context's workspace grows by half of itself at least.
+int gst_req_estimate(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes, int64_t n_seq, int64_t n_steps,
+                     size_t* bytes) {
+  if (!bytes) return fail(GST_EINVAL, "bytes is NULL");
+  const int D = dim_of(n_qubits);
+  if (!D) return fail(GST_EINVAL, "n_qubits must be 1, 2 or 3");
+  if (n_gates < 1 || n_gates > gst_max_gates(n_qubits)) return fail(GST_EINVAL, "n_gates out of range");
+  if (n_outcomes < 1 || n_outcomes > std::min(D, 16)) return fail(GST_EINVAL, "n_outcomes must be in 1..min(D, 16)");
+  if (n_seq < 0 || n_steps < 0) return fail(GST_EINVAL, "n_seq and n_steps >= 0 required");
+  const size_t S = (size_t)n_seq, L = (size_t)n_steps, M = (size_t)n_outcomes;
+  size_t b = 16 * (S + 1) + L + 4 * S * M + 8192;  // offsets, order, gate indices, counts; the arrays' ends
+  if (D == 64) {
+    const Shape64 h = shape64(ctx, n_seq);
+    const size_t rows = (size_t)h.blocks + gst::READOUT64_WAVES * (S / (16 * gst::READOUT64_WAVES) + 1);
+    const size_t Pc = 1 + 64 + M * 64;
+    b += S * 512 + (rows + gst::reduce_parts((int)std::min<size_t>(rows, 1 << 20))) * Pc * 8;
+    b += 16 * ((size_t)h.n_tiles + 1) + 4 * (2 * L + 4 * (size_t)h.n_tiles + 1);
+    b += chain64_ws_bytes(n_gates, h.blocks, n_steps) / 2 * 3;
+  } else {
+    const int64_t t = tile_seqs_of_group(ctx, tile_group(D, n_gates), n_seq);
+    const size_t tiles = (size_t)((n_seq + t - 1) / t);
+    b += std::max<size_t>(tiles, 1) * gst::slab_width(D, n_outcomes, n_gates) * 8 + (tiles + 1) * sizeof(gst::BatchTile);
+  }
+  *bytes = b;
+  return GST_OK;
 }
 
 int gst_req_footprint(const gst_req* req, size_t* bytes) {
@@ -1866,7 +1908,7 @@ static int run64(gst_req* r, const gst_gateset* th, int mode, const double* w, d
   // context are stream ordered); without the gradient nothing is allocated
   double *fin = r->fin64, *dg = nullptr, *rec = nullptr;
   if (want_grad) {
-    int rc = ctx->ws.reserve(chain64_ws_bytes(r), ctx->stream);
+    int rc = ctx->ws.reserve(chain64_ws_bytes(r->K, r->blocks64, r->n_steps), ctx->stream);
     if (rc) return rc;
     dg = reinterpret_cast<double*>(ctx->ws.p);
     rec = dg + (size_t)r->K * r->blocks64 * 4096;

@@ -53,25 +53,15 @@ class Job:
     handle: Any = None          # engine state while admitted
 
 
-def tile_seqs(S: int) -> int:
-    """Sequences per tile of the one- and two-qubit tile kernel (as the library cuts them)."""
-    per = (S + 16 * 1024 - 1) // (16 * 1024)
-    return 16 * min(max(per, 1), 8)
-
-
-def footprint_estimate(n_qubits: int, K: int, M: int, S: int, sum_len: int) -> int:
-    """Device bytes a request will hold (inputs, tile partials, three-qubit
-    step records and positions); used to admit before allocating."""
-    D = 4 ** n_qubits
-    b = 8 * (S + 1) + sum_len + 4 * S * M + 8 * (S + 1) + 4096
-    if D == 64:
-        n_tiles = (S + 15) // 16
-        b += n_tiles * (1 + 64 + 64 * M) * 8 + 8 * sum_len + (sum_len // 8192 + K + 1) * 4096 * 8
-        b += sum_len * 64 * 8 * 2           # per-step records of one evaluation
-    else:
-        n_tiles = (S + tile_seqs(S) - 1) // tile_seqs(S)
-        b += n_tiles * (1 + D + M * D + K * D * D) * 8 + n_tiles * 24
-    return int(b)
+def footprint_estimate(n_qubits: int, K: int, M: int, S: int, sum_len: int, ctx=None) -> int:
+    """Device bytes a request will hold (inputs, tile partials, three-qubit schedules, final states and
+    workspace), as the library sizes them (``gst_req_estimate``); used to admit before allocating."""
+    import ctypes
+    from . import _lib
+    b = ctypes.c_size_t()
+    lib = _lib.load()
+    _lib.check(lib.gst_req_estimate(None if ctx is None else ctx.handle, n_qubits, K, M, S, sum_len, ctypes.byref(b)))
+    return int(b.value)
 
 
 def step_cost(n_qubits: int) -> float:
@@ -298,7 +288,7 @@ class _LibEngine:
     def estimate(self, j: Job) -> int:
         d = j.data
         g = d.iterates[0]
-        return footprint_estimate(g.n_qubits, g.K, g.M, d.seqs.S, int(d.seqs.offsets[-1]))
+        return footprint_estimate(g.n_qubits, g.K, g.M, d.seqs.S, int(d.seqs.offsets[-1]), self.ctx)
 
     def work(self, j: Job) -> float:
         return step_cost(j.data.iterates[0].n_qubits) * float(j.data.seqs.offsets[-1])
