@@ -440,7 +440,6 @@ struct gst_batch {
     int item_grid = 0, gemm_grid = 0, red_x = 0, red_stage1 = 1;
     gst::PlanBatch dev{};
   } pgroup[2];
-  DevBuf plan_ws;                       // the batched plans' scratch, one region per request
   // one group of tiles per tile kernel (see TileKind), each with its own queue
   int n_tiles[6] = {0, 0, 0, 0, 0, 0}, grid_of[6] = {0, 0, 0, 0, 0, 0};
   gst::BatchLaunch launch[6] = {};
@@ -1201,9 +1200,10 @@ void plan_setup(gst_req* r, const gst_gateset* th, int mode, const double* w, do
   g.BA = d.BA;
 }
 
-// The scratch of a plan request's evaluations, sized for one with the gradient:
-// allocated with the request, so that its first evaluation waits for no
-// allocation (30 us of 140 on a two-qubit fit's first).
+// The scratch of a plan request's evaluations, sized for one with the gradient (no
+// evaluation needs more, so it never moves again): allocated with the request, so
+// that its first evaluation waits for no allocation (30 us of 140 on a two-qubit fit's
+// first), and used by its evaluations in batches too.
 int reserve_plan_ws(gst_req* r) {
   const gst_gateset none{};
   double unused = 0.0;
@@ -1731,8 +1731,14 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
     opt.jump = ctx->plan_jump;
     if (gst::build_plan(sl->offsets, sl->gate_idx, S, n_gates, opt, &hp)) {
       rc = upload_plan(r.get(), hp, counts_host);
-      if (rc == GST_OK) rc = reserve_plan_ws(r.get());
       if (rc) return rc;
+      // (a request that never needs it is not refused for want of it: the first
+      // evaluation tries again)
+      const std::string err = g_err;
+      if (reserve_plan_ws(r.get()) != GST_OK) {
+        (void)hipGetLastError();
+        g_err = err;
+      }
     }
   }
   if (use_p64) {
@@ -2205,12 +2211,12 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
     if (!bad.empty()) return fail(GST_EINVAL, "internal: batch tile list: " + bad);
   }
   b->n_items = (int)items.size();
-  // batched plans: each request's launch arguments, its scratch region in
-  // plan_ws, and its level tables (trunk ranges, reverse head rows, slot ranges)
+  // batched plans: each request's launch arguments (its own scratch, as alone: its
+  // arenas are its own too, so it runs once at a time on the context's stream), and
+  // its level tables (trunk ranges, reverse head rows, slot ranges)
   std::vector<PlanSetup> psetup[2];
   std::vector<int64_t> lvl_tab[2];
-  std::vector<size_t> ws_at[2], lvl_at[2];
-  size_t ws_total = 0;
+  std::vector<size_t> lvl_at[2];
   for (int gi = 0; gi < 2; ++gi) {
     gst_batch::PlanGroup& pg = b->pgroup[gi];
     pg.D = gi == 1 ? 16 : 4;
@@ -2223,8 +2229,8 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
       PlanSetup& st = psetup[gi][y];
       plan_setup(r, &b->thetas[x], b->objectives[x] ? gst::MODE_LOGLIK : gst::MODE_PROBS, nullptr, b->probs[x],
                  b->objectives[x], b->grads[x], nullptr, &st);
-      ws_at[gi].push_back(ws_total);
-      ws_total += (st.ws_bytes() + 255) / 256 * 256;
+      int rc = reserve_plan_ws(r);
+      if (rc) return rc;
       lvl_at[gi].push_back(lvl_tab[gi].size());
       for (int l = 0; l <= P.n_levels; ++l) lvl_tab[gi].push_back(P.trunk_level_ptr[l]);
       for (int l = 0; l < P.n_levels; ++l) lvl_tab[gi].push_back(st.tb_at[l]);
@@ -2276,10 +2282,6 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
       pg.item_grid = std::max(pg.item_grid, st.a.item_blocks + st.a.fill_blocks);
     }
   }
-  if (ws_total > 0) {
-    int rc = b->plan_ws.reserve(ws_total, ctx->stream);
-    if (rc) return rc;
-  }
   Carver cv;
   size_t o_t[6], o_pa[2], o_pi[2], o_pg[2], o_pr[2], o_pl[2];
   const size_t o_rq = cv.take<gst::BatchReq>(rq.size() + 1);
@@ -2309,7 +2311,7 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
       PlanSetup& st = psetup[gi][y];
       const int x = plan_x[gi][y];
       const int L = b->reqs[x]->plan.host.n_levels;
-      st.bind((char*)b->plan_ws.p + ws_at[gi][y]);
+      st.bind(b->reqs[x]->ws.p);
       st.a.req_nonpos = reinterpret_cast<unsigned long long*>(base + o_np) + x;
       st.a.lvl_trunk = lvl + lvl_at[gi][y];
       st.a.lvl_head = lvl + lvl_at[gi][y] + (L + 1);
