@@ -228,8 +228,11 @@ int gst_batch_destroy(gst_batch* batch);
  * requests created afterwards on this context (a request keeps the tile cut
  * it was created with, so its results stay the same alone and in any
  * batch).  seqs_per_tile is rounded up to the kernel's granularity (64 for
- * one qubit with at most four gates, else 16; any value for three qubits);
- * 0 restores the default.  blocks_per_cu = 0 uses as many as fit.
+ * one qubit with at most four gates, 16 for the other one- and two-qubit
+ * kernels; three qubits: 1 to 16, more is taken as 16); 0 restores the default,
+ * which for three qubits depends on the list (tiles for two workgroups per CU, at
+ * most 16 sequences).  blocks_per_cu = 0 uses as many as fit; the three-qubit
+ * kernels run at most one workgroup per CU whatever it is.
  */
 int gst_tune_set(gst_ctx* ctx, int n_qubits, int seqs_per_tile, int blocks_per_cu);
 

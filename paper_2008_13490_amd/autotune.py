@@ -22,11 +22,13 @@ import numpy as np
 from . import api
 from . import workloads as W
 
-# candidate (sequences per tile, workgroups per CU; 0 = as many as fit)
+# candidate (sequences per tile, 0 = the library's rule; workgroups per CU, 0 = as many as fit); the first one
+# stays unless another is faster.  Three qubits: the rule gives short lists small tiles, up to sixteen words (the
+# most a tile takes), so a fixed size has to beat it; the kernels run one workgroup per CU.
 CANDIDATES = {
     1: [(64, 0), (128, 0), (256, 0), (64, 1)],
     2: [(16, 0), (32, 0), (64, 0), (16, 1), (32, 1)],
-    3: [(4, 0), (8, 0), (16, 0), (32, 0)],
+    3: [(0, 0), (4, 0), (8, 0), (16, 0)],
 }
 
 
