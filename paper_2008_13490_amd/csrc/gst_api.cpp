@@ -485,8 +485,11 @@ static int group_family(int g) { return g == 0 ? FAM_TILES16 : FAM_TILES4; }
 // Workgroups of a launch over n tiles (lane kernel: four waves, one tile each).
 static int capped(int bpc, int cap) { return cap > 0 ? std::min(bpc, cap) : bpc; }
 
-// A launch of n workgroups' worth of tiles that two per CU hold.
-static bool few_tiles(const gst_ctx* ctx, int64_t n) { return n <= 2 * (int64_t)ctx->n_cu; }
+// Launches of the team kernels that load rows ahead (see seq_waves in gst_seq.h): n
+// workgroups of the plain kernel that run at once, or n tiles of the persistent one,
+// whose workgroups take the third of a CU when they are done.
+static bool few_blocks(const gst_ctx* ctx, int64_t n) { return n <= 2 * (int64_t)ctx->n_cu; }
+static bool few_tiles(const gst_ctx* ctx, int64_t n) { return n <= 3 * (int64_t)ctx->n_cu; }
 
 static int group_grid(gst_ctx* ctx, int g, int kmax, int64_t n) {
   if (n <= 0) return 0;
@@ -590,7 +593,7 @@ int enqueue_leaf(gst_ctx* ctx, const gst::LeafLaunch& base, int64_t max_len, dou
   a.ckpt = a.want_grad ? reinterpret_cast<double*>((char*)buf + z.slab_bytes + z.part_bytes) : nullptr;
   const int64_t ck_team = z.ck_team;
   a.ckpt_per_team = ck_team;
-  a.few = few_tiles(ctx, blocks) ? 1 : 0;
+  a.few = few_blocks(ctx, blocks) ? 1 : 0;
   a.max_len = (int)max_len;
   a.status = ctx->status;
   if (max_len > (int64_t)1 << 30) return fail(GST_EINVAL, "sequence too long");

@@ -161,7 +161,7 @@ size_t batch_lds(int kmax) { return batch_lds_bytes(kmax); }
 // Accumulators for six gates cover the two-qubit configurations; with more the
 // gate set leaves room for two workgroups per CU, and one-qubit requests come
 // here with more than four gates only: those load ahead whatever their number.
-// `few`: the launch's tiles fill at most two workgroups per CU.
+// `few`: the variant that loads rows ahead.
 int batch_blocks_per_cu(int D, int kmax, bool few) {
   int n = 0;
   const size_t bytes = batch_lds_bytes(kmax);

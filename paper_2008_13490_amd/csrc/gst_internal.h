@@ -38,7 +38,7 @@ enum Mode : int { MODE_PROBS = 0, MODE_LOGLIK = 1, MODE_VJP = 2 };
 // at rho and applies its gates in time order.
 struct LeafLaunch {
   int D, M, K;                 // D = 4^n (4, 16 or 64)
-  int few;                     // at most two workgroups per CU: the variant that loads rows ahead
+  int few;                     // the variant that loads rows ahead
   const double* rho;           // [D]
   const double* E;             // [M][D]
   const double* G;             // [K][D][D]
@@ -231,7 +231,7 @@ struct BatchLaunch {
   BatchReq one;
   const BatchTile* tiles;
   int n_tiles;
-  int few;                         // at most two workgroups per CU: the variant that loads rows ahead
+  int few;                         // the variant that loads rows ahead
   unsigned* queue;
   double* ckpt;
   int64_t ckpt_per_team;

@@ -30,9 +30,15 @@ namespace {
 
 // Waves per SIMD.  A launch that fills the chip with three runs each step's row
 // loads when they are needed and leaves the waiting to the other waves; one of
-// at most two loads every row a step ahead (PRE), which takes 64 more
-// registers.  Both do the same operations in the same order.  3,001 words, vjp:
-// 93 us without loading ahead, 78 with; 30,000 words: 301 and 328 us.
+// fewer loads every row a step ahead (PRE), which takes 64 more registers and leaves
+// room for two.  Both do the same operations in the same order.  Where the line
+// lies, in us without and with loading ahead:
+//   tile kernel, words of up to 256 gates: 4,000 words 145, 129; 8,192 (two tiles per CU)
+//     158, 146; 10,000 168, 149; 12,000 (2.9) 177, 152; 16,000 189, 199; 30,000 285, 321.
+//     Its workgroups are persistent: loading ahead is the faster one up to three tiles
+//     per CU, although only two run at once.
+//   plain kernel, up to 64 gates: 2,000 words 43, 40; 8,192 (two workgroups per CU) 55.4,
+//     54.6; 8,300 65, 75; 12,000 70, 88.  A third workgroup would wait for a whole one.
 constexpr int seq_waves(bool pre) { return pre ? 2 : 3; }
 
 // A wave's partial sums.  Tile element (r, c) of dE (outcome r) and dG is in
