@@ -182,7 +182,7 @@ def cpu_baseline(name: str, seconds: float, workers: int, param: str = "full"):
 # while this file and the headers it includes are unchanged)
 FAMILY_SOURCE = {
     "leaf": ["gst_plan_kernels.hip"], "trunk_fwd": ["gst_plan_kernels.hip"], "trunk_bwd": ["gst_plan_kernels.hip"],
-    "inject": ["gst_plan_kernels.hip"], "fill": ["gst_plan_kernels.hip"], "grad_gemm": ["gst_plan_kernels.hip"],
+    "inject": ["gst_plan_kernels.hip"], "grad_gemm": ["gst_plan_kernels.hip"],
     "reduce": ["gst_plan_kernels.hip"], "tiles_3q_fwd": ["gst_kernels64.hip"], "tiles_3q_bwd": ["gst_kernels64.hip"],
     "readout_3q": ["gst_kernels64.hip"], "gemm_3q": ["gst_kernels64.hip"],
     "reduce_3q": ["gst_kernels64.hip", "gst_kernels.hip"], "chain_3q": ["gst_kernels64.hip", "gst_sched.hip"],
@@ -536,7 +536,7 @@ def run_structured(args):
                                               ctypes.byref(seqs.as_struct()), api._ptr(counts), None,
                                               api._ptr(obj), api._ptr(grad)))
 
-    families = ("leaf", "reduce", "trunk_fwd", "trunk_bwd", "inject", "grad_gemm", "fill", "tiles_2q", "tiles_1q",
+    families = ("leaf", "reduce", "trunk_fwd", "trunk_bwd", "inject", "grad_gemm", "tiles_2q", "tiles_1q",
                 "tiles_reduce", "chain_3q", "gemm_3q", "reduce_3q", "tiles_3q_fwd", "tiles_3q_bwd", "readout_3q",
                 "param_fwd", "param_bwd")
     for _ in range(args.warmup):
@@ -863,7 +863,7 @@ def run_fit_bench(args):
     warm = 1 if args.warmup == 20 else args.warmup
     for _ in range(warm):
         one_fit()
-    families = ("leaf", "reduce", "trunk_fwd", "trunk_bwd", "inject", "grad_gemm", "fill", "tiles_2q", "param_fwd",
+    families = ("leaf", "reduce", "trunk_fwd", "trunk_bwd", "inject", "grad_gemm", "tiles_2q", "param_fwd",
                 "param_bwd")
     torch.cuda.synchronize()
     t0 = time.perf_counter()

@@ -98,9 +98,8 @@ typedef struct gst_diag {
 } gst_diag;
 
 /* Largest K supported for a qubit count: 8 for one and two qubits (the
-   on-chip gradient tiles of the tile kernels), 5 for three (the gate set of
-   the per-sequence kernel fills the 160 KB of LDS of a CU); 0 for other qubit
-   counts.  Every call given more gates returns GST_EINVAL. */
+   on-chip gradient tiles of the tile kernels), 5 for three (a wave holds its
+   operands of all gates in registers); 0 for other qubit counts.  Every call given more gates returns GST_EINVAL. */
 int gst_max_gates(int n_qubits);
 
 /* Create a context on device `device_ordinal` that enqueues work on
@@ -241,9 +240,9 @@ int gst_tune_set(gst_ctx* ctx, int n_qubits, int seqs_per_tile, int blocks_per_c
  * this context.  Germ-power sequences (thesis Eq. GSTFullFiducialsGerms) put
  * long runs of one repeated germ on a trunk.  With reps > 0 the trunk chain
  * applies such a run `reps` repetitions at a time with the matrix power of
- * the germ (built per evaluation in LDS by repeated squaring), and independent
- * fill tasks compute the states and adjoints inside each jump; this shortens
- * the sequential chain several times over.  The states after a jump carry the
+ * the germ (built per evaluation in LDS by repeated squaring); independent fill
+ * tasks compute the states inside each jump, and the gradient's kernel the
+ * adjoints there; this shortens the sequential chain several times over.  The states after a jump carry the
  * rounding of the matrix products, so probabilities agree with the plain
  * evaluation to rounding (a few 1e-13 relative on the germ-power lists)
  * instead of bit for bit.  reps = 0 turns jumps off (bit-identical
@@ -431,10 +430,11 @@ int gst_hamiltonian_decomposition_target(int n_qubits, const double* G, const do
  * kernel also counts for the families enclosing it ("batch").
  * gst_profile_read synchronizes the stream and returns, for the kernel family
  * `kernel` ("leaf", "reduce", "trunk_fwd", "trunk_bwd", "inject",
- * "grad_gemm", "fill", "tiles_2q", "tiles_1q", "tiles_reduce",
- * "chain_3q", "gemm_3q", "reduce_3q", "predict_chain", "predict_fill",
- * "tv_distance", "param_fwd", "param_bwd", or "batch" for a whole
- * gst_batch_run), the summed
+ * "grad_gemm", "tiles_2q", "tiles_1q", "tiles_reduce", "chain_3q",
+ * "tiles_3q_fwd", "tiles_3q_bwd", "readout_3q", "gemm_3q", "reduce_3q",
+ * "predict_chain", "predict_fill", "tv_distance", "param_fwd", "param_bwd",
+ * or "batch" for a whole gst_batch_run; "fill" has no launch of its own and
+ * reads zero), the summed
  * elapsed milliseconds and the number of kernels since profiling was
  * enabled; the counters are not reset by reading.
  */

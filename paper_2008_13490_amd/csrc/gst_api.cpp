@@ -139,7 +139,9 @@ struct Profiler {
 
 enum Family { FAM_LEAF = 0, FAM_REDUCE = 1, FAM_TRUNK_FWD = 2, FAM_TRUNK_BWD = 3, FAM_INJECT = 4, FAM_GEMM = 5,
               FAM_BATCH = 6, FAM_TILES16 = 7, FAM_TILES4 = 8, FAM_TILES_RED = 9, FAM_CHAIN64 = 10,
-              FAM_GEMM64 = 11, FAM_REDUCE64 = 12, FAM_FILL = 13, FAM_PRED_CHAIN = 14,
+              FAM_GEMM64 = 11, FAM_REDUCE64 = 12,
+              FAM_FILL = 13,  // (the fill tasks run in the items' launch: this name reads zero)
+              FAM_PRED_CHAIN = 14,
               FAM_PRED_FILL = 15, FAM_TV = 16, FAM_PARAM_FWD = 17, FAM_PARAM_BWD = 18, FAM_P64_FWD = 19,
               FAM_P64_BWD = 20, FAM_P64_READ = 21, FAM_N = 22 };
 static_assert(FAM_N <= Profiler::kMaxFamilies, "profiler arrays too small");
@@ -262,7 +264,14 @@ struct DevicePlan {
 // Levels whose longest chain has at least this many steps run the sweeps four
 // chains to a workgroup with the gate operands held in registers (loaded once);
 // the others sixteen, loading each step's operands (a tile of a few steps would
-// load all K gates for nothing).
+// load all K gates for nothing).  A level has one kind: its short tiles run with
+// the long ones' kernel.  Evaluations in us with the line at 16, 32, 64 steps and with
+// no such levels: the list of 200,960 sequences 437, 437, 437, 568; 73 germs of
+// three, powers to 16 (longest 50) 447, 398, 459, 460; 40 fiducials, powers 1, 8 and 16
+// 918, 798, 816, 816.  Where a list's longest chain has 16 to 31 steps, 16 is the
+// better one (powers 5 to 7: 230, 401, 401, 401), but on large lists the short
+// levels of many tiles that it takes in as well cost more (powers to 8, 40
+// fiducials: 1477, 1101, 1145, 1147).
 constexpr int kRegGateSteps = 32;
 
 // Device copy of a three-qubit grouped-chain plan (gst_plan64.h) with its
@@ -275,7 +284,7 @@ struct DevicePlan64 {
   std::vector<char> level_long;  // per level: chains long enough to keep the gates in registers
   DevBuf buf;
   int64_t *tile_row0 = nullptr, *tile_word = nullptr, *tile_ev = nullptr, *col_anchor = nullptr,
-          *col_chain = nullptr, *ev_ptr = nullptr, *ev_src = nullptr, *slot_row = nullptr, *slot_ptr = nullptr,
+          *col_chain = nullptr, *ev_ptr = nullptr, *ev_src = nullptr,
           *slot_seq = nullptr, *slot_pack = nullptr, *root_chains = nullptr, *ts_tile = nullptr, *chunk_beg = nullptr,
           *chunk_end = nullptr, *gate_chunk_ptr = nullptr;
   int32_t *tile_len = nullptr, *ts_step = nullptr;
@@ -795,7 +804,6 @@ int upload_plan64(gst_req* r, gst::Plan64& P, const int32_t* counts_host) {
                o_tev = c.take<int64_t>(T + 1), o_anc = c.take<int64_t>(T * 16 + 1), o_ch = c.take<int64_t>(T * 16 + 1),
                o_words = c.take<uint8_t>(P.words.size() + 1), o_evp = c.take<int64_t>(TS + 2),
                o_evc = c.take<uint8_t>(TS * 16 + 16), o_evs = c.take<int64_t>(NE + 1),
-               o_sr = c.take<int64_t>(P.n_slots + 1), o_sp = c.take<int64_t>(P.n_slots + 2),
                o_sq = c.take<int64_t>(P.S + 1), o_spk = c.take<int64_t>(P.n_slots * 4 + 4),
                o_scn = c.take<double>(P.n_slots * M + 1), o_rc = c.take<int64_t>(NRC + 1),
                o_rb = c.take<int64_t>(NR + 1),
@@ -821,8 +829,6 @@ int upload_plan64(gst_req* r, gst::Plan64& P, const int32_t* counts_host) {
   d.ev_ptr = reinterpret_cast<int64_t*>(b + o_evp);
   d.ev_cend = reinterpret_cast<uint8_t*>(b + o_evc);
   d.ev_src = reinterpret_cast<int64_t*>(b + o_evs);
-  d.slot_row = reinterpret_cast<int64_t*>(b + o_sr);
-  d.slot_ptr = reinterpret_cast<int64_t*>(b + o_sp);
   d.slot_seq = reinterpret_cast<int64_t*>(b + o_sq);
   d.slot_pack = reinterpret_cast<int64_t*>(b + o_spk);
   d.slot_cnt = reinterpret_cast<double*>(b + o_scn);
@@ -857,8 +863,6 @@ int upload_plan64(gst_req* r, gst::Plan64& P, const int32_t* counts_host) {
   if ((rc = put(d.ev_ptr, P.ev_ptr.data(), P.ev_ptr.size() * 8))) return rc;
   if ((rc = put(d.ev_cend, P.ev_cend.data(), TS * 16))) return rc;
   if ((rc = put(d.ev_src, P.ev_src.data(), NE * 8))) return rc;
-  if ((rc = put(d.slot_row, P.slot_row.data(), P.n_slots * 8))) return rc;
-  if ((rc = put(d.slot_ptr, P.slot_ptr.data(), P.slot_ptr.size() * 8))) return rc;
   if ((rc = put(d.slot_seq, P.slot_seq.data(), P.slot_seq.size() * 8))) return rc;
   {
     // per slot: its node row, its first sequence and its sequence range, and
@@ -951,8 +955,6 @@ static gst::Plan64Req plan64_req(gst_req* r, const gst_gateset* th, int mode, co
   ro.E = th->effects;
   ro.FA = d.FA;
   ro.n_slots = d.host.n_slots;
-  ro.slot_row = d.slot_row;
-  ro.slot_ptr = d.slot_ptr;
   ro.slot_seq = d.slot_seq;
   ro.slot_pack = d.slot_pack;
   ro.slot_cnt = d.slot_cnt;

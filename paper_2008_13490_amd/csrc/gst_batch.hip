@@ -156,8 +156,6 @@ __global__ __launch_bounds__(256) void batch_reduce_final_kernel(const BatchRedu
 
 }  // namespace
 
-size_t batch_lds(int kmax) { return batch_lds_bytes(kmax); }
-
 // Accumulators for six gates cover the two-qubit configurations; with more the
 // gate set leaves room for two workgroups per CU, and one-qubit requests come
 // here with more than four gates only: those load ahead whatever their number.

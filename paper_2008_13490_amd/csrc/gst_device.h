@@ -121,8 +121,8 @@ __device__ __forceinline__ double dot16(double x, const Row16& r) { return dot16
 
 // A row of a D x D matrix and its product with a state.  A one-qubit state has
 // four components: two reads and four multiply-adds a step instead of eight and
-// sixteen (the chains wait for them one after another; a fit of 900 sequences with
-// a sharing plan 47.8 -> 43.7 us, sixteen of them 59 -> 53 us).
+// sixteen (the chains wait for them one after another; a fit of 1,044 sequences
+// with a sharing plan 47.8 -> 43.7 us, sixteen of them 59 -> 53 us).
 struct Row4 {
   double2 a0, a1;
 };
@@ -181,21 +181,6 @@ __device__ __forceinline__ T* uniform_ptr(T* p) {
 template <class T>
 __device__ __forceinline__ __attribute__((address_space(1))) T* as_global(T* p) {
   return (__attribute__((address_space(1))) T*)p;
-}
-
-// 16 consecutive doubles of global memory (16-byte aligned) as a Row16.
-__device__ __forceinline__ Row16 load_row_global(const double* p) {
-  const auto* q = as_global(p);
-  Row16 R;
-  R.a0 = double2{q[0], q[1]};
-  R.a1 = double2{q[2], q[3]};
-  R.a2 = double2{q[4], q[5]};
-  R.a3 = double2{q[6], q[7]};
-  R.a4 = double2{q[8], q[9]};
-  R.a5 = double2{q[10], q[11]};
-  R.a6 = double2{q[12], q[13]};
-  R.a7 = double2{q[14], q[15]};
-  return R;
 }
 
 // max over the four 16-lane rows of a wave, as a wave-uniform value
@@ -332,13 +317,6 @@ __device__ void stage_gateset_compact(const Lds& s, const double* __restrict__ G
   }
   if (tid < 16) s.rho[tid] = tid < D ? rho[tid] : 0.0;
   __syncthreads();
-}
-
-__device__ __forceinline__ const double2* grow(const Lds& s, int k, int i) {
-  return reinterpret_cast<const double2*>(s.Gs + k * GATE_STRIDE + i * ROW);
-}
-__device__ __forceinline__ const double2* gtrow(const Lds& s, int k, int i) {
-  return reinterpret_cast<const double2*>(s.GTs + k * GATE_STRIDE + i * ROW);
 }
 
 // C = A B for 16 x 16 matrices in the gate layout (LDS), by one wave on the

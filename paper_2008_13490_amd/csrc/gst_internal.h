@@ -252,7 +252,6 @@ struct BatchReduce {
   BatchReduceItem one;
   const unsigned long long* req_nonpos;
 };
-size_t batch_lds(int kmax);
 // One-qubit requests with K <= 4 gates: one chain per lane, a wave per tile
 // of 64 sequences (gst_lane1q.hip).  ckpt_per_team of the launch is the
 // checkpoint stride of one wave.
@@ -368,10 +367,8 @@ struct Readout64Launch {
   const double* E;
   const double* FA;
   int64_t n_slots;
-  const int64_t* slot_row;
-  const int64_t* slot_ptr;
   const int64_t* slot_seq;
-  const int64_t* slot_pack;  // [n_slots][4]: node row, first sequence, slot_ptr[s], slot_ptr[s + 1]
+  const int64_t* slot_pack;  // [n_slots][4]: node row, first sequence, the slot's range in slot_seq
                              // (null: slot s is the one sequence slot_seq[s], its state row s)
   const double* slot_cnt;    // [n_slots][M]: the counts of the slot's sequences added up (null without a plan)
   const int32_t* counts;
@@ -535,8 +532,6 @@ struct ParamLaunch {
 hipError_t launch_param_forward(const ParamLaunch& a, hipStream_t stream);
 hipError_t launch_param_backward(const ParamLaunch& a, hipStream_t stream);
 
-// reverse fill tasks (adjoints inside the jumps into BA)
-int fill_blocks_for(int64_t n_fill);
 
 // The allocation-free evaluation (gst_noalloc.hip): the scratch array's address
 // on `device`, resolved once per device (0 or a gst_status), and gst_loglik on a

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void reduce_stage2(const double* __restrict__ 
 
 int leaf_ckpt_interval(int) { return C; }
 int leaf_teams_per_block(int) { return WAVES * TPW; }
-int max_gates_for(int D) { return D <= 16 ? KMAX : (D == 64 ? 5 : 0); }  // D = 64: the gate set fills the LDS
+int max_gates_for(int D) { return D <= 16 ? KMAX : (D == 64 ? 5 : 0); }  // D = 64: a wave's operands of all gates in registers
 
 int leaf_blocks_for(int D, int64_t n_items) {
   (void)D;
