@@ -318,10 +318,9 @@ static int64_t tile_seqs_for(int64_t S) {
 // A grouped schedule on the device (gst_sched.hip).
 struct Schedule {
   int tile_seqs = 0;
-  int64_t n_tiles = 0, n_entries = 0;
-  DevBuf buf;
-  int64_t* tile_ptr = nullptr;
+  int64_t n_tiles = 0;
   int64_t* tile_rec = nullptr;
+  int* tile_n = nullptr;
   uint32_t* entries = nullptr;
 };
 
@@ -388,14 +387,10 @@ static size_t chain64_ws_bytes(int K, int blocks, int64_t n_steps) {
   return ((size_t)K * blocks * 4096 + (size_t)(n_steps + 1) * 64) * 8 + 256;
 }
 
-// The grouped schedule of a request's words (tile_rec: the steps of the tiles
-// before each): counted, then written (on the null stream, like the request's
-// uploads).
-static int build_schedule(gst_req* r, const std::vector<int64_t>& tile_rec) {
-  Schedule& d = r->sched;
-  DevBuf count;
-  int rc = count.reserve((size_t)(d.n_tiles + 1) * 8, nullptr);
-  if (rc) return rc;
+// The grouped schedule of a request's words (on the null stream, like the
+// request's uploads).
+static int build_schedule(gst_req* r) {
+  const Schedule& d = r->sched;
   gst::SchedBuild b{};
   b.off = r->offsets;
   b.gates = r->gates;
@@ -403,24 +398,8 @@ static int build_schedule(gst_req* r, const std::vector<int64_t>& tile_rec) {
   b.S = r->S;
   b.K = r->K;
   b.tile_seqs = d.tile_seqs;
-  b.tile_n = reinterpret_cast<int64_t*>(count.p);
-  HIP_TRY(gst::launch_sched(b, d.n_tiles, nullptr));
-  std::vector<int64_t> ptr((size_t)d.n_tiles + 1, 0);
-  if (d.n_tiles > 0) HIP_TRY(hipMemcpy(ptr.data() + 1, count.p, (size_t)d.n_tiles * 8, hipMemcpyDeviceToHost));
-  for (int64_t t = 0; t < d.n_tiles; ++t) ptr[t + 1] += ptr[t];
-  d.n_entries = ptr[d.n_tiles];
-  Carver cv;
-  const size_t o_p = cv.take<int64_t>(ptr.size()), o_r = cv.take<int64_t>(tile_rec.size()),
-               o_e = cv.take<uint32_t>((size_t)d.n_entries + 1);
-  rc = d.buf.reserve(cv.off, nullptr);
-  if (rc) return rc;
-  d.tile_ptr = reinterpret_cast<int64_t*>((char*)d.buf.p + o_p);
-  d.entries = reinterpret_cast<uint32_t*>((char*)d.buf.p + o_e);
-  d.tile_rec = reinterpret_cast<int64_t*>((char*)d.buf.p + o_r);
-  HIP_TRY(hipMemcpy(d.tile_ptr, ptr.data(), ptr.size() * 8, hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(d.tile_rec, tile_rec.data(), tile_rec.size() * 8, hipMemcpyHostToDevice));
-  b.tile_n = nullptr;
-  b.tile_ptr = d.tile_ptr;
+  b.tile_rec = d.tile_rec;
+  b.tile_n = d.tile_n;
   b.entries = d.entries;
   HIP_TRY(gst::launch_sched(b, d.n_tiles, nullptr));
   HIP_TRY(hipStreamSynchronize(nullptr));
@@ -1680,7 +1659,7 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   std::vector<gst::BatchTile> tiles = gst::batch_tiles({&r->tile_q}, {&r->tile_cost}, {0});
   const int64_t Pw = gst::slab_width(D, n_outcomes, n_gates);
   // three-qubit requests without deep sharing: tiles of a grouped schedule
-  std::vector<int64_t> gcp64;
+  std::vector<int64_t> gcp64, tile_rec;
   // three-qubit lists with deep sharing: the grouped-chain plan instead
   gst::Plan64 p64;
   gst::Plan64Options opt64;
@@ -1693,6 +1672,10 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
     r->blocks64 = shape.blocks;
     r->readout_blocks64 = readout_blocks_of(ctx, S);
     for (int k = 0; k <= n_gates; ++k) gcp64.push_back((int64_t)k * r->blocks64);
+    tile_rec.assign((size_t)shape.n_tiles + 1, 0);
+    for (int64_t q = 0; q < S; ++q)
+      tile_rec[(size_t)(q / shape.tile_seqs) + 1] += sl->offsets[order[q] + 1] - sl->offsets[order[q]];
+    for (int64_t t = 0; t < shape.n_tiles; ++t) tile_rec[t + 1] += tile_rec[t];
   }
   const int64_t Pc64 = 1 + 64 + (int64_t)n_outcomes * 64;
   Carver cv;
@@ -1700,7 +1683,9 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
                o_c = cv.take<int32_t>(counts_host ? S * n_outcomes : 1), o_ord = cv.take<int64_t>(S + 1),
                o_sl = cv.take<double>(D == 64 ? 1 : (size_t)std::max<int64_t>(r->n_tiles(), 1) * Pw),
                o_t = cv.take<gst::BatchTile>(tiles.size() + 1), o_q = cv.take<unsigned>(kQueueWords + 2),
-               o_gc64 = cv.take<int64_t>(gcp64.size() + 1),
+               o_gc64 = cv.take<int64_t>(gcp64.size() + 1), o_tr64 = cv.take<int64_t>(tile_rec.size() + 1),
+               o_tn64 = cv.take<int>((size_t)r->sched.n_tiles + 1),
+               o_en64 = cv.take<uint32_t>(gcp64.empty() ? 1 : (size_t)gst::sched_at(n_steps, r->sched.n_tiles) + 1),
                o_fin64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)S * 64 + 1),
                o_hd64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)head_rows64(r.get()) * Pc64),
                o_pt64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)gst::reduce_parts(head_rows64(r.get())) * Pc64);
@@ -1717,11 +1702,16 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   r->n_steps = n_steps;
   if (D == 64) {
     r->gate_chunk_ptr64 = reinterpret_cast<int64_t*>(base + o_gc64);
+    r->sched.tile_rec = reinterpret_cast<int64_t*>(base + o_tr64);
+    r->sched.tile_n = reinterpret_cast<int*>(base + o_tn64);
+    r->sched.entries = reinterpret_cast<uint32_t*>(base + o_en64);
     r->fin64 = reinterpret_cast<double*>(base + o_fin64);
     r->head64 = reinterpret_cast<double*>(base + o_hd64);
     r->part64 = reinterpret_cast<double*>(base + o_pt64);
     if (!gcp64.empty())
       HIP_TRY(hipMemcpy(r->gate_chunk_ptr64, gcp64.data(), gcp64.size() * 8, hipMemcpyHostToDevice));
+    if (!tile_rec.empty())
+      HIP_TRY(hipMemcpy(r->sched.tile_rec, tile_rec.data(), tile_rec.size() * 8, hipMemcpyHostToDevice));
   }
   if (!tiles.empty())
     HIP_TRY(hipMemcpy(r->tiles, tiles.data(), tiles.size() * sizeof(gst::BatchTile), hipMemcpyHostToDevice));
@@ -1751,15 +1741,11 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
     if (rc) return rc;
   }
   if (r->sched.tile_seqs > 0) {
-    std::vector<int64_t> tile_rec((size_t)r->sched.n_tiles + 1, 0);
-    for (int64_t q = 0; q < S; ++q)
-      tile_rec[(size_t)(q / r->sched.tile_seqs) + 1] += sl->offsets[order[q] + 1] - sl->offsets[order[q]];
-    for (int64_t t = 0; t < r->sched.n_tiles; ++t) tile_rec[t + 1] += tile_rec[t];
-    rc = build_schedule(r.get(), tile_rec);
+    rc = build_schedule(r.get());
     if (rc) return rc;
-    if (D == 64) r->eval_ws_bytes = chain64_ws_bytes(r->K, r->blocks64, r->n_steps);
+    r->eval_ws_bytes = chain64_ws_bytes(r->K, r->blocks64, r->n_steps);
   }
-  r->resident_bytes = r->data.bytes + r->plan.buf.bytes + r->plan64.buf.bytes + r->sched.buf.bytes;
+  r->resident_bytes = r->data.bytes + r->plan.buf.bytes + r->plan64.buf.bytes;
   (void)o_off;
   *out = r.release();
   return GST_OK;
@@ -1937,7 +1923,7 @@ static int run64(gst_req* r, const gst_gateset* th, int mode, const double* w, d
   a.tile_seqs = r->sched.tile_seqs;
   a.n_tiles = (int)r->sched.n_tiles;
   a.tile_row = std::max(r->blocks64, 1);
-  a.tile_ptr = r->sched.tile_ptr;
+  a.tile_n = r->sched.tile_n;
   a.entries = r->sched.entries;
   a.tile_rec = r->sched.tile_rec;
   a.zero_rec = (int)r->n_steps;

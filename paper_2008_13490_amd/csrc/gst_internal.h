@@ -272,11 +272,14 @@ hipError_t launch_batch_reduce(const BatchReduce& a, int n_items, int max_chunks
 // length-sorted order.  An entry advances up to four chains by one gate, and
 // entries 2m and 2m + 1 (a round) advance different chains: bits
 // 6r .. 6r + 5 hold, for column r, the chain's index in the tile times two plus
-// the parity of its step (chain 16: no chain), bits 24..27 the gate.  Tile t's
-// entries are tile_ptr[t] .. tile_ptr[t + 1], padded to a multiple of
-// SCHED_ALIGN with entries without chains.
+// the parity of its step (chain 16: no chain), bits 24..27 the gate.  Tile t has
+// tile_n[t] entries, a multiple of SCHED_ALIGN (padded with entries without chains),
+// from sched_at(tile_rec[t], t) on: a step takes a round at most.
 constexpr int SCHED_CHAINS = 16, SCHED_COLS = 4, SCHED_ALIGN = 4;
 constexpr uint32_t SCHED_NONE = (2u * SCHED_CHAINS) * (1u | 1u << 6 | 1u << 12 | 1u << 18);
+__host__ __device__ inline int64_t sched_at(int64_t steps_before, int64_t tile) {
+  return 2 * steps_before + SCHED_ALIGN * tile;
+}
 struct SchedBuild {
   const int64_t* off;
   const uint8_t* gates;
@@ -284,9 +287,9 @@ struct SchedBuild {
   int64_t S;
   int K;
   int tile_seqs;             // chains per tile (<= SCHED_CHAINS)
-  int64_t* tile_n;           // first pass (entries = null): the entries of each tile
-  const int64_t* tile_ptr;   // second pass
-  uint32_t* entries;
+  const int64_t* tile_rec;   // [tiles + 1]: the steps of the tiles before
+  int* tile_n;               // [tiles]
+  uint32_t* entries;         // [sched_at(steps, tiles) + 1]
 };
 hipError_t launch_sched(const SchedBuild& a, int64_t n_tiles, hipStream_t stream);
 
@@ -302,7 +305,7 @@ struct Chain64Launch {
   int tile_seqs;             // chains per tile (consecutive in `order`)
   int n_tiles;
   int tile_row;              // workgroups take the tiles there and back in rows of this many
-  const int64_t* tile_ptr;   // [n_tiles + 1]
+  const int* tile_n;         // [n_tiles]
   const uint32_t* entries;
   const int64_t* tile_rec;   // [n_tiles + 1]: the chain-steps of the tiles before
   int zero_rec;              // all of them

@@ -221,9 +221,9 @@ __global__ __launch_bounds__(512, 2) void chain64_fwd_kernel(const Chain64Launch
   for (int tile = next_tile(at, a.tile_row, a.n_tiles); tile < a.n_tiles; tile = next_tile(at, a.tile_row, a.n_tiles)) {
     const int64_t q0 = (int64_t)tile * a.tile_seqs;
     const int n = (int)(q0 + a.tile_seqs < a.S ? a.tile_seqs : a.S - q0);
-    const int64_t e0 = uniform64(a.tile_ptr[tile]);
-    const int ne = (int)(uniform64(a.tile_ptr[tile + 1]) - e0);
     int done = (int)uniform64(a.tile_rec[tile]);  // records of the entries before
+    const int64_t e0 = sched_at(uniform64(a.tile_rec[tile]), tile);
+    const int ne = uniform(a.tile_n[tile]);
     for (int c = wave; c <= SCHED_CHAINS; c += 8) {
       V[2 * c * SST + state_at(l)] = c < n ? rho : 0.0;
       if (c == SCHED_CHAINS) V[(2 * c + 1) * SST + state_at(l)] = 0.0;
@@ -286,8 +286,8 @@ __global__ __launch_bounds__(512, 2) void chain64_bwd_kernel(const Chain64Launch
          tile = next_tile(at, a.tile_row, a.n_tiles)) {
       const int64_t q0 = (int64_t)tile * a.tile_seqs;
       const int n = (int)(q0 + a.tile_seqs < a.S ? a.tile_seqs : a.S - q0);
-      const int64_t e0 = uniform64(a.tile_ptr[tile]);
-      const int ne = (int)(uniform64(a.tile_ptr[tile + 1]) - e0);
+      const int64_t e0 = sched_at(uniform64(a.tile_rec[tile]), tile);
+      const int ne = uniform(a.tile_n[tile]);
       uint32_t next = entries[e0 + max(ne - 1 - l, 0)];
       for (int c = w; c <= SCHED_CHAINS; c += 4) {
         if (c < n) {
@@ -334,8 +334,8 @@ __global__ __launch_bounds__(512, 2) void chain64_bwd_kernel(const Chain64Launch
     for (int tc = 0; tc < 4; ++tc) dg[x][tc] = d4{0.0, 0.0, 0.0, 0.0};
   int at = blockIdx.x;
   for (int tile = next_tile(at, a.tile_row, a.n_tiles); tile < a.n_tiles; tile = next_tile(at, a.tile_row, a.n_tiles)) {
-    const int64_t e0 = uniform64(a.tile_ptr[tile]);
-    const int ne = (int)(uniform64(a.tile_ptr[tile + 1]) - e0);
+    const int64_t e0 = sched_at(uniform64(a.tile_rec[tile]), tile);
+    const int ne = uniform(a.tile_n[tile]);
     // The records of 64 entries, backwards from the tile's last one: lane x has the
     // row of column w's state before entry x of them (no chain there: the row of
     // zeros), `end` moves to the first entry's.

@@ -33,9 +33,25 @@ __host__ __device__ inline void sched_tile(const SchedBuild& a, int64_t tile, Wi
   }
   auto least = [](int x, int y) { return x < y ? x : y; };
   const int longest = wave.first(len);  // the order is by length, descending
-  uint32_t* out = a.entries ? a.entries + a.tile_ptr[tile] : nullptr;
-  int64_t e = 0;
+  uint32_t* out = a.entries + sched_at(a.tile_rec[tile], tile);
+  int e = 0;
   int pos = 0;
+  if (n == 1) {
+    // one chain: a round per step, its second entry empty (a word of 100 gates took
+    // 90 us entry by entry)
+    const int64_t b = wave.from(beg, 0);
+    for (int t = lane; t < longest; t += 64) {
+      out[2 * t] = ((uint32_t)a.gates[b + t] << 24) | (SCHED_NONE & ~63u) | (uint32_t)(t & 1);
+      out[2 * t + 1] = SCHED_NONE;
+    }
+    e = 2 * longest;
+    if (e % SCHED_ALIGN) {
+      if (lane < 2) out[e + lane] = SCHED_NONE;
+      e += 2;
+    }
+    if (lane == 0) a.tile_n[tile] = e;
+    return;
+  }
   for (int w0 = 0; w0 < longest; w0 += SCHED_WINDOW) {
     wave.sync();
     for (int x = 0; x < n; ++x) {
@@ -86,7 +102,7 @@ __host__ __device__ inline void sched_tile(const SchedBuild& a, int64_t tile, Wi
           const uint32_t id = m ? (uint32_t)__builtin_ctzll(m) : (uint32_t)SCHED_CHAINS;
           entry |= (id * 2u + (odd ? 1u : 0u)) << (6 * r);
         }
-        if (out && lane == 0) out[e] = entry;
+        if (lane == 0) out[e] = entry;
         ++e;
         if (left && g == best) rank -= SCHED_COLS;  // the gate's next four, if it is taken twice
         left = left && !take;
@@ -101,8 +117,8 @@ __host__ __device__ inline void sched_tile(const SchedBuild& a, int64_t tile, Wi
   // the reverse sweeps run whole groups of entries
   const uint32_t none = SCHED_NONE;
   for (; e % SCHED_ALIGN; ++e)
-    if (out && lane == 0) out[e] = none;
-  if (!out && lane == 0) a.tile_n[tile] = e;
+    if (lane == 0) out[e] = none;
+  if (lane == 0) a.tile_n[tile] = e;
 }
 
 }  // namespace gst

@@ -69,10 +69,12 @@ void lane_main(int id) {
 
 }  // namespace
 
-// Runs every tile of one pass; returns the window accesses out of range.
+extern "C" int64_t sched_at(int64_t steps_before, int64_t tile) { return gst::sched_at(steps_before, tile); }
+
+// Runs every tile; returns the window accesses out of range.
 extern "C" int64_t sched_cpu(const int64_t* off, const uint8_t* gates, const int64_t* order, int64_t S, int K,
-                             int tile_seqs, int64_t* tile_n, const int64_t* tile_ptr, uint32_t* entries) {
-  const gst::SchedBuild a{off, gates, order, S, K, tile_seqs, tile_n, tile_ptr, entries};
+                             int tile_seqs, const int64_t* tile_rec, int* tile_n, uint32_t* entries) {
+  const gst::SchedBuild a{off, gates, order, S, K, tile_seqs, tile_rec, tile_n, entries};
   build = &a;
   out_of_range = 0;
   for (tile_of = 0; tile_of * tile_seqs < S; ++tile_of) {

@@ -21,12 +21,13 @@ def lib(tmp_path_factory):
     lib = ctypes.CDLL(out)
     P = ctypes.c_void_p
     lib.sched_cpu.argtypes = [P, P, P, ctypes.c_int64, ctypes.c_int, ctypes.c_int, P, P, P]
-    lib.sched_cpu.restype = ctypes.c_int64
+    lib.sched_cpu.restype = lib.sched_at.restype = ctypes.c_int64
+    lib.sched_at.argtypes = [ctypes.c_int64, ctypes.c_int64]
     return lib
 
 
 @pytest.mark.parametrize("K,tile,lengths", [
-    (5, 16, [513, 3, 0]), (5, 1, [520]), (2, 3, [530, 513, 512, 511, 1, 0, 0]), (1, 16, [9] * 17),
+    (5, 16, [513, 3, 0]), (5, 1, [520, 0, 7, 2]), (5, 16, [35]), (2, 3, [530, 513, 512, 511, 1, 0, 0]), (1, 16, [9] * 17),
     (5, 16, list(range(20, 41))), (4, 5, [24, 23, 1, 1, 0, 520, 40]),
 ])
 def test_schedule(lib, K, tile, lengths):
@@ -37,17 +38,19 @@ def test_schedule(lib, K, tile, lengths):
     S = len(lengths)
     order = np.argsort(-np.asarray(lengths), kind="stable").astype(np.int64)
     n_tiles = (S + tile - 1) // tile
-    count = np.zeros(n_tiles, np.int64)
+    rec = np.array([sum(lengths[q] for q in order[:t * tile]) for t in range(n_tiles + 1)], np.int64)
+    at = [lib.sched_at(int(rec[t]), t) for t in range(n_tiles + 1)]
+    count = np.full(n_tiles, -1, np.int32)
+    entries = np.full(at[-1] + 1, 0xffffffff, np.uint32)
     args = [x.ctypes.data for x in (off, gates, order)] + [S, K, tile]
-    assert lib.sched_cpu(*args, count.ctypes.data, None, None) == 0
-    ptr = np.concatenate([[0], np.cumsum(count)]).astype(np.int64)
-    entries = np.zeros(int(ptr[-1]) + 1, np.uint32)
-    assert lib.sched_cpu(*args, None, ptr.ctypes.data, entries.ctypes.data) == 0
+    assert lib.sched_cpu(*args, rec.ctypes.data, count.ctypes.data, entries.ctypes.data) == 0
+    assert entries[-1] == 0xffffffff
     for t in range(n_tiles):
         chains = order[t * tile:(t + 1) * tile]
         pos = [0] * len(chains)
-        es = entries[ptr[t]:ptr[t + 1]]
-        assert len(es) % 4 == 0
+        es = entries[at[t]:at[t] + count[t]]
+        assert len(es) % 4 == 0 and at[t] + len(es) <= at[t + 1]
+        assert (entries[at[t] + len(es):at[t + 1]] == 0xffffffff).all()
         for x in range(0, len(es), 2):
             seen = set()
             for e in es[x:x + 2]:
