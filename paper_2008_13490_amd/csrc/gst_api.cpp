@@ -163,6 +163,44 @@ struct Carver {
   }
 };
 
+// Host arrays on their way into one device allocation.  A copy costs the host about
+// 7 us whatever it moves, and a request has thirty arrays: small ones that lie next to
+// each other on the device travel as one copy, the space between them as zeros (so
+// nothing there may have been written yet).
+struct Uploads {
+  static constexpr size_t kSmall = 64 << 10, kGap = 1024;
+  struct Item {
+    char* dst;
+    const void* src;
+    size_t n;
+  };
+  std::vector<Item> items;
+  void put(void* dst, const void* src, size_t n) {
+    if (n) items.push_back({reinterpret_cast<char*>(dst), src, n});
+  }
+  int flush() {
+    std::sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.dst < b.dst; });
+    std::vector<char> run;
+    for (size_t i = 0; i < items.size();) {
+      size_t e = i + 1;
+      if (items[i].n <= kSmall)
+        while (e < items.size() && items[e].n <= kSmall &&
+               (size_t)(items[e].dst - (items[e - 1].dst + items[e - 1].n)) <= kGap)
+          ++e;
+      if (e == i + 1) {
+        HIP_TRY(hipMemcpy(items[i].dst, items[i].src, items[i].n, hipMemcpyHostToDevice));
+      } else {
+        run.assign((size_t)(items[e - 1].dst + items[e - 1].n - items[i].dst), 0);
+        for (size_t x = i; x < e; ++x) std::memcpy(run.data() + (items[x].dst - items[i].dst), items[x].src, items[x].n);
+        HIP_TRY(hipMemcpy(items[i].dst, run.data(), run.size(), hipMemcpyHostToDevice));
+      }
+      i = e;
+    }
+    items.clear();
+    return GST_OK;
+  }
+};
+
 struct gst_ctx {
   int device = 0;
   int n_cu = 0;
@@ -663,15 +701,18 @@ int upload_plan(gst_req* r, const gst::HostPlan& P, const int32_t* counts_host) 
                o_isrc = c.take<int32_t>(nI + 1), o_ikv = c.take<uint8_t>((size_t)nI * 16 + 1),
                o_icnt = c.take<int32_t>((size_t)nI * r->M + 1), o_tsrc = c.take<int32_t>(nT + 1), o_isp = c.take<int64_t>(nI + 1),
                o_rb = c.take<int64_t>(nR + 1), o_rf = c.take<int64_t>(nR + 1), o_cg = c.take<int64_t>(nC + 1),
-               o_cb = c.take<int64_t>(nC + 1), o_ce = c.take<int64_t>(nC + 1),
-               o_fa = c.take<double>((size_t)(1 + nTS + nIS + gst::JUMP_STEPS_MAX + 1) * D), o_ba = c.take<double>((size_t)(nTS + nIS + 1) * D),
-               o_src = c.take<double>((size_t)(P.n_src_rows() + 1) * D), o_inj = c.take<double>((size_t)(nJ + 1) * D);
+               o_cb = c.take<int64_t>(nC + 1), o_ce = c.take<int64_t>(nC + 1);
   const size_t nF = P.fill_first.size();
   const size_t o_jp = c.take<uint32_t>(nT + 1), o_jg3 = c.take<uint8_t>(nT + 1), o_jlv = c.take<uint8_t>(nT + 1),
-               o_jt = c.take<double>((size_t)nT * std::max(P.jump_levels, 1) * 256 + 1), o_ff = c.take<int64_t>(nF + 1),
+               o_ff = c.take<int64_t>(nF + 1),
                o_fi = c.take<int64_t>(nF + 1), o_fn = c.take<int32_t>(nF + 1), o_fp = c.take<uint32_t>(nF + 1),
                o_fg3 = c.take<uint8_t>(nF + 1), o_jf = c.take<int64_t>(gw.jump_first.size() + 1),
                o_ji = c.take<int64_t>(gw.jump_in.size() + 1), o_jm = c.take<int32_t>(gw.jump_meta.size() + 1);
+  // what the kernels write lies behind the host's arrays (small ones travel in one copy)
+  const size_t o_fa = c.take<double>((size_t)(1 + nTS + nIS + gst::JUMP_STEPS_MAX + 1) * D),
+               o_ba = c.take<double>((size_t)(nTS + nIS + 1) * D),
+               o_src = c.take<double>((size_t)(P.n_src_rows() + 1) * D), o_inj = c.take<double>((size_t)(nJ + 1) * D),
+               o_jt = c.take<double>((size_t)nT * std::max(P.jump_levels, 1) * 256 + 1);
   int rc = d.buf.reserve(c.off + 256, r->ctx->stream);
   if (rc) return rc;
   char* b = reinterpret_cast<char*>(d.buf.p);
@@ -712,44 +753,43 @@ int upload_plan(gst_req* r, const gst::HostPlan& P, const int32_t* counts_host) 
   d.n_jump_groups = (int64_t)gw.jump_meta.size() / 8;
   d.zero_row = 1 + nTS + nIS;
   d.tile_ptr = gw.tile_ptr;
-  auto put = [&](void* dst, const void* src, size_t bytes) -> int {
-    if (bytes) HIP_TRY(hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice));
-    return GST_OK;
-  };
-  if ((rc = put(d.op_ptr, P.op_ptr.data(), P.op_ptr.size() * 8))) return rc;
-  if ((rc = put(d.op_desc, P.op_desc.data(), nOp * 4))) return rc;
-  if ((rc = put(d.op_slot, P.op_slot.data(), nOp * 4))) return rc;
-  if ((rc = put(d.items, P.items.data(), P.items.size() * 8))) return rc;
-  if ((rc = put(d.trunk_ptr, P.trunk_ptr.data(), P.trunk_ptr.size() * 8))) return rc;
-  if ((rc = put(d.trunk_anchor, P.trunk_anchor.data(), P.trunk_anchor.size() * 8))) return rc;
-  if ((rc = put(d.inj_ptr, P.inj_ptr.data(), P.inj_ptr.size() * 8))) return rc;
-  if ((rc = put(d.item_src, P.item_src.data(), (size_t)nI * 4))) return rc;
-  if ((rc = put(d.item_kv, P.item_kv.data(), P.item_kv.size()))) return rc;
+  Uploads up;
+  up.put(d.op_ptr, P.op_ptr.data(), P.op_ptr.size() * 8);
+  up.put(d.op_desc, P.op_desc.data(), nOp * 4);
+  up.put(d.op_slot, P.op_slot.data(), nOp * 4);
+  up.put(d.items, P.items.data(), P.items.size() * 8);
+  up.put(d.trunk_ptr, P.trunk_ptr.data(), P.trunk_ptr.size() * 8);
+  up.put(d.trunk_anchor, P.trunk_anchor.data(), P.trunk_anchor.size() * 8);
+  up.put(d.inj_ptr, P.inj_ptr.data(), P.inj_ptr.size() * 8);
+  up.put(d.item_src, P.item_src.data(), (size_t)nI * 4);
+  up.put(d.item_kv, P.item_kv.data(), P.item_kv.size());
+  std::vector<int32_t> cnt;
   if (counts_host) {
-    std::vector<int32_t> cnt((size_t)nI * r->M);
+    cnt.resize((size_t)nI * r->M);
     for (int64_t q = 0; q < nI; ++q)
       for (int m = 0; m < r->M; ++m) cnt[(size_t)q * r->M + m] = counts_host[P.items[4 * q] * r->M + m];
-    if ((rc = put(d.item_cnt, cnt.data(), cnt.size() * 4))) return rc;
+    up.put(d.item_cnt, cnt.data(), cnt.size() * 4);
   }
-  if ((rc = put(d.trunk_src, P.trunk_src.data(), (size_t)nT * 4))) return rc;
-  if ((rc = put(d.item_step_ptr, P.item_step_ptr.data(), P.item_step_ptr.size() * 8))) return rc;
-  if ((rc = put(d.rec_b, gw.rec_b.data(), nR * 8))) return rc;
-  if ((rc = put(d.rec_f, gw.rec_f.data(), nR * 8))) return rc;
-  if ((rc = put(d.chunk_tile, gw.chunk_tile.data(), nC * 8))) return rc;
-  if ((rc = put(d.chunk_beg, gw.chunk_beg.data(), nC * 8))) return rc;
-  if ((rc = put(d.chunk_end, gw.chunk_end.data(), nC * 8))) return rc;
+  up.put(d.trunk_src, P.trunk_src.data(), (size_t)nT * 4);
+  up.put(d.item_step_ptr, P.item_step_ptr.data(), P.item_step_ptr.size() * 8);
+  up.put(d.rec_b, gw.rec_b.data(), nR * 8);
+  up.put(d.rec_f, gw.rec_f.data(), nR * 8);
+  up.put(d.chunk_tile, gw.chunk_tile.data(), nC * 8);
+  up.put(d.chunk_beg, gw.chunk_beg.data(), nC * 8);
+  up.put(d.chunk_end, gw.chunk_end.data(), nC * 8);
   HIP_TRY(hipMemset(d.FA + d.zero_row * D, 0, (size_t)(gst::JUMP_STEPS_MAX + 1) * D * 8));
-  if ((rc = put(d.jump_first, gw.jump_first.data(), gw.jump_first.size() * 8))) return rc;
-  if ((rc = put(d.jump_in, gw.jump_in.data(), gw.jump_in.size() * 8))) return rc;
-  if ((rc = put(d.jump_meta, gw.jump_meta.data(), gw.jump_meta.size() * 4))) return rc;
-  if ((rc = put(d.trunk_jpat, P.trunk_jump_pattern.data(), P.trunk_jump_pattern.size() * 4))) return rc;
-  if ((rc = put(d.trunk_jg3, P.trunk_jump_gate3.data(), P.trunk_jump_gate3.size()))) return rc;
-  if ((rc = put(d.trunk_jlev, P.trunk_jump_levels.data(), P.trunk_jump_levels.size()))) return rc;
-  if ((rc = put(d.fill_first, P.fill_first.data(), nF * 8))) return rc;
-  if ((rc = put(d.fill_in, P.fill_in.data(), nF * 8))) return rc;
-  if ((rc = put(d.fill_n, P.fill_n.data(), nF * 4))) return rc;
-  if ((rc = put(d.fill_pattern, P.fill_pattern.data(), nF * 4))) return rc;
-  if ((rc = put(d.fill_gate3, P.fill_gate3.data(), nF))) return rc;
+  up.put(d.jump_first, gw.jump_first.data(), gw.jump_first.size() * 8);
+  up.put(d.jump_in, gw.jump_in.data(), gw.jump_in.size() * 8);
+  up.put(d.jump_meta, gw.jump_meta.data(), gw.jump_meta.size() * 4);
+  up.put(d.trunk_jpat, P.trunk_jump_pattern.data(), P.trunk_jump_pattern.size() * 4);
+  up.put(d.trunk_jg3, P.trunk_jump_gate3.data(), P.trunk_jump_gate3.size());
+  up.put(d.trunk_jlev, P.trunk_jump_levels.data(), P.trunk_jump_levels.size());
+  up.put(d.fill_first, P.fill_first.data(), nF * 8);
+  up.put(d.fill_in, P.fill_in.data(), nF * 8);
+  up.put(d.fill_n, P.fill_n.data(), nF * 4);
+  up.put(d.fill_pattern, P.fill_pattern.data(), nF * 4);
+  up.put(d.fill_gate3, P.fill_gate3.data(), nF);
+  if ((rc = up.flush())) return rc;
   // injection slots of each level: slots of stored locations are sorted by
   // location (the root slot comes last) and a level's locations are contiguous
   d.inj_level_ptr.assign(P.n_levels + 1, 0);
@@ -787,14 +827,16 @@ int upload_plan64(gst_req* r, gst::Plan64& P, const int32_t* counts_host) {
                o_scn = c.take<double>(P.n_slots * M + 1), o_rc = c.take<int64_t>(NRC + 1),
                o_rb = c.take<int64_t>(NR + 1),
                o_rf = c.take<int32_t>(NR + 1), o_cb = c.take<int64_t>(NC + 1), o_ce = c.take<int64_t>(NC + 1),
-               o_gcp = c.take<int64_t>(K + 1), o_fa = c.take<double>((size_t)P.n_rows * 64),
+               o_gcp = c.take<int64_t>(K + 1), o_lt = c.take<int64_t>(P.n_levels + 1),
+               o_ll = c.take<uint8_t>(P.n_levels + 1);
+  // what the kernels write lies behind the host's arrays (small ones travel in one copy)
+  const size_t o_fa = c.take<double>((size_t)P.n_rows * 64),
                o_ba = c.take<double>((size_t)P.n_rows * 64),
                o_inj = c.take<double>((size_t)(P.n_slots + P.n_chains + 1) * 64),
                o_ga = c.take<double>((size_t)K * 4096), o_gat = c.take<double>((size_t)K * 4096),
                o_slab = c.take<double>((size_t)n_waves * Pc),
                o_part = c.take<double>((size_t)gst::reduce_parts((int)n_waves) * Pc),
-               o_cs = c.take<double>((size_t)std::max<int64_t>(NC, 1) * 4096), o_root = c.take<double>(64),
-               o_lt = c.take<int64_t>(P.n_levels + 1), o_ll = c.take<uint8_t>(P.n_levels + 1);
+               o_cs = c.take<double>((size_t)std::max<int64_t>(NC, 1) * 4096), o_root = c.take<double>(64);
   int rc = d.buf.reserve(c.off + 256, r->ctx->stream);
   if (rc) return rc;
   char* b = reinterpret_cast<char*>(d.buf.p);
@@ -828,52 +870,48 @@ int upload_plan64(gst_req* r, gst::Plan64& P, const int32_t* counts_host) {
   d.root_vec = reinterpret_cast<double*>(b + o_root);
   d.lvl_tile = reinterpret_cast<int64_t*>(b + o_lt);
   d.lvl_long = reinterpret_cast<uint8_t*>(b + o_ll);
-  auto put = [&](void* dst, const void* src, size_t bytes) -> int {
-    if (bytes) HIP_TRY(hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice));
-    return GST_OK;
-  };
-  if ((rc = put(d.tile_row0, P.tile_row0.data(), T * 8))) return rc;
-  if ((rc = put(d.tile_len, P.tile_len.data(), T * 4))) return rc;
-  if ((rc = put(d.tile_word, P.tile_word.data(), T * 8))) return rc;
-  if ((rc = put(d.tile_ev, P.tile_ev.data(), T * 8))) return rc;
-  if ((rc = put(d.col_anchor, P.col_anchor.data(), T * 16 * 8))) return rc;
-  if ((rc = put(d.col_chain, P.col_chain.data(), T * 16 * 8))) return rc;
-  if ((rc = put(d.words, P.words.data(), P.words.size()))) return rc;
-  if ((rc = put(d.ev_ptr, P.ev_ptr.data(), P.ev_ptr.size() * 8))) return rc;
-  if ((rc = put(d.ev_cend, P.ev_cend.data(), TS * 16))) return rc;
-  if ((rc = put(d.ev_src, P.ev_src.data(), NE * 8))) return rc;
-  if ((rc = put(d.slot_seq, P.slot_seq.data(), P.slot_seq.size() * 8))) return rc;
-  {
-    // per slot: its node row, its first sequence and its sequence range, and
-    // its sequences' counts added up (the readout loads them together, by slot)
-    std::vector<int64_t> pack((size_t)P.n_slots * 4);
-    std::vector<double> cnt((size_t)P.n_slots * M, 0.0);
-    for (int64_t x = 0; x < P.n_slots; ++x) {
-      const int64_t q0 = P.slot_ptr[x], q1 = P.slot_ptr[x + 1];
-      const int64_t seq0 = q1 > q0 ? P.slot_seq[q0] : 0;
-      pack[4 * x + 0] = P.slot_row[x];
-      pack[4 * x + 1] = seq0;
-      pack[4 * x + 2] = q0;
-      pack[4 * x + 3] = q1;
-      for (int64_t q = q0; counts_host && q < q1; ++q)
-        for (int m = 0; m < M; ++m) cnt[(size_t)x * M + m] += counts_host[P.slot_seq[q] * M + m];
-    }
-    if ((rc = put(d.slot_pack, pack.data(), pack.size() * 8))) return rc;
-    if ((rc = put(d.slot_cnt, cnt.data(), cnt.size() * 8))) return rc;
+  Uploads up;
+  up.put(d.tile_row0, P.tile_row0.data(), T * 8);
+  up.put(d.tile_len, P.tile_len.data(), T * 4);
+  up.put(d.tile_word, P.tile_word.data(), T * 8);
+  up.put(d.tile_ev, P.tile_ev.data(), T * 8);
+  up.put(d.col_anchor, P.col_anchor.data(), T * 16 * 8);
+  up.put(d.col_chain, P.col_chain.data(), T * 16 * 8);
+  up.put(d.words, P.words.data(), P.words.size());
+  up.put(d.ev_ptr, P.ev_ptr.data(), P.ev_ptr.size() * 8);
+  up.put(d.ev_cend, P.ev_cend.data(), TS * 16);
+  up.put(d.ev_src, P.ev_src.data(), NE * 8);
+  up.put(d.slot_seq, P.slot_seq.data(), P.slot_seq.size() * 8);
+  // per slot: its node row, its first sequence and its sequence range, and
+  // its sequences' counts added up (the readout loads them together, by slot)
+  std::vector<int64_t> pack((size_t)P.n_slots * 4);
+  std::vector<double> cnt((size_t)P.n_slots * M, 0.0);
+  for (int64_t x = 0; x < P.n_slots; ++x) {
+    const int64_t q0 = P.slot_ptr[x], q1 = P.slot_ptr[x + 1];
+    const int64_t seq0 = q1 > q0 ? P.slot_seq[q0] : 0;
+    pack[4 * x + 0] = P.slot_row[x];
+    pack[4 * x + 1] = seq0;
+    pack[4 * x + 2] = q0;
+    pack[4 * x + 3] = q1;
+    for (int64_t q = q0; counts_host && q < q1; ++q)
+      for (int m = 0; m < M; ++m) cnt[(size_t)x * M + m] += counts_host[P.slot_seq[q] * M + m];
   }
-  if ((rc = put(d.root_chains, P.root_chains.data(), NRC * 8))) return rc;
-  if ((rc = put(d.ts_tile, P.ts_tile.data(), NR * 8))) return rc;
-  if ((rc = put(d.ts_step, P.ts_step.data(), NR * 4))) return rc;
-  if ((rc = put(d.chunk_beg, P.chunk_beg.data(), NC * 8))) return rc;
-  if ((rc = put(d.chunk_end, P.chunk_end.data(), NC * 8))) return rc;
-  if ((rc = put(d.gate_chunk_ptr, P.gate_chunk_ptr.data(), (K + 1) * 8))) return rc;
+  up.put(d.slot_pack, pack.data(), pack.size() * 8);
+  up.put(d.slot_cnt, cnt.data(), cnt.size() * 8);
+  up.put(d.root_chains, P.root_chains.data(), NRC * 8);
+  up.put(d.ts_tile, P.ts_tile.data(), NR * 8);
+  up.put(d.ts_step, P.ts_step.data(), NR * 4);
+  up.put(d.chunk_beg, P.chunk_beg.data(), NC * 8);
+  up.put(d.chunk_end, P.chunk_end.data(), NC * 8);
+  up.put(d.gate_chunk_ptr, P.gate_chunk_ptr.data(), (K + 1) * 8);
   d.level_tile_ptr = P.level_tile_ptr;
   d.level_long.assign((size_t)P.n_levels, 0);
   for (int l = 0; l < P.n_levels; ++l)
     for (int64_t t = P.level_tile_ptr[l]; t < P.level_tile_ptr[l + 1]; ++t)
       if (P.tile_len[t] >= kRegGateSteps) d.level_long[l] = 1;
-  if ((rc = put(d.lvl_tile, d.level_tile_ptr.data(), d.level_tile_ptr.size() * 8))) return rc;
-  if ((rc = put(d.lvl_long, d.level_long.data(), d.level_long.size()))) return rc;
+  up.put(d.lvl_tile, d.level_tile_ptr.data(), d.level_tile_ptr.size() * 8);
+  up.put(d.lvl_long, d.level_long.data(), d.level_long.size());
+  if ((rc = up.flush())) return rc;
   d.n_root_chains = (int)NRC;
   d.n_chunks = NC;
   // keep the sizes, drop the host copies of the big arrays
@@ -1681,10 +1719,11 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   Carver cv;
   const size_t o_off = cv.take<int64_t>(S + 1), o_g = cv.take<uint8_t>(std::max<int64_t>(n_steps, 1)),
                o_c = cv.take<int32_t>(counts_host ? S * n_outcomes : 1), o_ord = cv.take<int64_t>(S + 1),
-               o_sl = cv.take<double>(D == 64 ? 1 : (size_t)std::max<int64_t>(r->n_tiles(), 1) * Pw),
-               o_t = cv.take<gst::BatchTile>(tiles.size() + 1), o_q = cv.take<unsigned>(kQueueWords + 2),
-               o_gc64 = cv.take<int64_t>(gcp64.size() + 1), o_tr64 = cv.take<int64_t>(tile_rec.size() + 1),
-               o_tn64 = cv.take<int>((size_t)r->sched.n_tiles + 1),
+               o_t = cv.take<gst::BatchTile>(tiles.size() + 1), o_gc64 = cv.take<int64_t>(gcp64.size() + 1),
+               o_tr64 = cv.take<int64_t>(tile_rec.size() + 1);
+  // what the kernels write lies behind the host's arrays (small ones travel in one copy)
+  const size_t o_sl = cv.take<double>(D == 64 ? 1 : (size_t)std::max<int64_t>(r->n_tiles(), 1) * Pw),
+               o_q = cv.take<unsigned>(kQueueWords + 2), o_tn64 = cv.take<int>((size_t)r->sched.n_tiles + 1),
                o_en64 = cv.take<uint32_t>(gcp64.empty() ? 1 : (size_t)gst::sched_at(n_steps, r->sched.n_tiles) + 1),
                o_fin64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)S * 64 + 1),
                o_hd64 = cv.take<double>(gcp64.empty() ? 1 : (size_t)head_rows64(r.get()) * Pc64),
@@ -1700,6 +1739,7 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
   r->tiles = reinterpret_cast<gst::BatchTile*>(base + o_t);
   r->queue = reinterpret_cast<unsigned*>(base + o_q);
   r->n_steps = n_steps;
+  Uploads up;
   if (D == 64) {
     r->gate_chunk_ptr64 = reinterpret_cast<int64_t*>(base + o_gc64);
     r->sched.tile_rec = reinterpret_cast<int64_t*>(base + o_tr64);
@@ -1708,18 +1748,16 @@ int gst_req_create_host(gst_ctx* ctx, int n_qubits, int n_gates, int n_outcomes,
     r->fin64 = reinterpret_cast<double*>(base + o_fin64);
     r->head64 = reinterpret_cast<double*>(base + o_hd64);
     r->part64 = reinterpret_cast<double*>(base + o_pt64);
-    if (!gcp64.empty())
-      HIP_TRY(hipMemcpy(r->gate_chunk_ptr64, gcp64.data(), gcp64.size() * 8, hipMemcpyHostToDevice));
-    if (!tile_rec.empty())
-      HIP_TRY(hipMemcpy(r->sched.tile_rec, tile_rec.data(), tile_rec.size() * 8, hipMemcpyHostToDevice));
+    up.put(r->gate_chunk_ptr64, gcp64.data(), gcp64.size() * 8);
+    up.put(r->sched.tile_rec, tile_rec.data(), tile_rec.size() * 8);
   }
-  if (!tiles.empty())
-    HIP_TRY(hipMemcpy(r->tiles, tiles.data(), tiles.size() * sizeof(gst::BatchTile), hipMemcpyHostToDevice));
+  up.put(r->tiles, tiles.data(), tiles.size() * sizeof(gst::BatchTile));
   std::vector<int64_t> zero_off(1, 0);
-  HIP_TRY(hipMemcpy(r->offsets, S > 0 ? sl->offsets : zero_off.data(), (size_t)(S + 1) * 8, hipMemcpyHostToDevice));
-  if (n_steps > 0) HIP_TRY(hipMemcpy(r->gates, sl->gate_idx, (size_t)n_steps, hipMemcpyHostToDevice));
-  if (counts_host && S > 0) HIP_TRY(hipMemcpy(r->counts, counts_host, (size_t)S * n_outcomes * 4, hipMemcpyHostToDevice));
-  if (S > 0) HIP_TRY(hipMemcpy(r->order, order.data(), (size_t)S * 8, hipMemcpyHostToDevice));
+  up.put(r->offsets, S > 0 ? sl->offsets : zero_off.data(), (size_t)(S + 1) * 8);
+  up.put(r->gates, sl->gate_idx, (size_t)n_steps);
+  if (counts_host) up.put(r->counts, counts_host, (size_t)S * n_outcomes * 4);
+  up.put(r->order, order.data(), (size_t)S * 8);
+  if ((rc = up.flush())) return rc;
   if (S > 0 && D <= 16) {
     gst::HostPlan hp;
     gst::PlanOptions opt;
