@@ -55,7 +55,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // Both kernels run eight waves, two per SIMD.  Forward: four waves per entry of
 // the round, so the two products fill each other's latencies (302 -> 170 us
 // below, against one entry after the other on two workgroups of four waves per
-// CU); the states before each entry are recorded one after the other, so that a
+// CU; 164 since the gates' rows come through LDS); the states before each entry are recorded one after the other, so that a
 // chain-step takes 512 bytes whatever its entry holds.
 // Reverse: four waves step the adjoints of both entries, at a raised priority,
 // and the other four load the recorded states two rounds ahead and add
@@ -66,7 +66,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // fixed workgroup, so the sums do not depend on scheduling.
 //
 // 8,000 words of up to 128 gates (510,378 steps), per evaluation with the
-// gradient: 4.86 -> 0.45 ms, against a chain per wave with the gates in LDS,
+// gradient: 4.86 -> 0.43 ms, against a chain per wave with the gates in LDS,
 // stored adjoints, and a GEMM over the stored pairs.  A round takes about 0.5 us
 // forward and 0.9 us reverse; the LDS reads of a round (each wave reads all
 // four states, repeated for its four row blocks) take half of that, the

@@ -16,9 +16,9 @@
 //     reverse sweep recomputes a segment from its checkpoint into the wave's
 //     LDS, applies b <- G^T b and accumulates dG_k += b f^T in per-lane
 //     registers, gate by gate, for the lanes that apply it.
-//   * Segments that all 64 words run through (the lengths of a tile are sorted)
-//     take their gate indices as one 8-byte load per lane, two segments ahead,
-//     and select no step.
+//   * Segments in which no word ends take their gate indices as one 8-byte load
+//     per lane, two segments ahead; those that all 64 words run through (the
+//     lengths of a tile are sorted) select no step.
 //   * At the end of a tile the wave adds its 64 lanes in a fixed butterfly
 //     order and writes the tile's row of partial sums (the slab layout of the
 //     other kernels), so a request's result does not depend on which wave ran
@@ -28,7 +28,7 @@
 // a step's latency counts: about 105 vector instructions (48 multiply-adds for
 // the three passes, 48 for the gradient, whose lanes are masked gate by gate)
 // and the LDS reads of three gates.  30,000 words of 256 steps: three gates 245 ->
-// 165 us, four gates 267 -> 174 us, against a kernel whose gates lay 16 doubles
+// 161 us, four gates 267 -> 172 us, against a kernel whose gates lay 16 doubles
 // apart (all on the same banks) and whose indices came byte by byte.  Loading the
 // reverse step's gate a step ahead too needs registers that spill at four gates
 // (296 us) and gains nothing at three (167 us).
@@ -116,11 +116,10 @@ __device__ __forceinline__ uint64_t load_pack(gbytes word, int t, int L, gbytes 
     __builtin_memcpy(&k, word + t, 8);
     return k;
   }
-  if (!__ballot(t < L && t + CL > L)) {
-    k = NONE * 0x0101010101010101ull;
-    if (t + CL <= L) __builtin_memcpy(&k, word + t, 8);
-    return k;
-  }
+  k = NONE * 0x0101010101010101ull;
+  if (t + CL <= L) __builtin_memcpy(&k, word + t, 8);
+  if (!__ballot(t < L && t + CL > L)) return k;
+  k = 0;
 #pragma unroll
   for (int x = 0; x < CL; ++x) {
     const bool in = t + x < L;
