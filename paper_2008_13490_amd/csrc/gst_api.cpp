@@ -466,6 +466,7 @@ struct gst_batch {
     int item_grid = 0, gemm_grid = 0, red_x = 0, red_stage1 = 1;
     gst::PlanBatch dev{};
   } pgroup[2];
+  std::vector<std::unique_ptr<DevBuf>> plan_ws;  // scratch of plan requests that could not get their own whole
   // one group of tiles per tile kernel (see TileKind), each with its own queue
   int n_tiles[6] = {0, 0, 0, 0, 0, 0}, grid_of[6] = {0, 0, 0, 0, 0, 0};
   gst::BatchLaunch launch[6] = {};
@@ -2133,6 +2134,22 @@ static int batch_enqueue(gst_batch* b, hipStream_t stream, bool eager) {
   return GST_OK;
 }
 
+// The scratch of a plan request in a batch: its own, which then never moves; where
+// there is no room for the whole of it, as much as this batch needs.
+static int batch_plan_ws(gst_batch* b, gst_req* r, size_t need, void** ws) {
+  const std::string err = g_err;
+  if (reserve_plan_ws(r) == GST_OK) {
+    *ws = r->ws.p;
+    return GST_OK;
+  }
+  (void)hipGetLastError();
+  g_err = err;
+  b->plan_ws.emplace_back(new DevBuf());
+  const int rc = b->plan_ws.back()->reserve(need, b->ctx->stream);
+  *ws = b->plan_ws.back()->p;
+  return rc;
+}
+
 int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gateset* thetas, double* const* probs,
                      double* const* objectives, double* const* grads, int capture_graph, gst_batch** out) {
   if (!ctx || !out || n < 0 || (n > 0 && (!reqs || !thetas))) return fail(GST_EINVAL, "NULL argument");
@@ -2246,6 +2263,7 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
   std::vector<PlanSetup> psetup[2];
   std::vector<int64_t> lvl_tab[2];
   std::vector<size_t> lvl_at[2];
+  std::vector<void*> ws_of[2];
   for (int gi = 0; gi < 2; ++gi) {
     gst_batch::PlanGroup& pg = b->pgroup[gi];
     pg.D = gi == 1 ? 16 : 4;
@@ -2258,8 +2276,10 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
       PlanSetup& st = psetup[gi][y];
       plan_setup(r, &b->thetas[x], b->objectives[x] ? gst::MODE_LOGLIK : gst::MODE_PROBS, nullptr, b->probs[x],
                  b->objectives[x], b->grads[x], nullptr, &st);
-      int rc = reserve_plan_ws(r);
+      void* ws = nullptr;
+      int rc = batch_plan_ws(b.get(), r, st.ws_bytes(), &ws);
       if (rc) return rc;
+      ws_of[gi].push_back(ws);
       lvl_at[gi].push_back(lvl_tab[gi].size());
       for (int l = 0; l <= P.n_levels; ++l) lvl_tab[gi].push_back(P.trunk_level_ptr[l]);
       for (int l = 0; l < P.n_levels; ++l) lvl_tab[gi].push_back(st.tb_at[l]);
@@ -2340,7 +2360,7 @@ int gst_batch_create(gst_ctx* ctx, int n, gst_req* const* reqs, const gst_gatese
       PlanSetup& st = psetup[gi][y];
       const int x = plan_x[gi][y];
       const int L = b->reqs[x]->plan.host.n_levels;
-      st.bind(b->reqs[x]->ws.p);
+      st.bind(ws_of[gi][y]);
       st.a.req_nonpos = reinterpret_cast<unsigned long long*>(base + o_np) + x;
       st.a.lvl_trunk = lvl + lvl_at[gi][y];
       st.a.lvl_head = lvl + lvl_at[gi][y] + (L + 1);
